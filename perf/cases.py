@@ -74,8 +74,10 @@ def _grid(rng, lo, hi, cells):
 
 
 def _ninecell(rng, big):
-    m = rng.choice([12, 24, 36, 48] if big else [12, 24, 36])
-    return dict(geom="ninecell", nx=m, ny=m, nz=32 * m // 3)
+    m = rng.choice([12, 16, 20, 24, 32, 40, 48] if big else [12, 16, 20, 24, 32])
+    # about 32/3 cells of length per cell of radius, in multiples that the levels halve
+    nz = {12: 128, 16: 168, 20: 208, 24: 256, 32: 336, 40: 416, 48: 512}[m]
+    return dict(geom="ninecell", nx=m, ny=m, nz=nz)
 
 
 def draw(rng):
