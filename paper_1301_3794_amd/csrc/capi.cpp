@@ -374,9 +374,9 @@ int dm_smooth(dm_op *op, int prec, int level, int n_sweeps, int reverse, const v
                 // the first colour of each component leaves the second's cross sums
                 const ClassList cl = L.cut_list(comp, col, (q % 2) == 0 ? kPairFirst : kPairSecond, op->cut_s);
                 if (prec == 64)
-                    launch_smooth<double>(L.g, L.coef64, op->sigma, comp, col, (const double *)f, (double *)x, s, cl);
+                    launch_smooth<double>(L.g, op->sigma, comp, (const double *)f, (double *)x, s, cl);
                 else
-                    launch_smooth<float>(L.g, L.coef32, (float)op->sigma, comp, col, (const float *)f, (float *)x, s, cl);
+                    launch_smooth<float>(L.g, (float)op->sigma, comp, (const float *)f, (float *)x, s, cl);
             }
         return DM_OK;
     });
@@ -931,8 +931,8 @@ static int time_kernel_impl(dm_op *op, int kernel, int prec, int level, int nrhs
                             const ClassList cl = kernel == DM_KERNEL_SMOOTH
                                                      ? L.cut_list(0, 0)
                                                      : L.cut_list(q / 2, q % 2, q % 2 ? kPairSecond : kPairFirst, op->cut_s);
-                            if (prec == 64) launch_smooth<double>(L.g, L.coef64, op->sigma, q / 2, q % 2, (double *)f, (double *)x, s, cl);
-                            else launch_smooth<float>(L.g, L.coef32, (float)op->sigma, q / 2, q % 2, (float *)f, (float *)x, s, cl);
+                            if (prec == 64) launch_smooth<double>(L.g, op->sigma, q / 2, (double *)f, (double *)x, s, cl);
+                            else launch_smooth<float>(L.g, (float)op->sigma, q / 2, (float *)f, (float *)x, s, cl);
                         }
                         break;
                     case DM_KERNEL_RESTRICT:
@@ -965,13 +965,13 @@ static int time_kernel_impl(dm_op *op, int kernel, int prec, int level, int nrhs
                 switch (kernel) {
                     case DM_KERNEL_APPLY:
                     case DM_KERNEL_RESIDUAL:
-                        launch_apply_b<T>(L.g, coef, (T)op->sigma, kernel == DM_KERNEL_APPLY ? AK_M : AK_RESID, nrhs,
+                        launch_apply_b<T>(L.g, (T)op->sigma, kernel == DM_KERNEL_APPLY ? AK_M : AK_RESID, nrhs,
                                           as_const(F), as_const(X), Y, s, L.cut_cells());
                         break;
                     case DM_KERNEL_SMOOTH:
                     case DM_KERNEL_SWEEP:
                         for (int q = 0; q < (kernel == DM_KERNEL_SMOOTH ? 1 : 6); ++q)
-                            launch_smooth_b<T>(L.g, coef, (T)op->sigma, q / 2, q % 2, nrhs, as_const(F), X, s,
+                            launch_smooth_b<T>(L.g, (T)op->sigma, q / 2, nrhs, as_const(F), X, s,
                                                kernel == DM_KERNEL_SMOOTH
                                                    ? L.cut_list(q / 2, q % 2)
                                                    : L.cut_list(q / 2, q % 2, q % 2 ? kPairSecond : kPairFirst, op->cut_s));

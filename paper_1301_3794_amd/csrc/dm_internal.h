@@ -325,17 +325,43 @@ __host__ __device__ inline VPtr<const T> as_const(const VPtr<T> &x) {
     return v;
 }
 
-// The non-vacuum (cut) rows of one smoother class as padded indices; with a
-// list the class update runs as two parts (see k_smooth_split).
+// Up to 64 consecutive cells of one colour in a grid row, for the smoother's
+// vacuum rows: lane l stands for padded index p + 2 l, and updates it where
+// bit l of the mask is set (the face there is a vacuum row of the class).
+// image: the run's faces (for component x its lane 0) have a PMC ghost image
+// two cells down their own axis, the only image a vacuum row can have (it
+// touches no symmetry plane).
+struct VacRun {
+    int32_t p, image;
+    uint64_t mask;
+};
+
+// Up to 64 consecutive cells of a grid row, for the cells of an apply or
+// residual without a cut row: lane l stands for padded index p + l, is
+// visited where bit l of `visit` is set (the cell is in the grid and not in
+// the cut-cell list), and its face of component c is active (a vacuum row)
+// where bit l of act[c] is.  pmc: bit 0, lanes 0 and 1 may have PMC ghost
+// images; bit 1, every lane may.
+struct CellRun {
+    int32_t p, pmc;
+    uint64_t visit, act[3];
+};
+
+// The rows of one smoother class (component and colour), or the cut cells of
+// an apply or residual.
 struct ClassList {
-    // smoother: the cut rows of one component, both colours, in index order;
-    // apply and residual: the cells with a cut row
+    // smoother: the component's cut (non-vacuum) rows as padded indices with
+    // the colour in the sign bit, both colours in index order; apply and
+    // residual: the cells with a cut row
     const int32_t *idx = nullptr;
     int64_t n = 0;
-    // for the smoother's vacuum part: the grid rows (k * ny + j) holding a
-    // vacuum row of any component; the colour sweep visits only these
-    const int32_t *rows = nullptr;
-    int64_t nrows = 0;
+    // apply and residual: the runs of the other cells, 2^run_log lanes per run
+    const CellRun *cells = nullptr;
+    int colour = 0;      // smoother: the class's colour
+    // smoother: the class's vacuum rows, 2^run_log lanes per run
+    const VacRun *runs = nullptr;
+    int64_t nruns = 0;   // runs, or cells
+    int run_log = 6;
     // block smoother: below this many listed rows each vector gets its own
     // wavefront, else one thread per row loops over the vectors
     int64_t wave_split_max = 65536;
@@ -381,11 +407,12 @@ struct Span {
 // with a cut-cell list (cells with an active non-vacuum row) the launch runs
 // as two parts, the listed cells and the vacuum-only rest (M and residual)
 template <class T>
-void launch_apply_b(const Grid &g, const T *coef, T sigma, int kind, int nr, const VPtr<const T> &f,
+void launch_apply_b(const Grid &g, T sigma, int kind, int nr, const VPtr<const T> &f,
                     const VPtr<const T> &x, const VPtr<T> &y, hipStream_t s, ClassList cut = {});
+// one class update: `cl` holds the class's rows (Level::cut_list)
 template <class T>
-void launch_smooth_b(const Grid &g, const T *coef, T sigma, int comp, int colour, int nr, const VPtr<const T> &f,
-                     const VPtr<T> &x, hipStream_t s, ClassList cut = {});
+void launch_smooth_b(const Grid &g, T sigma, int comp, int nr, const VPtr<const T> &f, const VPtr<T> &x,
+                     hipStream_t s, const ClassList &cl);
 // xz (optional, one coarse iterate per vector): set to zero in the same pass;
 // rows (optional): the coarse grid rows (k * ny + j) to visit, those holding
 // an active face (fc and xz stay zero on the others)
@@ -405,8 +432,7 @@ template <class T>
 void launch_apply(const Grid &g, const T *coef, T sigma, int kind, const T *f, const T *x, T *y,
                   hipStream_t s, ClassList cut = {});
 template <class T>
-void launch_smooth(const Grid &g, const T *coef, T sigma, int comp, int colour, const T *f, T *x,
-                   hipStream_t s, ClassList cut = {});
+void launch_smooth(const Grid &g, T sigma, int comp, const T *f, T *x, hipStream_t s, const ClassList &cl);
 template <class T>
 void launch_restrict(const Grid &gf, const Grid &gc, const T *coef_c, const T *r, T *fc,
                      hipStream_t s);
@@ -478,7 +504,7 @@ void launch_axpy(int64_t n, double a, const double *x, double *y, hipStream_t s)
 // widened before use, so y equals the product with the widened x; takes the
 // cut-cell list of the level (the split form), and with its rows leaves y
 // untouched on the other rows
-void launch_apply_m_f32in(const Grid &g, const double *coef, double sigma, int nr, const VPtr<const float> &x,
+void launch_apply_m_f32in(const Grid &g, double sigma, int nr, const VPtr<const float> &x,
                           const VPtr<double> &y, hipStream_t s, ClassList cut);
 void launch_axpby(int64_t n, double a, const double *x, double b, double *y, hipStream_t s);
 void launch_scale(int64_t n, double a, double *x, hipStream_t s);

@@ -55,13 +55,16 @@ __device__ inline int64_t wave_item(int &q) {
     return logical * 64 + (threadIdx.x & 63);
 }
 
+// item t (x fastest) -> cell; false past the grid.  A grid has fewer than 2^31
+// padded elements (checked when the operator is built), so the divisions are
+// 32-bit ones.
 __device__ inline bool cell_of(const Grid &g, int64_t t, int &i, int &j, int &k) {
-    const int64_t n = (int64_t)g.nx * g.ny * g.nz;
-    if (t >= n) return false;
-    i = (int)(t % g.nx);
-    const int64_t r = t / g.nx;
-    j = (int)(r % g.ny);
-    k = (int)(r / g.ny);
+    if (t >= (int64_t)g.nx * g.ny * g.nz) return false;
+    const uint32_t u = (uint32_t)t, nx = (uint32_t)g.nx, ny = (uint32_t)g.ny;
+    const uint32_t r = u / nx, kk = r / ny;
+    i = (int)(u - r * nx);
+    j = (int)(r - kk * ny);
+    k = (int)kk;
     return true;
 }
 
@@ -71,7 +74,8 @@ __device__ inline bool cell_of(const Grid &g, int64_t t, int &i, int &j, int &k)
 __device__ inline int64_t listed_item(const Grid &g, const int32_t *rows, int64_t nrows, int64_t t) {
     if (!rows) return t;
     if (t >= nrows * g.nx) return (int64_t)g.nx * g.ny * g.nz;
-    return (int64_t)rows[t / g.nx] * g.nx + t % g.nx;
+    const uint32_t u = (uint32_t)t, nx = (uint32_t)g.nx, r = u / nx;
+    return (int64_t)rows[r] * g.nx + (u - r * nx);
 }
 
 template <class T>
@@ -131,35 +135,51 @@ __device__ __forceinline__ void apply_body(const Grid &g, const Coefs<T> &c, T s
     put_face<T>(g, y + 2 * P, 2, i, j, k, p, yz);
 }
 
-// apply_body of M or the residual for the cells whose active rows are all
-// vacuum rows (the other cells are listed and run the full body): the same
-// values, written the same way, zeros on the inactive components included.
-// (K alone has no vacuum shortcut: its rows keep the cross terms.)
+// put_face from a padded index: the cell's coordinates are only worked out
+// where a PMC plane asks for ghost images
+template <class T>
+__device__ __forceinline__ void put_face_at(const Grid &g, T *arr, int comp, uint32_t p, T v) {
+    if (!g.pmc) {
+        arr[p] = v;
+        return;
+    }
+    const uint32_t sy = (uint32_t)g.sy, sz = (uint32_t)g.sz;
+    const uint32_t kk = p / sz, rr = p - kk * sz, jj = rr / sy;
+    put_face<T>(g, arr, comp, (int)(rr - jj * sy) - 1, (int)jj - 1, (int)kk - 1, (int64_t)p, v);
+}
+
+// apply_body of M or the residual for lane `lane` of a run of cells whose
+// active rows are all vacuum rows (the other cells are listed and run the
+// full body): the same values, written the same way, zeros on the inactive
+// components included.  (K alone has no vacuum shortcut: its rows keep the
+// cross terms.)
 template <class T, int KIND, class TX = T>
-__device__ __forceinline__ void apply_vac_body(const Grid &g, T sigma, uint8_t fl, const T *__restrict__ f,
-                                               const TX *__restrict__ x, T *__restrict__ y, int i, int j, int k,
-                                               int64_t p) {
+__device__ __forceinline__ void apply_vac_body(const Grid &g, T sigma, const CellRun &run, uint32_t lane,
+                                               const T *__restrict__ f, const TX *__restrict__ x,
+                                               T *__restrict__ y) {
     static_assert(KIND == AK_M || KIND == AK_RESID, "vacuum rows of M only");
     const int64_t P = g.P, dy = g.sy, dz = g.sz;
+    const uint32_t p = (uint32_t)run.p + lane;
     const T ih2 = inv_h2_of<T>(g);
     T v[3];
 #pragma unroll
     for (int comp = 0; comp < 3; ++comp) {
         const TX *C = x + comp * P;
         v[comp] = T(0);
-        if (fl & (kFaceActive << comp)) {
+        if ((run.act[comp] >> lane) & 1) {
             v[comp] = ih2 * vac_row<T, TX>(C, p, dy, dz) - sigma * T(C[p]);
             if (KIND == AK_RESID) v[comp] = f[comp * P + p] - v[comp];
         }
     }
-    put_face<T>(g, y, 0, i, j, k, p, v[0]);
-    put_face<T>(g, y + P, 1, i, j, k, p, v[1]);
-    put_face<T>(g, y + 2 * P, 2, i, j, k, p, v[2]);
-}
-
-// cells with an active non-vacuum row (those in the cut-cell list)
-__device__ inline bool has_cut_row(uint8_t fl) {
-    return ((fl & 7) & ~(fl >> 3)) != 0;
+    if ((run.pmc & 2) || (run.pmc && lane < 2)) {
+        put_face_at<T>(g, y, 0, p, v[0]);
+        put_face_at<T>(g, y + P, 1, p, v[1]);
+        put_face_at<T>(g, y + 2 * P, 2, p, v[2]);
+    } else {
+        y[p] = v[0];
+        (y + P)[p] = v[1];
+        (y + 2 * P)[p] = v[2];
+    }
 }
 
 template <class T, int KIND>
@@ -169,30 +189,11 @@ k_apply(Grid g, Coefs<T> c, T sigma, const T *__restrict__ f, const T *__restric
     apply_body<T, KIND>(g, c, sigma, f, x, y, xcd_item());
 }
 
-// Block forms of apply, restriction and prolongation: wave q of a workgroup
-// applies the one-vector body to vector q of the workgroup's 64 cells (see
-// wave_item), so every lane keeps the register budget of the one-vector
-// body.  (Looping over the vectors inside a thread kept every vector's loads
-// and addresses live at once: 170-240 VGPRs, two waves per SIMD; giving the
-// vectors to neighbouring lanes split every load of a wave over NR arrays.)
-
-template <class T, int KIND, int NR>
-__global__ void __launch_bounds__(kThreads)
-k_apply_b(Grid g, Coefs<T> c, T sigma, VPtr<const T> f, VPtr<const T> x, VPtr<T> y) {
-    int q;
-    const int64_t t = wave_item(q);
-    apply_body<T, KIND>(g, c, sigma, f.p[q], x.p[q], y.p[q], t);
-}
-
-// The block apply in two parts, as the smoother's class updates: the first
-// ncb workgroups (a multiple of 8) take the cut-cell list (full body), the
-// rest all cells, skipping listed ones (vacuum rows only); wave q of a
-// workgroup takes vector q of 64 entries in either part.
 // M x or f - M x at listed cell e (padded index p) from the cell's tabulated
 // rows W (3 x kCutW x ncut; see cut_term); inactive faces (a = 0) get 0
 template <class T, int KIND, class TX>
 __device__ __forceinline__ void apply_cut_tab(const Grid &g, T sigma, const T *__restrict__ W, int64_t ncut,
-                                              int64_t e, int64_t p, const T *__restrict__ f,
+                                              int64_t e, uint32_t p, const T *__restrict__ f,
                                               const TX *__restrict__ x, T *__restrict__ y) {
     const int64_t P = g.P, dy = g.sy, dz = g.sz;
     T v[3];
@@ -211,33 +212,41 @@ __device__ __forceinline__ void apply_cut_tab(const Grid &g, T sigma, const T *_
             v[comp] = KIND == AK_RESID ? f[comp * P + p] - row : row;
         }
     }
-    const int64_t kk = p / dz, rr = p - kk * dz, jj = rr / dy;
-    const int i = (int)(rr - jj * dy) - 1, j = (int)jj - 1, k = (int)kk - 1;
-    put_face<T>(g, y, 0, i, j, k, p, v[0]);
-    put_face<T>(g, y + P, 1, i, j, k, p, v[1]);
-    put_face<T>(g, y + 2 * P, 2, i, j, k, p, v[2]);
+    put_face_at<T>(g, y, 0, p, v[0]);
+    put_face_at<T>(g, y + P, 1, p, v[1]);
+    put_face_at<T>(g, y + 2 * P, 2, p, v[2]);
 }
 
+// Block forms of apply, restriction and prolongation: wave q of a workgroup
+// applies the one-vector body to vector q of the workgroup's 64 cells (see
+// wave_item), so every lane keeps the register budget of the one-vector
+// body.  (Looping over the vectors inside a thread kept every vector's loads
+// and addresses live at once: 170-240 VGPRs, two waves per SIMD; giving the
+// vectors to neighbouring lanes split every load of a wave over NR arrays.)
+
+// The block apply in two parts, as the smoother's class updates: the first
+// ncb workgroups (a multiple of 8) take the cut-cell list (full body), the
+// rest all cells, skipping listed ones (vacuum rows only); wave q of a
+// workgroup takes vector q of 64 entries in either part.
 template <class T, int KIND, int NR, class TX = T>
 __global__ void __launch_bounds__(kThreads)
-k_apply_split(Grid g, Coefs<T> c, T sigma, const int32_t *__restrict__ cut, int64_t ncut, int64_t ncb,
-              const T *__restrict__ W, const int32_t *__restrict__ rows, int64_t nrows, VPtr<const T> f,
-              VPtr<const TX> x, VPtr<T> y) {
-    const int64_t b = blockIdx.x;
+k_apply_split(Grid g, T sigma, const int32_t *__restrict__ cut, int64_t ncut, uint32_t ncb, const T *__restrict__ W,
+              const CellRun *__restrict__ cells, uint32_t nruns, int run_log, VPtr<const T> f, VPtr<const TX> x,
+              VPtr<T> y) {
+    const uint32_t b = blockIdx.x;
     const int q = threadIdx.x >> 6;
     if (b < ncb) {
-        const int64_t e = ((b % kXcd) * (ncb / kXcd) + b / kXcd) * 64 + (threadIdx.x & 63);
+        const uint32_t e = ((b % kXcd) * (ncb / kXcd) + b / kXcd) * 64 + (threadIdx.x & 63);
         if (e >= ncut) return;
-        apply_cut_tab<T, KIND, TX>(g, sigma, W, ncut, e, cut[e], f.p[q], x.p[q], y.p[q]);
+        apply_cut_tab<T, KIND, TX>(g, sigma, W, ncut, e, (uint32_t)cut[e], f.p[q], x.p[q], y.p[q]);
     } else {
-        const int64_t bv = b - ncb, nvb = (int64_t)gridDim.x - ncb;
-        const int64_t t = ((bv % kXcd) * (nvb / kXcd) + bv / kXcd) * 64 + (threadIdx.x & 63);
-        int i, j, k;
-        if (!cell_of(g, listed_item(g, rows, nrows, t), i, j, k)) return;
-        const int64_t p = pidx(g, i, j, k);
-        const uint8_t fl = c.flags[p];
-        if (has_cut_row(fl)) return;
-        apply_vac_body<T, KIND, TX>(g, sigma, fl, f.p[q], x.p[q], y.p[q], i, j, k, p);
+        const uint32_t bv = b - ncb, nvb = gridDim.x - ncb;
+        const uint32_t t = ((bv % kXcd) * (nvb / kXcd) + bv / kXcd) * 64 + (threadIdx.x & 63);
+        if (t >> run_log >= nruns) return;
+        const CellRun run = cells[t >> run_log];
+        const uint32_t lane = t & ((1u << run_log) - 1);
+        if (!((run.visit >> lane) & 1)) return;
+        apply_vac_body<T, KIND, TX>(g, sigma, run, lane, f.p[q], x.p[q], y.p[q]);
     }
 }
 
@@ -304,27 +313,31 @@ __device__ __forceinline__ void smooth_body_n(const Grid &g, const Coefs<T> &c, 
     for (int q = 0; q < NR; ++q) put_face<T>(g, x.p[q] + COMP * P, COMP, i, j, k, p, nv[q]);
 }
 
-// The two parts of a class update when the class's cut rows are listed:
-// smooth_vac_n updates the vacuum rows of the colour sweep and skips every
-// other row; smooth_cut_n updates entry e of the list of the class's
+// The two parts of a class update: smooth_vac_n updates the class's vacuum
+// rows from their runs, smooth_cut_n entry e of the component's list of
 // non-vacuum rows.  Rows of one class do not read each other, so the parts
-// may run in any order; separating them keeps the waves of the colour sweep
-// on the short vacuum path (a cut row in a wave made the whole wave take
-// the long path as well).
+// may run in any order; separating them keeps the waves of the vacuum part
+// on the short path (a cut row in a wave made the whole wave take the long
+// path as well).
+//
+// Below the finest level a class update is bound by its launch (1.85 us for
+// an empty node of a graph) and the latency of its dependent loads, so both
+// parts keep that chain at two: the run (or the listed index), then
+// everything else at once.  Walking listed grid rows instead (row number,
+// then the cell's class byte, then the values, with 64-bit divisions in
+// between) took 2.98 us per launch on the 32^3 level of one vector's V-cycle
+// and 516 us for the whole V-cycle at 128^3; the runs take 2.67 and 476 us.
 template <class T, int COMP, int NR>
-__device__ __forceinline__ void smooth_vac_n(const Grid &g, const Coefs<T> &c, T sigma, int colour,
-                                             const VPtr<const T> &f, const VPtr<T> &x, int64_t t,
-                                             const int32_t *__restrict__ rows, int64_t nrows) {
-    const int nxh = (g.nx + 1) >> 1;
-    if (t >= (rows ? nrows : (int64_t)g.ny * g.nz) * nxh) return;
-    const int ih = (int)(t % nxh);
-    const int64_t r = rows ? (int64_t)rows[t / nxh] : t / nxh;
-    const int j = (int)(r % g.ny), k = (int)(r / g.ny);
-    const int i = 2 * ih + ((j + k + colour) & 1);
-    if (i >= g.nx) return;
+__device__ __forceinline__ void smooth_vac_n(const Grid &g, T sigma, const VPtr<const T> &f, const VPtr<T> &x,
+                                             uint32_t t, const VacRun *__restrict__ runs, uint32_t nruns,
+                                             int run_log) {
+    const uint32_t r = t >> run_log;
+    if (r >= nruns) return;
+    const VacRun run = runs[r];
+    const uint32_t lane = t & ((1u << run_log) - 1);
+    if (!((run.mask >> lane) & 1)) return;
     const int64_t P = g.P, dy = g.sy, dz = g.sz;
-    const int64_t p = pidx(g, i, j, k);
-    if (!(c.flags[p] & (kFaceVacuum << COMP))) return;
+    const uint32_t p = (uint32_t)run.p + 2 * lane;
     const T ih2 = inv_h2_of<T>(g);
     const T d = T(6) * ih2 - sigma;
     T nv[NR];
@@ -336,35 +349,42 @@ __device__ __forceinline__ void smooth_vac_n(const Grid &g, const Coefs<T> &c, T
         nv[q] = xp + (f.p[q][COMP * P + p] - row) / d;
     }
 #pragma unroll
-    for (int q = 0; q < NR; ++q) put_face<T>(g, x.p[q] + COMP * P, COMP, i, j, k, p, nv[q]);
+    for (int q = 0; q < NR; ++q) (x.p[q] + COMP * P)[p] = nv[q];
+    if (run.image && (COMP != 0 || lane == 0)) {
+        const int64_t off = COMP * P - 2 * (COMP == 0 ? 1 : COMP == 1 ? dy : dz);
+#pragma unroll
+        for (int q = 0; q < NR; ++q) (x.p[q] + off)[p] = nv[q];
+    }
 }
 
-// entry e of the component's cut list (both colours, index order) from its
-// tabulated row W (kCutW x ncut, term-major; see cut_term), for the update of
-// colour `colour` paired as `pair` says (see ClassList): the row is
+// entry e of the component's cut list (n entries, the colour in the sign bit)
+// from its tabulated row W (kCutW x n, term-major; see cut_term), for the
+// update of colour `colour` paired as `pair` says (see ClassList): the row is
 // -sigma a x_f + (own-component terms) + (cross-component terms), the latter
-// summed first, inline or taken from S (ncut per vector, vector q0 + q);
-// the weights are loaded once for the NR vectors
+// summed first, inline or taken from S (n per vector, vector q0 + q).  The
+// weights are loaded once for the NR vectors, those that every entry takes
+// before the index they do not depend on.  (The list keeps both colours in
+// index order: sorted by colour, the first update of a pair walked the
+// surface twice, 16.5 -> 21.5 us per launch at 128^3 for 3 vectors.)
 template <class T, int COMP, int NR>
-__device__ __forceinline__ void smooth_cut_n(const Grid &g, T sigma, const int32_t *__restrict__ cut, int64_t ncut,
-                                             const T *__restrict__ W, int colour, int pair, T *__restrict__ S,
-                                             int q0, const VPtr<const T> &f, const VPtr<T> &x, int64_t e) {
-    if (e >= ncut) return;
+__device__ __forceinline__ void smooth_cut_n(const Grid &g, T sigma, const int32_t *__restrict__ cut, int64_t n,
+                                             int colour, const T *__restrict__ W, int pair, T *__restrict__ S,
+                                             int q0, const VPtr<const T> &f, const VPtr<T> &x, uint32_t e) {
     const int64_t P = g.P, dy = g.sy, dz = g.sz;
-    const int64_t p = cut[e];
-    const int64_t kk = p / dz, rr = p - kk * dz, jj = rr / dy;
-    const int i = (int)(rr - jj * dy) - 1, j = (int)jj - 1, k = (int)kk - 1;
-    const bool mine = ((i + j + k) & 1) == colour;
+    T w[kCutTerms], cross[NR];
+    const int32_t ce = cut[e];
+    if (pair != kPairSecond) {
+#pragma unroll
+        for (int t = kCutOwn; t < kCutTerms; ++t) w[t] = W[t * n + e];
+    }
+    const uint32_t p = (uint32_t)ce & 0x7fffffffu;
     // the other colour's rows: nothing, or (first of a pair) their cross sums
+    const bool mine = (ce < 0) == (colour != 0);
     if (!mine && pair != kPairFirst) return;
-    T cross[NR];
     if (pair == kPairSecond) {
 #pragma unroll
-        for (int q = 0; q < NR; ++q) cross[q] = S[(int64_t)(q0 + q) * ncut + e];
+        for (int q = 0; q < NR; ++q) cross[q] = S[(int64_t)(q0 + q) * n + e];
     } else {
-        T w[kCutTerms - kCutOwn];
-#pragma unroll
-        for (int t = kCutOwn; t < kCutTerms; ++t) w[t - kCutOwn] = W[t * ncut + e];
 #pragma unroll
         for (int q = 0; q < NR; ++q) {
             const T *X = x.p[q];
@@ -372,37 +392,36 @@ __device__ __forceinline__ void smooth_cut_n(const Grid &g, T sigma, const int32
 #pragma unroll
             for (int t = kCutOwn; t < kCutTerms; ++t) {
                 const CutTerm ct = cut_term(COMP, t);
-                c += w[t - kCutOwn] * X[ct.comp * P + p + ct.di + ct.dj * dy + ct.dk * dz];
+                c += w[t] * (X + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz))[p];
             }
             cross[q] = c;
         }
         if (!mine) {
 #pragma unroll
-            for (int q = 0; q < NR; ++q) S[(int64_t)(q0 + q) * ncut + e] = cross[q];
+            for (int q = 0; q < NR; ++q) S[(int64_t)(q0 + q) * n + e] = cross[q];
             return;
         }
     }
-    T w[kCutOwn];
 #pragma unroll
-    for (int t = 0; t < kCutOwn; ++t) w[t] = W[t * ncut + e];
-    const T a = W[kCutTerms * ncut + e];
-    const T d = W[(kCutTerms + 1) * ncut + e] - sigma * a;
+    for (int t = 0; t < kCutOwn; ++t) w[t] = W[t * n + e];
+    const T a = W[kCutTerms * n + e];
+    const T d = W[(kCutTerms + 1) * n + e] - sigma * a;
     T nv[NR];
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
         const T *X = x.p[q];
-        const T xs = X[COMP * P + p];
+        const T xs = (X + COMP * P)[p];
         T row = -sigma * a * xs;
 #pragma unroll
         for (int t = 0; t < kCutOwn; ++t) {
             const CutTerm ct = cut_term(COMP, t);
-            row += w[t] * X[ct.comp * P + p + ct.di + ct.dj * dy + ct.dk * dz];
+            row += w[t] * (X + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz))[p];
         }
         row += cross[q];
-        nv[q] = xs + (f.p[q][COMP * P + p] - row) / d;
+        nv[q] = xs + ((f.p[q] + COMP * P)[p] - row) / d;
     }
 #pragma unroll
-    for (int q = 0; q < NR; ++q) put_face<T>(g, x.p[q] + COMP * P, COMP, i, j, k, p, nv[q]);
+    for (int q = 0; q < NR; ++q) put_face_at<T>(g, x.p[q] + COMP * P, COMP, p, nv[q]);
 }
 
 template <class T, int COMP>
@@ -411,46 +430,45 @@ __device__ __forceinline__ void smooth_body(const Grid &g, const Coefs<T> &c, T 
     smooth_body_n<T, COMP, 1>(g, c, sigma, colour, vptr1(f), vptr1(x), t);
 }
 
-template <class T, int COMP>
-__global__ void __launch_bounds__(kThreads)
-k_smooth(Grid g, Coefs<T> c, T sigma, int colour, const T *__restrict__ f, T *__restrict__ x) {
-    smooth_body<T, COMP>(g, c, sigma, colour, f, x, xcd_item());
-}
-
-template <class T, int COMP, int NR>
-__global__ void __launch_bounds__(kThreads)
-k_smooth_b(Grid g, Coefs<T> c, T sigma, int colour, VPtr<const T> f, VPtr<T> x) {
-    smooth_body_n<T, COMP, NR>(g, c, sigma, colour, f, x, xcd_item());
-}
-
 // A class update from its two parts: the first ncb workgroups (a multiple of
-// 8) take the cut-row list, the rest the vacuum rows of the colour sweep;
-// each part maps its workgroups to the XCDs as xcd_item does.  With several
-// vectors and a short list (wave_split) a cut workgroup takes 64 rows, wave
-// q the vector q: the cut rows are latency-bound, and one thread per row and
-// vector keeps more of them in flight (the waves share the rows' coefficient
-// lines in cache); a long list fills the GPU with one thread per row looping
-// over the vectors, which reuses the coefficients in registers.
+// 8) take the cut rows, the rest the vacuum runs; each part maps its
+// workgroups to the XCDs as xcd_item does.  With several vectors and a short list
+// (wave_split) a cut workgroup takes 64 rows, wave q the vector q: the cut
+// rows are latency-bound, and one thread per row and vector keeps more of
+// them in flight (the waves share the rows' coefficient lines in cache); a
+// long list fills the GPU with one thread per row looping over the vectors,
+// which reuses the coefficients in registers.
+template <class T>
+struct SmoothArgs {
+    const int32_t *cut;
+    const T *W;
+    T *S;
+    const VacRun *runs;
+    int64_t n;
+    uint32_t nruns, ncb;
+    int run_log, colour, pair, wave_split;
+};
+
 template <class T, int COMP, int NR>
 __global__ void __launch_bounds__(kThreads)
-k_smooth_split(Grid g, Coefs<T> c, T sigma, int colour, const int32_t *__restrict__ cut, int64_t ncut, int64_t ncb,
-               int wave_split, const T *__restrict__ W, int pair, T *__restrict__ S,
-               const int32_t *__restrict__ rows, int64_t nrows, VPtr<const T> f, VPtr<T> x) {
-    const int64_t b = blockIdx.x;
-    if (b < ncb) {
-        const int64_t L = (b % kXcd) * (ncb / kXcd) + b / kXcd;
-        if (!wave_split) {
-            smooth_cut_n<T, COMP, NR>(g, sigma, cut, ncut, W, colour, pair, S, 0, f, x, L * kThreads + threadIdx.x);
+k_smooth_split(Grid g, T sigma, SmoothArgs<T> A, VPtr<const T> f, VPtr<T> x) {
+    const uint32_t b = blockIdx.x;
+    if (b < A.ncb) {
+        const uint32_t L = (b % kXcd) * (A.ncb / kXcd) + b / kXcd;
+        if (!A.wave_split) {
+            const uint32_t e = L * kThreads + threadIdx.x;
+            if (e < A.n) smooth_cut_n<T, COMP, NR>(g, sigma, A.cut, A.n, A.colour, A.W, A.pair, A.S, 0, f, x, e);
         } else {
             const int q = threadIdx.x >> 6;
-            if (q >= NR) return;
-            smooth_cut_n<T, COMP, 1>(g, sigma, cut, ncut, W, colour, pair, S, q, vptr1(f.p[q]), vptr1(x.p[q]),
-                                     L * 64 + (threadIdx.x & 63));
+            const uint32_t e = L * 64 + (threadIdx.x & 63);
+            if (q < NR && e < A.n)
+                smooth_cut_n<T, COMP, 1>(g, sigma, A.cut, A.n, A.colour, A.W, A.pair, A.S, q, vptr1(f.p[q]),
+                                         vptr1(x.p[q]), e);
         }
     } else {
-        const int64_t bv = b - ncb, nvb = (int64_t)gridDim.x - ncb;
-        const int64_t L = (bv % kXcd) * (nvb / kXcd) + bv / kXcd;
-        smooth_vac_n<T, COMP, NR>(g, c, sigma, colour, f, x, L * kThreads + threadIdx.x, rows, nrows);
+        const uint32_t bv = b - A.ncb, nvb = gridDim.x - A.ncb;
+        const uint32_t L = (bv % kXcd) * (nvb / kXcd) + bv / kXcd;
+        smooth_vac_n<T, COMP, NR>(g, sigma, f, x, L * kThreads + threadIdx.x, A.runs, A.nruns, A.run_log);
     }
 }
 
@@ -732,9 +750,10 @@ __device__ __forceinline__ void s_smooth_body(const Grid &g, const Coefs<T> &c, 
                                               const int32_t *__restrict__ rows = nullptr, int64_t nrows = 0) {
     const int nxh = (g.nx + 1) >> 1;
     if (t >= (rows ? nrows : (int64_t)g.ny * g.nz) * nxh) return;
-    const int ih = (int)(t % nxh);
-    const int64_t r = rows ? (int64_t)rows[t / nxh] : t / nxh;
-    const int j = (int)(r % g.ny), k = (int)(r / g.ny);
+    const uint32_t u = (uint32_t)t, ur = u / (uint32_t)nxh, r = rows ? (uint32_t)rows[ur] : ur;
+    const int ih = (int)(u - ur * nxh);
+    const uint32_t kk = r / (uint32_t)g.ny;
+    const int j = (int)(r - kk * g.ny), k = (int)kk;
     const int i = 2 * ih + ((j + k + colour) & 1);
     if (i >= g.nx) return;
     const int64_t dy = g.sy, dz = g.sz, p = pidx(g, i, j, k);
@@ -1661,18 +1680,12 @@ inline dim3 flat_grid(int64_t n) {
 template <class T>
 void launch_apply(const Grid &g, const T *coef, T sigma, int kind, const T *f, const T *x, T *y,
                   hipStream_t s, ClassList cut) {
-    if (cut.idx && (kind == AK_M || kind == AK_RESID)) {
-        launch_apply_b<T>(g, coef, sigma, kind, 1, vptr1(f), vptr1(x), vptr1(y), s, cut);
+    if (kind == AK_M || kind == AK_RESID) {
+        launch_apply_b<T>(g, sigma, kind, 1, vptr1(f), vptr1(x), vptr1(y), s, cut);
         return;
     }
     const int64_t n = (int64_t)g.nx * g.ny * g.nz;
-    Coefs<T> c = coefs_of(coef, g.P);
-    if (kind == AK_M)
-        hipLaunchKernelGGL((k_apply<T, AK_M>), xcd_grid(n), dim3(kThreads), 0, s, g, c, sigma, f, x, y);
-    else if (kind == AK_K)
-        hipLaunchKernelGGL((k_apply<T, AK_K>), xcd_grid(n), dim3(kThreads), 0, s, g, c, sigma, f, x, y);
-    else
-        hipLaunchKernelGGL((k_apply<T, AK_RESID>), xcd_grid(n), dim3(kThreads), 0, s, g, c, sigma, f, x, y);
+    hipLaunchKernelGGL((k_apply<T, AK_K>), xcd_grid(n), dim3(kThreads), 0, s, g, coefs_of(coef, g.P), sigma, f, x, y);
 }
 
 template <class T>
@@ -1686,24 +1699,8 @@ void launch_apply_A(const Grid &g, const double *coef, const double *x, double *
 }
 
 template <class T>
-void launch_smooth(const Grid &g, const T *coef, T sigma, int comp, int colour, const T *f, T *x,
-                   hipStream_t s, ClassList cut) {
-    if (cut.idx) {
-        VPtr<const T> F{};
-        VPtr<T> X{};
-        F.p[0] = f;
-        X.p[0] = x;
-        launch_smooth_b<T>(g, coef, sigma, comp, colour, 1, F, X, s, cut);
-        return;
-    }
-    const int64_t n = (int64_t)((g.nx + 1) >> 1) * g.ny * g.nz;
-    Coefs<T> c = coefs_of(coef, g.P);
-    if (comp == 0)
-        hipLaunchKernelGGL((k_smooth<T, 0>), xcd_grid(n), dim3(kThreads), 0, s, g, c, sigma, colour, f, x);
-    else if (comp == 1)
-        hipLaunchKernelGGL((k_smooth<T, 1>), xcd_grid(n), dim3(kThreads), 0, s, g, c, sigma, colour, f, x);
-    else
-        hipLaunchKernelGGL((k_smooth<T, 2>), xcd_grid(n), dim3(kThreads), 0, s, g, c, sigma, colour, f, x);
+void launch_smooth(const Grid &g, T sigma, int comp, const T *f, T *x, hipStream_t s, const ClassList &cl) {
+    launch_smooth_b<T>(g, sigma, comp, 1, vptr1(f), vptr1(x), s, cl);
 }
 
 template <class T>
@@ -1722,12 +1719,6 @@ void launch_prolong_add(const Grid &gf, const Grid &gc, const T *coef_f, const T
                        coefs_of(coef_f, gf.P), coefs_of(coef_c, gc.P), xc, x);
 }
 
-// cut rows of a component (both colours) below which the block smoother
-// gives each vector its own wave: ClassList::wave_split_max, an operator
-// option (default 65536, measured on the 128^3 sphere: ~60k rows per colour
-// on the finest level favour the in-thread loop, ~15k rows on the next the
-// waves)
-
 // ---- block forms: dispatch nr (1..kMaxRhs) to the template
 #define DM_NR_SWITCH(nr, CALL)                      \
     switch (nr) {                                   \
@@ -1739,89 +1730,61 @@ void launch_prolong_add(const Grid &gf, const Grid &gc, const T *coef_f, const T
     }
 
 template <class T>
-void launch_apply_b(const Grid &g, const T *coef, T sigma, int kind, int nr, const VPtr<const T> &f,
+void launch_apply_b(const Grid &g, T sigma, int kind, int nr, const VPtr<const T> &f,
                     const VPtr<const T> &x, const VPtr<T> &y, hipStream_t s, ClassList cut) {
-    const int64_t n = (int64_t)g.nx * g.ny * g.nz;
-    const Coefs<T> c = coefs_of(coef, g.P);
-    if (cut.idx && (kind == AK_M || kind == AK_RESID)) {
-        if (cut.n > 0 && !cut_weights<T>(cut)) throw std::runtime_error("apply: cut-cell list without its row table");
-        // the vacuum part visits the listed grid rows (every row without a list)
-        const int64_t ncb = ceil_div(ceil_div(cut.n, 64), kXcd) * kXcd;
-        const int64_t nvac = cut.rows ? cut.nrows * g.nx : n;
-        const int64_t nvb = ceil_div(ceil_div(nvac, 64), kXcd) * kXcd;
-        const dim3 grid((unsigned)(ncb + nvb));
-        if (kind == AK_M)
-            DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<T, AK_M, NR>), grid, dim3(64 * NR), 0, s, g, c, sigma,
-                                                cut.idx, cut.n, ncb, cut_weights<T>(cut), cut.rows, cut.nrows, f, x, y))
-        else
-            DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<T, AK_RESID, NR>), grid, dim3(64 * NR), 0, s, g, c,
-                                                sigma, cut.idx, cut.n, ncb, cut_weights<T>(cut), cut.rows, cut.nrows, f, x, y))
-        return;
-    }
+    if (kind != AK_M && kind != AK_RESID) throw std::runtime_error("block apply: M or residual only");
+    if (cut.n > 0 && !cut_weights<T>(cut)) throw std::runtime_error("apply: cut-cell list without its row table");
+    const uint32_t ncb = (uint32_t)(ceil_div(ceil_div(cut.n, 64), kXcd) * kXcd);
+    const int64_t nvb = ceil_div(ceil_div(cut.nruns << cut.run_log, 64), kXcd) * kXcd;
+    const dim3 grid((unsigned)(ncb + nvb));
     if (kind == AK_M)
-        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_b<T, AK_M, NR>), xcd_grid_waves(n), dim3(64 * NR), 0, s, g, c,
-                                            sigma, f, x, y))
-    else if (kind == AK_RESID)
-        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_b<T, AK_RESID, NR>), xcd_grid_waves(n), dim3(64 * NR), 0, s, g,
-                                            c, sigma, f, x, y))
+        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<T, AK_M, NR>), grid, dim3(64 * NR), 0, s, g, sigma, cut.idx,
+                                            cut.n, ncb, cut_weights<T>(cut), cut.cells, (uint32_t)cut.nruns,
+                                            cut.run_log, f, x, y))
     else
-        throw std::runtime_error("block apply: M or residual only");
+        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<T, AK_RESID, NR>), grid, dim3(64 * NR), 0, s, g, sigma,
+                                            cut.idx, cut.n, ncb, cut_weights<T>(cut), cut.cells, (uint32_t)cut.nruns,
+                                            cut.run_log, f, x, y))
 }
 
-void launch_apply_m_f32in(const Grid &g, const double *coef, double sigma, int nr, const VPtr<const float> &x,
+void launch_apply_m_f32in(const Grid &g, double sigma, int nr, const VPtr<const float> &x,
                          const VPtr<double> &y, hipStream_t s, ClassList cut) {
-    // the split form; without cut cells (no list) every cell takes the vacuum part
-    if (!cut.idx && cut.n != 0) throw std::runtime_error("apply with FP32 input: cut-cell list missing");
     if (cut.n > 0 && !cut.w64) throw std::runtime_error("apply: cut-cell list without its row table");
-    const int64_t n = (int64_t)g.nx * g.ny * g.nz;
-    const Coefs<double> c = coefs_of(coef, g.P);
-    const int64_t ncb = cut.idx ? ceil_div(ceil_div(cut.n, 64), kXcd) * kXcd : 0;
-    const int64_t nvac = cut.rows ? cut.nrows * g.nx : n;
-    const int64_t nvb = ceil_div(ceil_div(nvac, 64), kXcd) * kXcd;
+    const uint32_t ncb = (uint32_t)(ceil_div(ceil_div(cut.n, 64), kXcd) * kXcd);
+    const int64_t nvb = ceil_div(ceil_div(cut.nruns << cut.run_log, 64), kXcd) * kXcd;
     const dim3 grid((unsigned)(ncb + nvb));
     const VPtr<const double> f{};
-    DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<double, AK_M, NR, float>), grid, dim3(64 * NR), 0, s, g, c,
-                                        sigma, cut.idx, cut.n, ncb, cut_weights<double>(cut), cut.rows, cut.nrows, f, x, y))
+    DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<double, AK_M, NR, float>), grid, dim3(64 * NR), 0, s, g, sigma,
+                                        cut.idx, cut.n, ncb, cut_weights<double>(cut), cut.cells, (uint32_t)cut.nruns,
+                                        cut.run_log, f, x, y))
 }
 
 template <class T>
-void launch_smooth_b(const Grid &g, const T *coef, T sigma, int comp, int colour, int nr, const VPtr<const T> &f,
-                     const VPtr<T> &x, hipStream_t s, ClassList cut) {
-    const int64_t n = (int64_t)((g.nx + 1) >> 1) * g.ny * g.nz;
-    const Coefs<T> c = coefs_of(coef, g.P);
-    if (cut.idx) {
-        if (cut.n > 0 && !cut_weights<T>(cut)) throw std::runtime_error("smoother: cut list without its row table");
-        if (cut.pair != kPairNone && !cut.s) throw std::runtime_error("smoother: paired update without its sums");
-        T *S = static_cast<T *>(cut.s);
-        const int wave_split = nr > 1 && cut.n < cut.wave_split_max;
-        const int64_t ncb = ceil_div(ceil_div(cut.n, wave_split ? 64 : kThreads), kXcd) * kXcd;
-        // the vacuum part sweeps the listed rows (every row without a list)
-        const int64_t nvac = cut.rows ? cut.nrows * ((g.nx + 1) >> 1) : n;
-        const int64_t nvb = ceil_div(ceil_div(nvac, kThreads), kXcd) * kXcd;
-        const dim3 grid((unsigned)(ncb + nvb));
-        if (comp == 0)
-            DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_smooth_split<T, 0, NR>), grid, dim3(kThreads), 0, s, g, c, sigma,
-                                                colour, cut.idx, cut.n, ncb, wave_split, cut_weights<T>(cut), cut.pair,
-                                                S, cut.rows, cut.nrows, f, x))
-        else if (comp == 1)
-            DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_smooth_split<T, 1, NR>), grid, dim3(kThreads), 0, s, g, c, sigma,
-                                                colour, cut.idx, cut.n, ncb, wave_split, cut_weights<T>(cut), cut.pair,
-                                                S, cut.rows, cut.nrows, f, x))
-        else
-            DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_smooth_split<T, 2, NR>), grid, dim3(kThreads), 0, s, g, c, sigma,
-                                                colour, cut.idx, cut.n, ncb, wave_split, cut_weights<T>(cut), cut.pair,
-                                                S, cut.rows, cut.nrows, f, x))
-        return;
-    }
+void launch_smooth_b(const Grid &g, T sigma, int comp, int nr, const VPtr<const T> &f, const VPtr<T> &x,
+                     hipStream_t s, const ClassList &cl) {
+    if (cl.n > 0 && !cut_weights<T>(cl)) throw std::runtime_error("smoother: cut list without its row table");
+    if (cl.pair != kPairNone && !cl.s) throw std::runtime_error("smoother: paired update without its sums");
+    SmoothArgs<T> A;
+    A.cut = cl.idx;
+    A.W = cut_weights<T>(cl);
+    A.S = static_cast<T *>(cl.s);
+    A.runs = cl.runs;
+    A.n = cl.n;
+    A.colour = cl.colour;
+    A.nruns = (uint32_t)cl.nruns;
+    A.run_log = cl.run_log;
+    A.pair = cl.pair;
+    A.wave_split = nr > 1 && cl.n < cl.wave_split_max;
+    A.ncb = (uint32_t)(ceil_div(ceil_div(cl.n, A.wave_split ? 64 : kThreads), kXcd) * kXcd);
+    const int64_t nvb = ceil_div(ceil_div(cl.nruns << cl.run_log, kThreads), kXcd) * kXcd;
+    const dim3 grid((unsigned)(A.ncb + nvb));
+    if (grid.x == 0) return;   // no active face of the class on this level
     if (comp == 0)
-        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_smooth_b<T, 0, NR>), xcd_grid(n), dim3(kThreads), 0, s, g, c, sigma,
-                                            colour, f, x))
+        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_smooth_split<T, 0, NR>), grid, dim3(kThreads), 0, s, g, sigma, A, f, x))
     else if (comp == 1)
-        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_smooth_b<T, 1, NR>), xcd_grid(n), dim3(kThreads), 0, s, g, c, sigma,
-                                            colour, f, x))
+        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_smooth_split<T, 1, NR>), grid, dim3(kThreads), 0, s, g, sigma, A, f, x))
     else
-        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_smooth_b<T, 2, NR>), xcd_grid(n), dim3(kThreads), 0, s, g, c, sigma,
-                                            colour, f, x))
+        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_smooth_split<T, 2, NR>), grid, dim3(kThreads), 0, s, g, sigma, A, f, x))
 }
 
 template <class T>
@@ -2306,10 +2269,10 @@ template void launch_add_scaled_a<float>(int64_t, const float *, const float *, 
 
 // explicit instantiations
 #define DM_BLOCK_INST(T)                                                                                   \
-    template void launch_apply_b<T>(const Grid &, const T *, T, int, int, const VPtr<const T> &,                 \
+    template void launch_apply_b<T>(const Grid &, T, int, int, const VPtr<const T> &,                            \
                                     const VPtr<const T> &, const VPtr<T> &, hipStream_t, ClassList);              \
-    template void launch_smooth_b<T>(const Grid &, const T *, T, int, int, int, const VPtr<const T> &,           \
-                                     const VPtr<T> &, hipStream_t, ClassList);                                    \
+    template void launch_smooth_b<T>(const Grid &, T, int, int, const VPtr<const T> &, const VPtr<T> &,          \
+                                     hipStream_t, const ClassList &);                                             \
     template void launch_restrict_b<T>(const Grid &, const Grid &, const T *, int, const VPtr<const T> &,        \
                                        const VPtr<T> &, hipStream_t, const VPtr<T> &, const int32_t *, int64_t);                                             \
     template void launch_prolong_add_b<T>(const Grid &, const Grid &, const T *, const T *, int,                 \
@@ -2326,10 +2289,9 @@ template void launch_apply<float>(const Grid &, const float *, float, int, const
                                   const float *, float *, hipStream_t, ClassList);
 template void launch_apply_A_t<float>(const Grid &, const float *, const float *, float *, hipStream_t);
 template void launch_apply_A_t<double>(const Grid &, const double *, const double *, double *, hipStream_t);
-template void launch_smooth<double>(const Grid &, const double *, double, int, int, const double *,
-                                    double *, hipStream_t, ClassList);
-template void launch_smooth<float>(const Grid &, const float *, float, int, int, const float *,
-                                   float *, hipStream_t, ClassList);
+template void launch_smooth<double>(const Grid &, double, int, const double *, double *, hipStream_t,
+                                    const ClassList &);
+template void launch_smooth<float>(const Grid &, float, int, const float *, float *, hipStream_t, const ClassList &);
 template void launch_restrict<double>(const Grid &, const Grid &, const double *, const double *,
                                       double *, hipStream_t);
 template void launch_restrict<float>(const Grid &, const Grid &, const float *, const float *,

@@ -296,9 +296,12 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
         DM_HIP(hipMemcpyAsync(L.coef32, c32.data(), 7 * P * sizeof(float), hipMemcpyHostToDevice, op->stream));
         DM_HIP(hipMemcpyAsync(L.coef64 + 7 * P, fl.data(), P, hipMemcpyHostToDevice, op->stream));
         DM_HIP(hipMemcpyAsync(L.coef32 + 7 * P, fl.data(), P, hipMemcpyHostToDevice, op->stream));
-        // the cut (non-vacuum) rows of every component, both colours, in
-        // index order
+        // the cut (non-vacuum) rows of every component, both colours, in index
+        // order; and its vacuum rows as runs along the grid rows
         std::vector<int32_t> cut;
+        std::vector<VacRun> runs;
+        const int nxh = (L.g.nx + 1) >> 1;
+        L.vrun_log = nxh <= 8 ? 3 : nxh <= 16 ? 4 : nxh <= 32 ? 5 : 6;
         for (int comp = 0; comp < 3; ++comp) {
             L.cut_off[comp] = (int64_t)cut.size();
             for (int k = 0; k < L.g.nz; ++k)
@@ -308,7 +311,26 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
                         if ((fl[p] & (kFaceActive << comp)) && !(fl[p] & (kFaceVacuum << comp)))
                             cut.push_back((int32_t)p);
                     }
+            for (int col = 0; col < 2; ++col) {
+                L.vrun_off[2 * comp + col] = (int64_t)runs.size();
+                for (int k = 0; k < L.g.nz; ++k)
+                    for (int j = 0; j < L.g.ny; ++j) {
+                        const int i0 = (j + k + col) & 1;
+                        VacRun run{};
+                        for (int ih = 0; 2 * ih + i0 < L.g.nx; ++ih) {
+                            const int64_t p = pidx(L.g, 2 * ih + i0, j, k);
+                            const int lane = ih & 63;
+                            if (lane == 0) {
+                                const int at[3] = {2 * ih + i0, j, k};
+                                run = VacRun{(int32_t)p, ((L.g.pmc >> comp) & 1) && at[comp] == 1, 0};
+                            }
+                            if (fl[p] & (kFaceVacuum << comp)) run.mask |= 1ull << lane;
+                            if ((lane == 63 || 2 * (ih + 1) + i0 >= L.g.nx) && run.mask) runs.push_back(run);
+                        }
+                    }
+            }
         }
+        L.vrun_off[6] = (int64_t)runs.size();
         L.cut_off[3] = (int64_t)cut.size();
         std::vector<int32_t> cutc;
         for (int k = 0; k < L.g.nz; ++k)
@@ -318,13 +340,6 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
                     if ((fl[p] & 7) & ~(fl[p] >> 3)) cutc.push_back((int32_t)p);
                 }
         L.ncutc = (int64_t)cutc.size();
-        std::vector<int32_t> vrows;
-        for (int k = 0; k < L.g.nz; ++k)
-            for (int j = 0; j < L.g.ny; ++j) {
-                bool any = false;
-                for (int i = 0; i < L.g.nx && !any; ++i) any = (fl[pidx(L.g, i, j, k)] >> 3) & 7;
-                if (any) vrows.push_back((int32_t)(k * L.g.ny + j));
-            }
         std::vector<int32_t> arows;
         for (int k = 0; k < L.g.nz; ++k)
             for (int j = 0; j < L.g.ny; ++j) {
@@ -339,6 +354,32 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
                 for (int i = 0; i < L.g.nx && !any; ++i) any = fl[pidx(L.g, i, j, k)] & 7;
                 if (any) frows.push_back((int32_t)(k * L.g.ny + j));
             }
+        // the cells without a cut row as runs: every grid row, then those
+        // holding an active face
+        std::vector<CellRun> cruns;
+        L.crun_log = L.g.nx <= 8 ? 3 : L.g.nx <= 16 ? 4 : L.g.nx <= 32 ? 5 : 6;
+        auto add_cruns = [&](int64_t row) {
+            const int j = (int)(row % L.g.ny), k = (int)(row / L.g.ny);
+            for (int i0 = 0; i0 < L.g.nx; i0 += 64) {
+                CellRun run{};
+                run.p = (int32_t)pidx(L.g, i0, j, k);
+                run.pmc = ((L.g.pmc & 1) && i0 == 0 ? 1 : 0) |
+                          (((L.g.pmc & 2) && j < 2) || ((L.g.pmc & 4) && k < 2) ? 2 : 0);
+                for (int l = 0; l < 64 && i0 + l < L.g.nx; ++l) {
+                    const uint8_t f = fl[run.p + l];
+                    if (!((f & 7) & ~(f >> 3))) run.visit |= 1ull << l;
+                    for (int c = 0; c < 3; ++c)
+                        if (f & (kFaceActive << c)) run.act[c] |= 1ull << l;
+                }
+                cruns.push_back(run);
+            }
+        };
+        for (int64_t row = 0; row < (int64_t)L.g.ny * L.g.nz; ++row) add_cruns(row);
+        L.ncrun = (int64_t)cruns.size();
+        for (int32_t row : frows) add_cruns(row);
+        L.nfrun = (int64_t)cruns.size() - L.ncrun;
+        L.crun = op->dalloc<CellRun>(cruns.size());
+        DM_HIP(hipMemcpyAsync(L.crun, cruns.data(), cruns.size() * sizeof(CellRun), hipMemcpyHostToDevice, op->stream));
         // tabulated rows of the cut lists and of the cells with a cut row
         {
             std::vector<double> tab, ctab;
@@ -367,10 +408,9 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
             DM_HIP(hipMemcpyAsync(L.arows, arows.data(), arows.size() * sizeof(int32_t), hipMemcpyHostToDevice,
                                   op->stream));
         }
-        L.nvrows = (int64_t)vrows.size();
-        if (!vrows.empty()) {
-            L.vrows = op->dalloc<int32_t>(vrows.size());
-            DM_HIP(hipMemcpyAsync(L.vrows, vrows.data(), vrows.size() * sizeof(int32_t), hipMemcpyHostToDevice,
+        if (!runs.empty()) {
+            L.vrun = op->dalloc<VacRun>(runs.size());
+            DM_HIP(hipMemcpyAsync(L.vrun, runs.data(), runs.size() * sizeof(VacRun), hipMemcpyHostToDevice,
                                   op->stream));
         }
         if (!cutc.empty()) {
@@ -380,6 +420,11 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
         }
         if (P > INT32_MAX) throw DmError{DM_EINVAL, "grid too large for 32-bit row lists"};
         if (!cut.empty()) {
+            for (int32_t &p : cut) {
+                const int32_t kk = (int32_t)(p / L.g.sz), jj = (int32_t)((p - kk * L.g.sz) / L.g.sy),
+                              ii = (int32_t)(p - kk * L.g.sz - (int64_t)jj * L.g.sy);
+                if ((ii + jj + kk - 3) & 1) p |= INT32_MIN;
+            }
             L.cut = op->dalloc<int32_t>(cut.size());
             DM_HIP(hipMemcpyAsync(L.cut, cut.data(), cut.size() * sizeof(int32_t), hipMemcpyHostToDevice, op->stream));
         }

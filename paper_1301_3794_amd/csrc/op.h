@@ -28,24 +28,36 @@ struct Level {
     float *bsx32 = nullptr, *bsf32 = nullptr, *bsr32 = nullptr;  // the same, FP32 scalar MG
     int64_t n_act_faces = 0, n_act_cells = 0;
     // non-vacuum rows of each component c (both colours, index order) as
-    // padded indices: cut[cut_off[c] .. cut_off[c+1])
+    // padded indices, the colour in the sign bit: cut[cut_off[c] .. cut_off[c+1])
     int32_t *cut = nullptr;
     int64_t cut_off[4] = {};
+    // vacuum rows of class 2 c + colour as runs: vrun[vrun_off[q] ..
+    // vrun_off[q+1]), 2^vrun_log lanes each
+    VacRun *vrun = nullptr;
+    int64_t vrun_off[7] = {};
+    int vrun_log = 6;
     // cells with an active non-vacuum row (any component), padded indices
     int32_t *cutc = nullptr;
     int64_t ncutc = 0;
     // tabulated rows of the cells in cutc (3 components x kCutW per cell)
     double *cellw64 = nullptr;
     float *cellw32 = nullptr;
+    // runs of the cells of every grid row (ncrun of them), then of the rows
+    // holding an active face only (nfrun); 2^crun_log lanes each
+    CellRun *crun = nullptr;
+    int64_t ncrun = 0, nfrun = 0;
+    int crun_log = 6;
     ClassList cut_cells() const {
-        ClassList cl{cutc, ncutc};
+        ClassList cl;
+        cl.idx = cutc;
+        cl.n = ncutc;
+        cl.cells = crun;
+        cl.nruns = ncrun;
+        cl.run_log = crun_log;
         cl.w64 = cellw64;
         cl.w32 = cellw32;
         return cl;
     }
-    // grid rows (k * ny + j) with a vacuum row of any component
-    int32_t *vrows = nullptr;
-    int64_t nvrows = 0;
     // grid rows (k * ny + j) with an active cell (the scalar problem's unknowns)
     int32_t *arows = nullptr;
     int64_t narows = 0;
@@ -56,8 +68,8 @@ struct Level {
     // that stay zero on the other rows (the block V-cycle's residual)
     ClassList cut_cells_rows() const {
         ClassList cl = cut_cells();
-        cl.rows = frows;
-        cl.nrows = nfrows;
+        cl.cells = crun + ncrun;
+        cl.nruns = nfrun;
         return cl;
     }
     // the block smoother's threshold for one wave per vector (dm_options)
@@ -70,8 +82,15 @@ struct Level {
     // paired as `pair` says (kPairNone, kPairFirst, kPairSecond) with the
     // cross sums in s (at least the list's length times the vectors)
     ClassList cut_list(int comp, int colour, int pair = kPairNone, void *s = nullptr) const {
-        ClassList cl{cut ? cut + cut_off[comp] : nullptr, cut_off[comp + 1] - cut_off[comp], vrows, nvrows,
-                     cut_wave_split};
+        ClassList cl;
+        cl.idx = cut ? cut + cut_off[comp] : nullptr;
+        cl.n = cut_off[comp + 1] - cut_off[comp];
+        cl.colour = colour;
+        const int q = 2 * comp + colour;
+        cl.runs = vrun ? vrun + vrun_off[q] : nullptr;
+        cl.nruns = vrun_off[q + 1] - vrun_off[q];
+        cl.run_log = vrun_log;
+        cl.wave_split_max = cut_wave_split;
         if (cutw64) cl.w64 = cutw64 + kCutW * cut_off[comp];
         if (cutw32) cl.w32 = cutw32 + kCutW * cut_off[comp];
         cl.pair = pair;

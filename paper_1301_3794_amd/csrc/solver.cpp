@@ -429,7 +429,7 @@ void vcycle(dm_op *op, int l, const T *f, T *x, hipStream_t s) {
     for (int it = 0; it < op->opt.nu_pre; ++it)
         for (int comp = 0; comp < 3; ++comp)
             for (int col = 0; col < 2; ++col)
-                launch_smooth<T>(g, c, sig, comp, col, f, x, s,
+                launch_smooth<T>(g, sig, comp, f, x, s,
                                  L.cut_list(comp, col, col == 0 ? kPairFirst : kPairSecond, op->cut_s));
     T *r = Prec<T>::r(L);
     launch_apply<T>(g, c, sig, AK_RESID, f, x, r, s, L.cut_cells());
@@ -453,7 +453,7 @@ void vcycle(dm_op *op, int l, const T *f, T *x, hipStream_t s) {
     for (int it = 0; it < op->opt.nu_post; ++it)
         for (int comp = 2; comp >= 0; --comp)
             for (int col = 1; col >= 0; --col)
-                launch_smooth<T>(g, c, sig, comp, col, f, x, s,
+                launch_smooth<T>(g, sig, comp, f, x, s,
                                  L.cut_list(comp, col, col == 1 ? kPairFirst : kPairSecond, op->cut_s));
 }
 
@@ -482,13 +482,13 @@ void vcycle_b(dm_op *op, int l, int nr, hipStream_t s) {
     for (int it = 0; it < op->opt.nu_pre; ++it)
         for (int comp = 0; comp < 3; ++comp)
             for (int col = 0; col < 2; ++col)
-                launch_smooth_b<T>(g, c, sig, comp, col, nr, as_const(F), X, s,
+                launch_smooth_b<T>(g, sig, comp, nr, as_const(F), X, s,
                                    L.cut_list(comp, col, col == 0 ? kPairFirst : kPairSecond, op->cut_s));
     const VPtr<T> R = slots(BPrec<T>::r(L), n3, nr);
     // the residual, restriction and prolongation visit only the grid rows
     // holding an active face: the residual slots, the coarse right-hand
     // sides and iterates stay zero on the others (written only here)
-    launch_apply_b<T>(g, c, sig, AK_RESID, nr, as_const(F), as_const(X), R, s, L.cut_cells_rows());
+    launch_apply_b<T>(g, sig, AK_RESID, nr, as_const(F), as_const(X), R, s, L.cut_cells_rows());
     Level &C = op->lv[l + 1];
     const int64_t c3 = 3 * C.g.P;
     launch_restrict_b<T>(g, C.g, Prec<T>::coef(C), nr, as_const(R), slots(BPrec<T>::f(C), c3, nr), s,
@@ -499,7 +499,7 @@ void vcycle_b(dm_op *op, int l, int nr, hipStream_t s) {
     for (int it = 0; it < op->opt.nu_post; ++it)
         for (int comp = 2; comp >= 0; --comp)
             for (int col = 1; col >= 0; --col)
-                launch_smooth_b<T>(g, c, sig, comp, col, nr, as_const(F), X, s,
+                launch_smooth_b<T>(g, sig, comp, nr, as_const(F), X, s,
                                    L.cut_list(comp, col, col == 1 ? kPairFirst : kPairSecond, op->cut_s));
 }
 
@@ -1044,7 +1044,7 @@ int fgmres_block(dm_op *op, int mode, int nb, const double *const *f, double *co
                     ++nres;
                 }
             }
-            if (nres) launch_apply_b<double>(L.g, L.coef64, op->sigma, AK_RESID, nres, bf, bx, by, s, L.cut_cells());
+            if (nres) launch_apply_b<double>(L.g, op->sigma, AK_RESID, nres, bf, bx, by, s, L.cut_cells());
             for (int r : act) {
                 launch_mdot(1, Fc(r, 0), 0, Fc(r, 0), nullptr, n, op->part, dres(r), s, sp);
                 if (b32) launch_cast<double, float>(Fc(r, 0), Vc32(r, 0), n, s, sp);
@@ -1106,10 +1106,10 @@ int fgmres_block(dm_op *op, int mode, int nb, const double *const *f, double *co
         if (z32) {
             if (b32) precondition_block_f32<float>(op, na, vin32, zout32, s);
             else precondition_block_f32<double>(op, na, vin, zout32, s);
-            launch_apply_m_f32in(L.g, L.coef64, op->sigma, na, zc32, wv, s, L.cut_cells_rows());
+            launch_apply_m_f32in(L.g, op->sigma, na, zc32, wv, s, L.cut_cells_rows());
         } else {
             precondition_block(op, mode, na, vin, zout, s, rej);
-            launch_apply_b<double>(L.g, L.coef64, op->sigma, AK_M, na, VPtr<const double>{}, zc, wv, s,
+            launch_apply_b<double>(L.g, op->sigma, AK_M, na, VPtr<const double>{}, zc, wv, s,
                                    L.cut_cells_rows());
         }
         // Gram--Schmidt as in fgmres(): (1) d = U^T w, (2) w -= U (sc^2 d)
