@@ -390,6 +390,29 @@ inline const double *cut_weights<double>(const ClassList &cl) { return cl.w64; }
 template <>
 inline const float *cut_weights<float>(const ClassList &cl) { return cl.w32; }
 
+// The rows of a level small enough that its iterate fits the LDS of one CU
+// (lds_level): a workgroup then runs whole smoothing sweeps of one vector in
+// one launch (launch_sweeps_lds).  Class q = 2 component + colour has the cut
+// rows cut[cut_off[q] .. cut_off[q + 1]) and the vacuum rows vac[vac_off[q] ..
+// vac_off[q + 1]), as padded indices (the colour in the sign bit of cut); the
+// table of a component's cut rows is that of ClassList.
+struct LdsRows {
+    const int32_t *cut = nullptr, *vac = nullptr;
+    int32_t cut_off[7] = {}, vac_off[7] = {};
+    const double *w64 = nullptr;
+    const float *w32 = nullptr;
+};
+constexpr int64_t kLdsBytes = 160 * 1024;
+// Whether a level of P padded elements per block and `faces` active faces runs
+// its sweeps this way (elem: bytes per value): its iterate fits, and its rows
+// are few enough that one CU's loads of their weights beat six launches per
+// sweep over the whole chip.  Per class update, a launch takes 2.7 us whatever
+// the size; one CU takes 1.5 us (FP32) or 2.3 us (FP64) for the 5,664 faces of
+// the 16^3 sphere, and 3.1 us (FP32) for the 15,400 of a 22 x 18 x 26 level.
+inline bool lds_level(int64_t P, int64_t faces, size_t elem) {
+    return 3 * P * (int64_t)elem <= kLdsBytes && faces <= (elem == 4 ? 10240 : 6656);
+}
+
 // Units of kSpanUnit consecutive doubles (one 128-byte line) of a level-0
 // face vector that can hold a nonzero entry: an active face, or a PMC ghost
 // image of one.  The Krylov reductions and multi-axpys visit only the listed
@@ -413,6 +436,11 @@ void launch_apply_b(const Grid &g, T sigma, int kind, int nr, const VPtr<const T
 template <class T>
 void launch_smooth_b(const Grid &g, T sigma, int comp, int nr, const VPtr<const T> &f, const VPtr<T> &x,
                      hipStream_t s, const ClassList &cl);
+// `sweeps` whole smoothing sweeps (the six classes in order, or reversed) of
+// nr vectors on an LDS level; zero: x starts at zero instead of being read
+template <class T>
+void launch_sweeps_lds(const Grid &g, T sigma, const LdsRows &rows, int sweeps, int reverse, int zero, int nr,
+                       const VPtr<const T> &f, const VPtr<T> &x, hipStream_t s);
 // xz (optional, one coarse iterate per vector): set to zero in the same pass;
 // rows (optional): the coarse grid rows (k * ny + j) to visit, those holding
 // an active face (fc and xz stay zero on the others)

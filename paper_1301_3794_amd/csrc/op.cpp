@@ -248,6 +248,12 @@ static void cut_tables(const Grid &g, const std::vector<double> &c, const std::v
     for (auto &t : th) t.join();
 }
 
+// whether a padded index is that of a cell of colour 1
+static bool odd_cell(const Grid &g, int64_t p) {
+    const int64_t kk = p / g.sz, rr = p - kk * g.sz, jj = rr / g.sy;
+    return (rr - jj * g.sy + jj + kk - 3) & 1;
+}
+
 void build_hierarchy(dm_op *op, const double *user_frac) {
     const int nl = op->opt.levels;
     int pmc = 0;
@@ -300,6 +306,10 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
         // order; and its vacuum rows as runs along the grid rows
         std::vector<int32_t> cut;
         std::vector<VacRun> runs;
+        std::vector<int32_t> vac;
+        int64_t faces = 0;
+        for (const uint8_t f : fl) faces += (f & 1) + ((f >> 1) & 1) + ((f >> 2) & 1);
+        const bool small = lds_level(P, faces, sizeof(float));
         const int nxh = (L.g.nx + 1) >> 1;
         L.vrun_log = nxh <= 8 ? 3 : nxh <= 16 ? 4 : nxh <= 32 ? 5 : 6;
         for (int comp = 0; comp < 3; ++comp) {
@@ -311,12 +321,23 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
                         if ((fl[p] & (kFaceActive << comp)) && !(fl[p] & (kFaceVacuum << comp)))
                             cut.push_back((int32_t)p);
                     }
+            if (small) {
+                const auto first = cut.begin() + L.cut_off[comp];
+                const auto mid = std::stable_partition(first, cut.end(), [&](int32_t p) { return !odd_cell(L.g, p); });
+                L.lds.cut_off[2 * comp] = (int32_t)L.cut_off[comp];
+                L.lds.cut_off[2 * comp + 1] = (int32_t)(mid - cut.begin());
+            }
             for (int col = 0; col < 2; ++col) {
                 L.vrun_off[2 * comp + col] = (int64_t)runs.size();
+                L.lds.vac_off[2 * comp + col] = (int32_t)vac.size();
                 for (int k = 0; k < L.g.nz; ++k)
                     for (int j = 0; j < L.g.ny; ++j) {
                         const int i0 = (j + k + col) & 1;
                         VacRun run{};
+                        if (small)
+                            for (int i = i0; i < L.g.nx; i += 2)
+                                if (fl[pidx(L.g, i, j, k)] & (kFaceVacuum << comp))
+                                    vac.push_back((int32_t)pidx(L.g, i, j, k));
                         for (int ih = 0; 2 * ih + i0 < L.g.nx; ++ih) {
                             const int64_t p = pidx(L.g, 2 * ih + i0, j, k);
                             const int lane = ih & 63;
@@ -332,6 +353,8 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
         }
         L.vrun_off[6] = (int64_t)runs.size();
         L.cut_off[3] = (int64_t)cut.size();
+        L.lds.cut_off[6] = (int32_t)cut.size();
+        L.lds.vac_off[6] = (int32_t)vac.size();
         std::vector<int32_t> cutc;
         for (int k = 0; k < L.g.nz; ++k)
             for (int j = 0; j < L.g.ny; ++j)
@@ -420,14 +443,19 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
         }
         if (P > INT32_MAX) throw DmError{DM_EINVAL, "grid too large for 32-bit row lists"};
         if (!cut.empty()) {
-            for (int32_t &p : cut) {
-                const int32_t kk = (int32_t)(p / L.g.sz), jj = (int32_t)((p - kk * L.g.sz) / L.g.sy),
-                              ii = (int32_t)(p - kk * L.g.sz - (int64_t)jj * L.g.sy);
-                if ((ii + jj + kk - 3) & 1) p |= INT32_MIN;
-            }
+            for (int32_t &p : cut)
+                if (odd_cell(L.g, p)) p |= INT32_MIN;
             L.cut = op->dalloc<int32_t>(cut.size());
             DM_HIP(hipMemcpyAsync(L.cut, cut.data(), cut.size() * sizeof(int32_t), hipMemcpyHostToDevice, op->stream));
         }
+        if (!vac.empty()) {
+            int32_t *d = op->dalloc<int32_t>(vac.size());
+            DM_HIP(hipMemcpyAsync(d, vac.data(), vac.size() * sizeof(int32_t), hipMemcpyHostToDevice, op->stream));
+            L.lds.vac = d;
+        }
+        L.lds.cut = L.cut;
+        L.lds.w64 = L.cutw64;
+        L.lds.w32 = L.cutw32;
         if (l == 0) {
             // units of 16 doubles of a face vector holding an active face or
             // a PMC ghost image (rows of a mirrored plane at index -1)

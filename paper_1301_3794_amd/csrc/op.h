@@ -27,8 +27,8 @@ struct Level {
     double *bsx = nullptr, *bsf = nullptr, *bsr = nullptr;  // kMaxRhs * P (scalar MG)
     float *bsx32 = nullptr, *bsf32 = nullptr, *bsr32 = nullptr;  // the same, FP32 scalar MG
     int64_t n_act_faces = 0, n_act_cells = 0;
-    // non-vacuum rows of each component c (both colours, index order) as
-    // padded indices, the colour in the sign bit: cut[cut_off[c] .. cut_off[c+1])
+    // non-vacuum rows of each component c (both colours, index order; on an
+    // LDS level colour 0 then colour 1) as padded indices, the colour in the sign bit: cut[cut_off[c] .. cut_off[c+1])
     int32_t *cut = nullptr;
     int64_t cut_off[4] = {};
     // vacuum rows of class 2 c + colour as runs: vrun[vrun_off[q] ..
@@ -36,6 +36,9 @@ struct Level {
     VacRun *vrun = nullptr;
     int64_t vrun_off[7] = {};
     int vrun_log = 6;
+    // LDS levels (lds_level in FP32): the cut list above is sorted by colour
+    // within each component, and lds names every class's rows
+    LdsRows lds;
     // cells with an active non-vacuum row (any component), padded indices
     int32_t *cutc = nullptr;
     int64_t ncutc = 0;

@@ -417,16 +417,19 @@ void vcycle(dm_op *op, int l, const T *f, T *x, hipStream_t s) {
     Level &L = op->lv[l];
     const Grid &g = L.g;
     const T sig = (T)op->sigma;
-    launch_zero<T>(3 * g.P, x, s);
-    if (l == op->nlev() - 1) {
+    const bool last = l == op->nlev() - 1, lds = !last && lds_level(g.P, L.n_act_faces, sizeof(T));
+    if (!lds) launch_zero<T>(3 * g.P, x, s);
+    if (last) {
         launch_coarse_solve<T>(op->nc, op->cinv, op->cidx, f, x, s);
         launch_mirror_faces<T>(g, x, s);
         return;
     }
     const T *c = Prec<T>::coef(L);
+    // a level whose iterate fits one CU's LDS runs its sweeps in one launch
+    if (lds) launch_sweeps_lds<T>(g, sig, L.lds, op->opt.nu_pre, 0, 1, 1, vptr1(f), vptr1(x), s);
     // the two colour updates of a component are paired: the first leaves the
     // second colour's cross-component sums in op->cut_s
-    for (int it = 0; it < op->opt.nu_pre; ++it)
+    for (int it = 0; it < op->opt.nu_pre && !lds; ++it)
         for (int comp = 0; comp < 3; ++comp)
             for (int col = 0; col < 2; ++col)
                 launch_smooth<T>(g, sig, comp, f, x, s,
@@ -450,7 +453,8 @@ void vcycle(dm_op *op, int l, const T *f, T *x, hipStream_t s) {
     } else {
         launch_prolong_add<T>(g, C.g, c, cc, xc, x, s);
     }
-    for (int it = 0; it < op->opt.nu_post; ++it)
+    if (lds) launch_sweeps_lds<T>(g, sig, L.lds, op->opt.nu_post, 1, 0, 1, vptr1(f), vptr1(x), s);
+    for (int it = 0; it < op->opt.nu_post && !lds; ++it)
         for (int comp = 2; comp >= 0; --comp)
             for (int col = 1; col >= 0; --col)
                 launch_smooth<T>(g, sig, comp, f, x, s,
@@ -472,14 +476,16 @@ void vcycle_b(dm_op *op, int l, int nr, hipStream_t s) {
     const VPtr<T> F = slots(BPrec<T>::f(L), n3, nr), X = slots(BPrec<T>::x(L), n3, nr);
     // the iterate starts at zero: here on the finest level, on the coarser
     // ones in the restriction that forms their right-hand side
-    if (l == 0) launch_zero<T>(nr * n3, BPrec<T>::x(L), s);
-    if (l == op->nlev() - 1) {
+    const bool last = l == op->nlev() - 1, lds = !last && lds_level(g.P, L.n_act_faces, sizeof(T));
+    if (l == 0 && !lds) launch_zero<T>(nr * n3, BPrec<T>::x(L), s);
+    if (last) {
         launch_coarse_solve_b<T>(op->nc, op->cinv, op->cidx, nr, as_const(F), X, s);
         for (int q = 0; q < nr; ++q) launch_mirror_faces<T>(g, X.p[q], s);
         return;
     }
     const T *c = Prec<T>::coef(L);
-    for (int it = 0; it < op->opt.nu_pre; ++it)
+    if (lds) launch_sweeps_lds<T>(g, sig, L.lds, op->opt.nu_pre, 0, 1, nr, as_const(F), X, s);
+    for (int it = 0; it < op->opt.nu_pre && !lds; ++it)
         for (int comp = 0; comp < 3; ++comp)
             for (int col = 0; col < 2; ++col)
                 launch_smooth_b<T>(g, sig, comp, nr, as_const(F), X, s,
@@ -496,7 +502,8 @@ void vcycle_b(dm_op *op, int l, int nr, hipStream_t s) {
     vcycle_b<T>(op, l + 1, nr, s);
     launch_prolong_add_b<T>(g, C.g, c, Prec<T>::coef(C), nr, as_const(slots(BPrec<T>::x(C), c3, nr)), X, s,
                             L.frows, L.nfrows);
-    for (int it = 0; it < op->opt.nu_post; ++it)
+    if (lds) launch_sweeps_lds<T>(g, sig, L.lds, op->opt.nu_post, 1, 0, nr, as_const(F), X, s);
+    for (int it = 0; it < op->opt.nu_post && !lds; ++it)
         for (int comp = 2; comp >= 0; --comp)
             for (int col = 1; col >= 0; --col)
                 launch_smooth_b<T>(g, sig, comp, nr, as_const(F), X, s,
