@@ -78,11 +78,9 @@ void forward(dm_net *net, const Grid &g, hipStream_t s) {
     launch_net_conv(NET_LINEAR, g, net->a2, net->wf + 2 * 27 * 256, nullptr, nullptr, net->y, s);
 }
 
-// s = ||r|| / sqrt(active faces), over owned entries only
-double rms_of(dm_op *op, const double *r, hipStream_t s) {
-    const double n2 = dot1(op, r, r, op->wface, op->n0(), s);
-    const double na = (double)std::max<int64_t>(1, op->lv[0].n_act_faces);
-    return std::sqrt(n2 / na);
+// s = ||r|| / sqrt(active faces) from ||r||^2 (over owned entries only)
+double rms_from(dm_op *op, double n2) {
+    return std::sqrt(n2 / (double)std::max<int64_t>(1, op->lv[0].n_act_faces));
 }
 
 }  // namespace
@@ -96,7 +94,7 @@ void net_init(dm_net *net, uint64_t seed) {
     net->grad = net_alloc<float>(kNetWeights, fa);
     net->wf = net_alloc<uint16_t>(3 * 27 * 256, fa);
     net->wb = net_alloc<uint16_t>(3 * 27 * 256, fa);
-    net->part = net_alloc<float>((size_t)kNetWaves * 27 * 256, fa);
+    net->part = net_alloc<float>((size_t)kNetParts * 27 * 256, fa);
     net->lpart = net_alloc<double>(2 * kLossBlocks, fa);
     DM_HIP(hipHostMalloc((void **)&net->hl, 2 * kLossBlocks * sizeof(double), hipHostMallocDefault));
     net->cap = 0;
@@ -162,7 +160,7 @@ void net_forward(dm_op *op, hipStream_t s) {
 void net_apply(dm_op *op, const double *r, double scale, double *out, hipStream_t s) {
     dm_net *net = attached(op);
     const Level &L = op->lv[0];
-    const double sc = scale > 0.0 ? scale : rms_of(op, r, s);
+    const double sc = scale > 0.0 ? scale : rms_from(op, dot1(op, r, r, op->wface, op->n0(), s));
     if (!(sc > 0.0) || !std::isfinite(sc)) {
         DM_HIP(hipMemsetAsync(out, 0, op->n0() * sizeof(double), s));
         return;
@@ -205,7 +203,10 @@ double net_loss_grad(dm_op *op, int kind, const double *r, const double *e, doub
     const Level &L = op->lv[0];
     const Grid &g = L.g;
     const int64_t n = op->n0();
-    const double sc = scale > 0.0 ? scale : rms_of(op, r, s);
+    // |r|^2 over owned entries: the input scale, and the residual loss's norm
+    const bool residual = kind != DM_NET_LOSS_ERROR;
+    const double rr = residual || !(scale > 0.0) ? dot1(op, r, r, op->wface, n, s) : 0.0;
+    const double sc = scale > 0.0 ? scale : rms_from(op, rr);
     if (!(sc > 0.0) || !std::isfinite(sc)) throw DmError{DM_EINVAL, "training pair with a zero residual"};
     launch_net_pack_r<double>(g, r, 1.0 / sc, net->x0, s);
     forward(net, g, s);
@@ -231,24 +232,28 @@ double net_loss_grad(dm_op *op, int kind, const double *r, const double *e, doub
         double *d = op->ln_t3, *r3 = op->ln_t4;
         launch_net_unpack<double>(g, L.coef64, net->y, c, d, s);
         launch_apply<double>(g, L.coef64, op->sigma, AK_RESID, r, d, r3, s, L.cut_cells());
-        const double rr = dot1(op, r, r, op->wface, n, s);
-        const double r33 = dot1(op, r3, r3, op->wface, n, s);
+        // |r3|^2 stays on the device until the gradients are queued
+        launch_mdot(1, r3, 0, r3, op->wface, n, op->part, op->dres, s);
         launch_apply<double>(g, L.coef64, op->sigma, AK_M, nullptr, r3, d, s, L.cut_cells());
         launch_net_dy_from_face(g, L.coef64, d, -2.0 * c / rr, net->dy, s);
-        loss = r33 / rr;
     }
     // layer 3: weights from a2 and dy; data gradient into d2 (masked by a2 > 0)
     launch_net_wgrad(g, net->a2, net->dy, net->part, s);
-    launch_net_wgrad_reduce(net->part, kNetIn[2], kNetOut[2], net->grad + net_offset(2), s);
+    launch_net_wgrad_reduce(g, net->part, kNetIn[2], kNetOut[2], net->grad + net_offset(2), s);
     launch_net_conv(NET_MASKED, g, net->dy, net->wb + 2 * 27 * 256, net->a2, net->d2, nullptr, s);
     // layer 2
     launch_net_wgrad(g, net->a1, net->d2, net->part, s);
-    launch_net_wgrad_reduce(net->part, kNetIn[1], kNetOut[1], net->grad + net_offset(1), s);
+    launch_net_wgrad_reduce(g, net->part, kNetIn[1], kNetOut[1], net->grad + net_offset(1), s);
     launch_net_conv(NET_MASKED, g, net->d2, net->wb + 27 * 256, net->a1, net->d1, nullptr, s);
     // layer 1
     launch_net_wgrad(g, net->x0, net->d1, net->part, s);
-    launch_net_wgrad_reduce(net->part, kNetIn[0], kNetOut[0], net->grad, s);
+    launch_net_wgrad_reduce(g, net->part, kNetIn[0], kNetOut[0], net->grad, s);
     DM_HIP(hipGetLastError());
+    if (residual) {
+        DM_HIP(hipMemcpyAsync(op->hres, op->dres, sizeof(double), hipMemcpyDeviceToHost, s));
+        DM_HIP(hipStreamSynchronize(s));
+        loss = op->hres[0] / rr;
+    }
     return loss;
 }
 

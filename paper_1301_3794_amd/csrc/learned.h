@@ -19,7 +19,7 @@ constexpr int kNetIn[3] = {10, 16, 16};
 constexpr int kNetOut[3] = {16, 16, 3};
 constexpr int kNetWeights = 27 * (10 * 16 + 16 * 16 + 16 * 3);  // 12528
 constexpr int kNetCh = 16;                                      // padded channels
-constexpr int kNetWaves = 1024;                                 // weight-gradient partials
+constexpr int kNetParts = 512;                                  // weight-gradient partials (one per workgroup)
 
 inline int64_t net_offset(int layer) {
     int64_t o = 0;
@@ -51,7 +51,7 @@ void launch_net_conv(int mode, const Grid &g, const uint16_t *in, const uint16_t
 // sum_p x[p + off][c] * d[p][o] over interior cells
 void launch_net_wgrad(const Grid &g, const uint16_t *x, const uint16_t *d, float *part, hipStream_t s);
 // grad[t][c][o] (c < cin, o < cout, flat layer layout) = sum over waves of part
-void launch_net_wgrad_reduce(const float *part, int cin, int cout, float *grad, hipStream_t s);
+void launch_net_wgrad_reduce(const Grid &g, const float *part, int cin, int cout, float *grad, hipStream_t s);
 // channels 0..2 of x0 = bf16(r_comp * inv_s) on interior cells
 template <class T>
 void launch_net_pack_r(const Grid &g, const T *r, double inv_s, uint16_t *x0, hipStream_t s);
