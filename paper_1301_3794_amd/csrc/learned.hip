@@ -49,86 +49,105 @@ k_net_conv(Grid g, const uint16_t *__restrict__ in, const uint16_t *__restrict__
     static_assert(kT / 64 == kTileY, "one wave per y-row of the tile");
     __shared__ uint4 xs[kTileCells * kCellStride];
     const int nsx = (g.nx + 15) >> 4, nty = (g.ny + kTileY - 1) / kTileY;
-    const int64_t b = blockIdx.x;
-    const int sx = (int)(b % nsx);
-    const int64_t rest = b / nsx;
-    const int j0 = (int)(rest % nty) * kTileY, k0 = (int)(rest / nty) * kTileZ;
+    // each XCD (workgroups reach them round-robin) takes one run of tiles, so
+    // that neighbours share their halos in its L2
+    const uint32_t per = gridDim.x / 8, b = blockIdx.x % 8 * per + blockIdx.x / 8;
+    const int sx = (int)(b % nsx), rest = (int)(b / nsx);
+    const int j0 = rest % nty * kTileY, k0 = rest / nty * kTileZ;
+    if (k0 >= g.nz) return;   // the grid is padded to a multiple of 8
     const int i0 = sx * 16;
-    for (int e = threadIdx.x; e < kTileCells * 2; e += kT) {
-        const int c = e >> 1, half = e & 1;
-        const int xi = c % 18, yi = (c / 18) % (kTileY + 2), zi = c / (18 * (kTileY + 2));
-        // cell (i, j, k) of the grid, padding at -1 and n
-        const int i = i0 - 1 + xi, j = j0 - 1 + yi, k = k0 - 1 + zi;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (i <= g.nx && j <= g.ny && k <= g.nz)
-            v = reinterpret_cast<const uint4 *>(in + pidx(g, i, j, k) * kNetCh)[half];
-        xs[c * kCellStride + half] = v;
+    // a wave stages every fourth row of the tile: 18 cells are 576 contiguous
+    // bytes, 36 lanes of 16; all its rows are in flight before the first is
+    // written (cells outside the padded grid are zero)
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    constexpr int kRows = (kTileY + 2) * (kTileZ + 2), kMine = (kRows + kT / 64 - 1) / (kT / 64);
+    static_assert(kRows % (kT / 64) == 0, "rows dealt evenly to the waves");
+    const bool on = lane < 36 && i0 - 1 + (lane >> 1) <= g.nx;
+    uint4 rows[kMine];
+#pragma unroll
+    for (int m = 0; m < kMine; ++m) {
+        const int r = wv + m * (kT / 64), j = j0 - 1 + r % (kTileY + 2), k = k0 - 1 + r / (kTileY + 2);
+        rows[m] = make_uint4(0u, 0u, 0u, 0u);
+        if (on && j <= g.ny && k <= g.nz)
+            rows[m] = reinterpret_cast<const uint4 *>(in + pidx(g, i0 - 1, j, k) * kNetCh)[lane];
     }
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, kg = lane >> 4;
     // this lane's A operands: output channel col, input channels 4 kg .. 4 kg + 3, every tap
+    const int col = lane & 15, kg = lane >> 4;
     uint2 wr[27];
 #pragma unroll
     for (int t = 0; t < 27; ++t) wr[t] = *reinterpret_cast<const uint2 *>(w + t * 256 + col * 16 + 4 * kg);
+    if (lane < 36)
+#pragma unroll
+        for (int m = 0; m < kMine; ++m)
+            xs[((wv + m * (kT / 64)) * 18 + (lane >> 1)) * kCellStride + (lane & 1)] = rows[m];
     __syncthreads();
     const int j = j0 + wv;
     if (j >= g.ny) return;
     const int ia = i0 + col;
     const bool va = ia < g.nx;
     const uint2 *xs2 = reinterpret_cast<const uint2 *>(xs);
-    // two z-planes at a time: their product chains are independent, so one
-    // hides the other's latency
-    for (int zz = 0; zz < kTileZ; zz += 2) {
-        if (k0 + zz >= g.nz) break;
-        // all 2 x 27 taps from LDS before the first product
-        uint2 raw[2][27];
+    // D = W X: rows the output channels (A = the tap's weights, row = output
+    // channel, k = input channel), columns the 16 cells (B = the inputs, k =
+    // input channel, column = cell); lane (col, kg) ends with output channels
+    // 4 kg .. 4 kg + 3 of cell i0 + col, stored as one 8-byte write (a
+    // wavefront writes the segment's 512 contiguous bytes).
+    // The wave marches through the input planes of its y-row: the nine
+    // operands of a plane (three rows, three shifts along x) are read once and
+    // serve the last nine taps of the output plane below, the middle nine of
+    // the plane itself and the first nine of the one above, three independent
+    // chains of products; each output still sums its taps in order.  Reading
+    // all 27 operands per output plane kept the LDS as busy as the matrix
+    // cores (72 us per layer at 128^3, 61 with this); staging by rows instead
+    // of by cells, with its index arithmetic in scalars, took it to 49 us.
+    auto load = [&](uint2 *v, int zp) __attribute__((always_inline)) {   // input plane k0 - 1 + zp
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int t = 0; t < 27; ++t) {
-                const int dx = t % 3 - 1, dy = (t / 3) % 3 - 1, dz = t / 9 - 1;
-                const int c = (col + 1 + dx) + 18 * ((wv + 1 + dy) + (kTileY + 2) * (zz + h + 1 + dz));
-                raw[h][t] = xs2[c * (2 * kCellStride) + kg];
-            }
-        // D = W X: rows the output channels (A = the tap's weights, row = output
-        // channel, k = input channel), columns the 16 cells (B = the inputs,
-        // k = input channel, column = cell); lane (col, kg) ends with output
-        // channels 4 kg .. 4 kg + 3 of cell i0 + col, stored as one 8-byte
-        // write (a wavefront writes the segment's 512 contiguous bytes)
-        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-        for (int t = 0; t < 27; ++t) {
-            const bf16x4 aw = *reinterpret_cast<const bf16x4 *>(&wr[t]);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const uint2 xv = va ? raw[h][t] : make_uint2(0u, 0u);
-                const bf16x4 bx = *reinterpret_cast<const bf16x4 *>(&xv);
-                acc[h] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(aw, bx, acc[h], 0, 0, 0);
-            }
+        for (int r = 0; r < 9; ++r)
+            v[r] = xs2[((col + r % 3) + 18 * ((wv + r / 3) + (kTileY + 2) * zp)) * (2 * kCellStride) + kg];
+    };
+    auto store = [&](const f32x4 &a, int k) __attribute__((always_inline)) {
+        if (!va) return;
+        const int64_t p = pidx(g, ia, j, k);
+        if (MODE == NET_LINEAR) {
+            if (kg == 0) *reinterpret_cast<float4 *>(out_f + p * 4) = make_float4(a[0], a[1], a[2], a[3]);
+            return;
         }
-        if (!va) continue;
+        uint16_t o[4];
+        if (MODE == NET_RELU) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int k = k0 + zz + h;
-            if (k >= g.nz) break;
-            const int64_t p = pidx(g, ia, j, k);
-            if (MODE == NET_LINEAR) {
-                if (kg == 0)
-                    *reinterpret_cast<float4 *>(out_f + p * 4) = make_float4(acc[h][0], acc[h][1], acc[h][2], acc[h][3]);
-                continue;
-            }
-            uint16_t o[4];
-            if (MODE == NET_RELU) {
+            for (int r = 0; r < 4; ++r) o[r] = f2bf(a[r] > 0.f ? a[r] : 0.f);
+        } else {
+            const uint2 mraw = *reinterpret_cast<const uint2 *>(mask + p * kNetCh + 4 * kg);
+            const uint16_t *m = reinterpret_cast<const uint16_t *>(&mraw);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) o[r] = f2bf(acc[h][r] > 0.f ? acc[h][r] : 0.f);
-            } else {
-                const uint2 mraw = *reinterpret_cast<const uint2 *>(mask + p * kNetCh + 4 * kg);
-                const uint16_t *m = reinterpret_cast<const uint16_t *>(&mraw);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[r] = f2bf(bf2f(m[r]) > 0.f ? acc[h][r] : 0.f);
-            }
-            *reinterpret_cast<uint2 *>(out_bf + p * kNetCh + 4 * kg) =
-                make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
+            for (int r = 0; r < 4; ++r) o[r] = f2bf(bf2f(m[r]) > 0.f ? a[r] : 0.f);
         }
+        *reinterpret_cast<uint2 *>(out_bf + p * kNetCh + 4 * kg) =
+            make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
+    };
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 below = zero, here = zero;   // output planes zp - 2 and zp - 1 (of the tile) when plane zp is read
+    uint2 v[2][9];
+    load(v[0], 0);
+#pragma unroll
+    for (int zp = 0; zp < kTileZ + 2; ++zp) {
+        if (zp + 1 < kTileZ + 2) load(v[(zp + 1) & 1], zp + 1);
+        f32x4 above = zero;
+#pragma unroll
+        for (int r = 0; r < 9; ++r) {
+            const bf16x4 bx = *reinterpret_cast<const bf16x4 *>(&v[zp & 1][r]);
+            if (zp >= 2)
+                below = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const bf16x4 *>(&wr[18 + r]), bx,
+                                                                  below, 0, 0, 0);
+            if (zp >= 1 && zp <= kTileZ)
+                here = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const bf16x4 *>(&wr[9 + r]), bx,
+                                                                 here, 0, 0, 0);
+            if (zp < kTileZ)
+                above = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const bf16x4 *>(&wr[r]), bx, above,
+                                                                  0, 0, 0);
+        }
+        if (zp >= 2 && k0 + zp - 2 < g.nz) store(below, k0 + zp - 2);
+        below = here;
+        here = above;
     }
 }
 
@@ -376,10 +395,17 @@ k_net_adam(const float *__restrict__ g, float *__restrict__ w, float *__restrict
 
 }  // namespace
 
+namespace {
+inline int net_tiles(const Grid &g) {
+    return (int)(ceil_div(g.nx, 16) * ceil_div(g.ny, kTileY) * ceil_div(g.nz, kTileZ));
+}
+inline int net_parts(const Grid &g) { return std::min(kNetParts, net_tiles(g)); }
+}  // namespace
+
 void launch_net_conv(int mode, const Grid &g, const uint16_t *in, const uint16_t *w, const uint16_t *mask,
                      uint16_t *out_bf, float *out_f, hipStream_t s) {
-    // one workgroup per tile of 16 x kTileY x kTileZ cells
-    const dim3 grid((unsigned)(ceil_div(g.nx, 16) * ceil_div(g.ny, kTileY) * ceil_div(g.nz, kTileZ)));
+    // one workgroup per tile of 16 x kTileY x kTileZ cells, padded to the XCDs
+    const dim3 grid((unsigned)(ceil_div(net_tiles(g), 8) * 8));
     if (mode == NET_RELU)
         hipLaunchKernelGGL(k_net_conv<NET_RELU>, grid, dim3(kT), 0, s, g, in, w, mask, out_bf, out_f);
     else if (mode == NET_MASKED)
@@ -387,13 +413,6 @@ void launch_net_conv(int mode, const Grid &g, const uint16_t *in, const uint16_t
     else
         hipLaunchKernelGGL(k_net_conv<NET_LINEAR>, grid, dim3(kT), 0, s, g, in, w, mask, out_bf, out_f);
 }
-
-namespace {
-inline int net_tiles(const Grid &g) {
-    return (int)(ceil_div(g.nx, 16) * ceil_div(g.ny, kTileY) * ceil_div(g.nz, kTileZ));
-}
-inline int net_parts(const Grid &g) { return std::min(kNetParts, net_tiles(g)); }
-}  // namespace
 
 void launch_net_wgrad(const Grid &g, const uint16_t *x, const uint16_t *d, float *part, hipStream_t s) {
     hipLaunchKernelGGL(k_net_wgrad, dim3((unsigned)net_parts(g)), dim3(kT), 0, s, g, x, d, part);
