@@ -25,7 +25,7 @@ namespace dm {
 namespace {
 
 struct HostStep {
-    int kind, comp, colour;
+    int kind, comp;
     std::vector<BJob> jobs;
 };
 
@@ -44,14 +44,17 @@ LevelBufs bufs(dm_op *op, int l) {
 
 int64_t cells(const Grid &g) { return (int64_t)g.nx * g.ny * g.nz; }
 
+// whether member op smooths its level l in LDS when the whole depth does
+bool lds_at(dm_op *op, int l) { return lds_level(op->lv[l].g.P, op->lv[l].n_act_faces, sizeof(float)); }
+
 // the fused V-cycle as a list of batched steps
 std::vector<HostStep> schedule(dm_batch *b) {
     std::vector<HostStep> st;
     int dmax = 0;
     for (dm_op *op : b->ops) dmax = std::max(dmax, op->nlev());
     const int nu_pre = b->ops[0]->opt.nu_pre, nu_post = b->ops[0]->opt.nu_post;
-    auto add = [&](int kind, int comp, int colour, std::vector<BJob> jobs) {
-        if (!jobs.empty()) st.push_back({kind, comp, colour, std::move(jobs)});
+    auto add = [&](int kind, int comp, std::vector<BJob> jobs) {
+        if (!jobs.empty()) st.push_back({kind, comp, std::move(jobs)});
     };
     auto job = [&](dm_op *op, int l) {
         BJob J{};
@@ -61,8 +64,61 @@ std::vector<HostStep> schedule(dm_batch *b) {
             J.cc = op->lv[l + 1].coef32;
         }
         J.c = op->lv[l].coef32;
-        J.sigma = op->sigma;
+        J.sigma = (float)op->sigma;
         return J;
+    };
+    // the rows of a class update or of the residual
+    auto rows = [&](BJob &J, const ClassList &cl) {
+        J.cut = cl.idx;
+        J.w = cl.w32;
+        J.s = static_cast<float *>(cl.s);
+        J.runs = cl.runs;
+        J.cells = cl.cells;
+        J.n = cl.n;
+        J.nruns = (uint32_t)cl.nruns;
+        J.run_log = cl.run_log;
+        J.colour = cl.colour;
+        J.pair = cl.pair;
+        J.items = cl.nruns << cl.run_log;
+    };
+    // the smoothing sweeps of every member with a coarser level than d: one
+    // launch of one workgroup per member where all of them fit LDS, else a
+    // launch per class (a member that fits joins it at no cost)
+    auto smooth = [&](int d, int sweeps, bool reverse) {
+        std::vector<dm_op *> at;
+        bool lds = true;
+        for (dm_op *op : b->ops)
+            if (d < op->nlev() - 1) {
+                at.push_back(op);
+                lds = lds && lds_at(op, d);
+            }
+        auto jobs_of = [&](auto &&fill) {
+            std::vector<BJob> v;
+            for (dm_op *op : at) {
+                const LevelBufs B = bufs(op, d);
+                BJob J = job(op, d);
+                J.in = B.f;
+                J.out = B.x;
+                fill(J, op);
+                v.push_back(J);
+            }
+            return v;
+        };
+        if (lds) {
+            add(BS_SWEEPS, 0, jobs_of([&](BJob &J, dm_op *op) {
+                    J.lds = op->lv[d].lds;
+                    J.sweeps = sweeps;
+                    J.reverse = reverse;
+                }));
+            return;
+        }
+        for (int it = 0; it < sweeps; ++it)
+            for (int q = 0; q < 6; ++q) {
+                const int cls = reverse ? 5 - q : q, comp = cls / 2, col = cls % 2;
+                add(BS_SMOOTH, comp, jobs_of([&](BJob &J, dm_op *op) {
+                        rows(J, op->lv[d].cut_list(comp, col, q % 2 == 0 ? kPairFirst : kPairSecond, op->cut_s));
+                    }));
+            }
     };
     for (int d = 0; d < dmax; ++d) {
         std::vector<BJob> zero, coarse, resid, restr;
@@ -70,10 +126,12 @@ std::vector<HostStep> schedule(dm_batch *b) {
             const int nl = op->nlev();
             if (d >= nl) continue;
             const LevelBufs B = bufs(op, d);
-            BJob z = job(op, d);
-            z.out = B.x;
-            z.items = 3 * z.g.P;
-            zero.push_back(z);
+            if (d == 0) {   // coarser iterates are set to zero by the restriction
+                BJob z = job(op, d);
+                z.out = B.x;
+                z.items = 3 * z.g.P;
+                zero.push_back(z);
+            }
             if (d == nl - 1) {
                 BJob c = job(op, d);
                 c.in = B.f;
@@ -83,57 +141,47 @@ std::vector<HostStep> schedule(dm_batch *b) {
                 c.ncoarse = op->nc;
                 c.items = op->nc;
                 coarse.push_back(c);
+                continue;
             }
+            // residual, restriction and prolongation visit the grid rows
+            // holding an active face: what they write is zero elsewhere
+            const Level &C = op->lv[d + 1];
+            BJob R = job(op, d);
+            R.in = B.f;
+            R.aux = B.x;
+            R.out = B.r;
+            rows(R, op->lv[d].cut_cells_rows());
+            resid.push_back(R);
+            BJob T = job(op, d);
+            T.in = B.r;
+            T.out = bufs(op, d + 1).f;
+            T.xz = bufs(op, d + 1).x;
+            T.rows = C.frows;
+            T.nrows = C.nfrows;
+            T.items = C.frows ? C.nfrows * T.gc.nx : cells(T.gc);
+            restr.push_back(T);
         }
-        add(BS_ZERO, 0, 0, zero);
-        add(BS_COARSE, 0, 0, coarse);
-        std::vector<BJob> sm;
-        for (dm_op *op : b->ops)
-            if (d < op->nlev() - 1) {
-                const LevelBufs B = bufs(op, d);
-                BJob J = job(op, d);
-                J.in = B.f;
-                J.out = B.x;
-                J.items = (int64_t)((J.g.nx + 1) >> 1) * J.g.ny * J.g.nz;
-                sm.push_back(J);
-                BJob R = job(op, d);
-                R.in = B.f;
-                R.aux = B.x;
-                R.out = B.r;
-                R.items = cells(R.g);
-                resid.push_back(R);
-                BJob T = job(op, d);
-                T.in = B.r;
-                T.out = bufs(op, d + 1).f;
-                T.items = cells(T.gc);
-                restr.push_back(T);
-            }
-        for (int it = 0; it < nu_pre; ++it)
-            for (int comp = 0; comp < 3; ++comp)
-                for (int col = 0; col < 2; ++col) add(BS_SMOOTH, comp, col, sm);
-        add(BS_RESID, 0, 0, resid);
-        add(BS_RESTRICT, 0, 0, restr);
+        add(BS_ZERO, 0, zero);
+        add(BS_COARSE, 0, coarse);
+        smooth(d, nu_pre, false);
+        add(BS_RESID, 0, resid);
+        add(BS_RESTRICT, 0, restr);
     }
     for (int d = dmax - 2; d >= 0; --d) {
-        std::vector<BJob> pro, sm;
+        std::vector<BJob> pro;
         for (dm_op *op : b->ops)
             if (d < op->nlev() - 1) {
-                const LevelBufs B = bufs(op, d);
+                const Level &L = op->lv[d];
                 BJob P = job(op, d);
                 P.in = bufs(op, d + 1).x;
-                P.out = B.x;
-                P.items = cells(P.g);
+                P.out = bufs(op, d).x;
+                P.rows = L.frows;
+                P.nrows = L.nfrows;
+                P.items = L.frows ? L.nfrows * P.g.nx : cells(P.g);
                 pro.push_back(P);
-                BJob J = job(op, d);
-                J.in = B.f;
-                J.out = B.x;
-                J.items = (int64_t)((J.g.nx + 1) >> 1) * J.g.ny * J.g.nz;
-                sm.push_back(J);
             }
-        add(BS_PROLONG, 0, 0, pro);
-        for (int it = 0; it < nu_post; ++it)
-            for (int comp = 2; comp >= 0; --comp)
-                for (int col = 1; col >= 0; --col) add(BS_SMOOTH, comp, col, sm);
+        add(BS_PROLONG, 0, pro);
+        smooth(d, nu_post, true);
     }
     return st;
 }
@@ -145,26 +193,51 @@ void free_tables(dm_batch *b) {
 
 // job tables for block size tpb, then the fused V-cycle recorded into a graph
 hipGraphExec_t capture(dm_batch *b, const std::vector<HostStep> &steps, int tpb) {
-    std::vector<std::pair<const BJob *, std::pair<int, int64_t>>> launches;
+    struct Launch {
+        const BJob *jobs;
+        const int32_t *job_of;
+        int64_t blocks;
+        size_t lds;
+    };
+    std::vector<Launch> launches;
+    auto table = [&](const void *host, size_t bytes) {
+        void *dev = nullptr;
+        DM_HIP(hipMalloc(&dev, bytes));
+        b->tables.push_back(dev);
+        DM_HIP(hipMemcpy(dev, host, bytes, hipMemcpyHostToDevice));
+        return dev;
+    };
     for (const HostStep &h : steps) {
         std::vector<BJob> jobs = h.jobs;
-        int64_t blocks = 0;
-        for (BJob &J : jobs) {
-            J.block0 = blocks;
-            blocks += h.kind == BS_COARSE ? J.items : std::max<int64_t>(1, cdiv(J.items, tpb));
+        std::vector<int32_t> job_of;
+        size_t lds = 0;
+        for (size_t q = 0; q < jobs.size(); ++q) {
+            BJob &J = jobs[q];
+            J.block0 = (int64_t)job_of.size();
+            int64_t blocks = 1;
+            if (h.kind == BS_COARSE) {
+                blocks = J.items;
+            } else if (h.kind == BS_SWEEPS) {
+                lds = std::max(lds, (size_t)(3 * J.g.P) * sizeof(float));
+            } else {
+                J.ncut = cdiv(J.n, tpb);
+                blocks = J.ncut + cdiv(J.items, tpb);
+            }
+            job_of.resize(job_of.size() + (size_t)blocks, (int32_t)q);
         }
-        void *dev = nullptr;
-        DM_HIP(hipMalloc(&dev, jobs.size() * sizeof(BJob)));
-        b->tables.push_back(dev);
-        DM_HIP(hipMemcpy(dev, jobs.data(), jobs.size() * sizeof(BJob), hipMemcpyHostToDevice));
-        launches.push_back({(const BJob *)dev, {(int)jobs.size(), blocks}});
+        if (h.kind != BS_SWEEPS)
+            while (job_of.size() % 8) job_of.push_back(-1);
+        if (job_of.empty()) job_of.assign(8, -1);
+        launches.push_back({(const BJob *)table(jobs.data(), jobs.size() * sizeof(BJob)),
+                            (const int32_t *)table(job_of.data(), job_of.size() * sizeof(int32_t)),
+                            (int64_t)job_of.size(), lds});
     }
     hipGraph_t gph = nullptr;
     hipGraphExec_t exec = nullptr;
     DM_HIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
     for (size_t q = 0; q < steps.size(); ++q)
-        launch_batched(steps[q].kind, steps[q].comp, steps[q].colour, launches[q].first, launches[q].second.first,
-                       launches[q].second.second, tpb, b->stream);
+        launch_batched(steps[q].kind, steps[q].comp, launches[q].jobs, launches[q].job_of, launches[q].blocks, tpb,
+                       launches[q].lds, b->stream);
     const hipError_t e1 = hipStreamEndCapture(b->stream, &gph);
     if (e1 != hipSuccess) {
         if (gph) (void)hipGraphDestroy(gph);

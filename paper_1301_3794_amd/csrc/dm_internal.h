@@ -273,34 +273,6 @@ __host__ __device__ constexpr CutTerm cut_term(int comp, int t) {
 }
 
 // ---------------------------------------------------------------------------
-// Batched launches: one launch performs the same V-cycle step for several
-// operators (cavities), each its own grid, coefficients and buffers.  A job
-// is one operator's share; its work items occupy blocks [block0, block0 +
-// its block count) of the launch.  Used only without PMC planes.
-// ---------------------------------------------------------------------------
-struct BJob {
-    Grid g, gc;           // the job's level (and the next coarser one)
-    const void *c;        // coefficient base of g (7 blocks + row classes)
-    const void *cc;       // coefficient base of gc
-    const void *in;       // f (smooth, residual), r (restrict), xc (prolong), f (coarse)
-    const void *aux;      // x (residual)
-    void *out;            // x (smooth, prolong, zero, coarse), r (residual), fc (restrict)
-    const double *inv;    // coarsest dense inverse (coarse)
-    const int64_t *idx;   // its active-face index (coarse)
-    int64_t items;        // work items of the job
-    int ncoarse;          // coarsest active faces (coarse)
-    double sigma;
-    int64_t block0;
-};
-
-enum BatchStep { BS_ZERO = 0, BS_SMOOTH, BS_RESID, BS_RESTRICT, BS_PROLONG, BS_COARSE };
-
-// one batched launch of `step` over `njobs` jobs (device array) covering
-// `nblocks` blocks of `tpb` threads (tpb <= 256; the coarse step uses 256)
-void launch_batched(int step, int comp, int colour, const BJob *jobs, int njobs, int64_t nblocks, int tpb,
-                    hipStream_t s);
-
-// ---------------------------------------------------------------------------
 // Kernel launchers (kernels.hip).  All take a stream; none synchronise.
 // ---------------------------------------------------------------------------
 enum ApplyKind { AK_M = 0, AK_K = 1, AK_RESID = 2 };
@@ -412,6 +384,52 @@ constexpr int64_t kLdsBytes = 160 * 1024;
 inline bool lds_level(int64_t P, int64_t faces, size_t elem) {
     return 3 * P * (int64_t)elem <= kLdsBytes && faces <= (elem == 4 ? 10240 : 6656);
 }
+
+// ---------------------------------------------------------------------------
+// Batched launches: one launch performs the same FP32 V-cycle step for several
+// operators (cavities), each its own grid, coefficients and buffers.  A job
+// is one operator's share; its work items occupy the logical blocks [block0,
+// block0 + its block count) of the launch.  Used only without PMC planes.
+// ---------------------------------------------------------------------------
+struct BJob {
+    Grid g, gc;           // the job's level (and the next coarser one)
+    const float *c, *cc;  // coefficient bases of g and gc (7 blocks + row classes)
+    const float *in;      // f (smooth, residual), r (restrict), xc (prolong), f (coarse)
+    const float *aux;     // x (residual)
+    float *out;           // x (smooth, prolong, zero, coarse), r (residual), fc (restrict)
+    float *xz;            // restrict: the coarse iterate, set to zero
+    const double *inv;    // coarsest dense inverse (coarse)
+    const int64_t *idx;   // its active-face index (coarse)
+    // smooth and residual: the class's or the level's rows (ClassList); the
+    // cut part takes the job's first ncut blocks, the runs the others
+    const int32_t *cut;
+    const float *w;
+    float *s;
+    const VacRun *runs;
+    const CellRun *cells;
+    int64_t n, ncut;
+    uint32_t nruns;
+    int run_log, colour, pair;
+    // transfers: the grid rows to visit
+    const int32_t *rows;
+    int64_t nrows;
+    // sweeps of an LDS level
+    LdsRows lds;
+    int sweeps, reverse;
+    int64_t items;        // work items of the job (smooth and residual: of the runs)
+    int ncoarse;          // coarsest active faces (coarse)
+    float sigma;
+    int64_t block0;
+};
+
+enum BatchStep { BS_ZERO = 0, BS_SMOOTH, BS_RESID, BS_RESTRICT, BS_PROLONG, BS_COARSE, BS_SWEEPS };
+
+// one batched launch of `step` over the jobs (device array); job_of (device)
+// names the job of every logical block, nblocks (a multiple of 8) of tpb
+// threads (tpb <= 256; the coarse step uses 256, the sweeps of LDS levels
+// one block of 1024 per job); lds: bytes of LDS per block of the sweeps
+void launch_batched(int step, int comp, const BJob *jobs, const int32_t *job_of, int64_t nblocks, int tpb,
+                    size_t lds, hipStream_t s);
 
 // Units of kSpanUnit consecutive doubles (one 128-byte line) of a level-0
 // face vector that can hold a nonzero entry: an active face, or a PMC ghost

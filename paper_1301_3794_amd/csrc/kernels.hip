@@ -93,43 +93,21 @@ __device__ inline T vac_row(const TX *C, int64_t p, int64_t dy, int64_t dz) {
            (T(C[p - dz]) + T(C[p + dz]));
 }
 
-// NR right-hand sides at once (block solves): the coefficients of a row are
-// loaded once and serve every vector; all rows are formed before any store.
-template <class T, int KIND, class TX = T>
-__device__ __forceinline__ void apply_body(const Grid &g, const Coefs<T> &c, T sigma, const T *__restrict__ f,
-                                           const TX *__restrict__ x, T *__restrict__ y, int64_t item) {
+// y = K x: rows keep their curl-curl cross terms (no vacuum shortcut)
+template <class T>
+__device__ __forceinline__ void apply_k_body(const Grid &g, const Coefs<T> &c, const T *__restrict__ x,
+                                             T *__restrict__ y, int64_t item) {
     int i, j, k;
     if (!cell_of(g, item, i, j, k)) return;
     const int64_t P = g.P, dy = g.sy, dz = g.sz;
     const int64_t p = pidx(g, i, j, k);
-    const TX *X = x, *Y = x + P, *Z = x + 2 * P;
+    const T *X = x, *Y = x + P, *Z = x + 2 * P;
     const T ih2 = inv_h2_of<T>(g);
     const uint8_t fl = c.flags[p];
     T yx = T(0), yy = T(0), yz = T(0);
-    if (KIND == AK_K) {
-        if (fl & (kFaceActive << 0)) yx = ih2 * row_x<T, false, TX>(c, X, Y, Z, p, dy, dz);
-        if (fl & (kFaceActive << 1)) yy = ih2 * row_y<T, false, TX>(c, X, Y, Z, p, dy, dz);
-        if (fl & (kFaceActive << 2)) yz = ih2 * row_z<T, false, TX>(c, X, Y, Z, p, dy, dz);
-    } else {
-        if (fl & (kFaceActive << 0)) {
-            yx = (fl & (kFaceVacuum << 0))
-                     ? ih2 * vac_row<T, TX>(X, p, dy, dz) - sigma * T(X[p])
-                     : ih2 * row_x<T, true, TX>(c, X, Y, Z, p, dy, dz) - sigma * c.ax[p] * T(X[p]);
-            if (KIND == AK_RESID) yx = f[p] - yx;
-        }
-        if (fl & (kFaceActive << 1)) {
-            yy = (fl & (kFaceVacuum << 1))
-                     ? ih2 * vac_row<T, TX>(Y, p, dy, dz) - sigma * T(Y[p])
-                     : ih2 * row_y<T, true, TX>(c, X, Y, Z, p, dy, dz) - sigma * c.ay[p] * T(Y[p]);
-            if (KIND == AK_RESID) yy = f[P + p] - yy;
-        }
-        if (fl & (kFaceActive << 2)) {
-            yz = (fl & (kFaceVacuum << 2))
-                     ? ih2 * vac_row<T, TX>(Z, p, dy, dz) - sigma * T(Z[p])
-                     : ih2 * row_z<T, true, TX>(c, X, Y, Z, p, dy, dz) - sigma * c.az[p] * T(Z[p]);
-            if (KIND == AK_RESID) yz = f[2 * P + p] - yz;
-        }
-    }
+    if (fl & (kFaceActive << 0)) yx = ih2 * row_x<T, false>(c, X, Y, Z, p, dy, dz);
+    if (fl & (kFaceActive << 1)) yy = ih2 * row_y<T, false>(c, X, Y, Z, p, dy, dz);
+    if (fl & (kFaceActive << 2)) yz = ih2 * row_z<T, false>(c, X, Y, Z, p, dy, dz);
     put_face<T>(g, y, 0, i, j, k, p, yx);
     put_face<T>(g, y + P, 1, i, j, k, p, yy);
     put_face<T>(g, y + 2 * P, 2, i, j, k, p, yz);
@@ -148,7 +126,7 @@ __device__ __forceinline__ void put_face_at(const Grid &g, T *arr, int comp, uin
     put_face<T>(g, arr, comp, (int)(rr - jj * sy) - 1, (int)jj - 1, (int)kk - 1, (int64_t)p, v);
 }
 
-// apply_body of M or the residual for lane `lane` of a run of cells whose
+// M x or f - M x at lane `lane` of a run of cells whose
 // active rows are all vacuum rows (the other cells are listed and run the
 // full body): the same values, written the same way, zeros on the inactive
 // components included.  (K alone has no vacuum shortcut: its rows keep the
@@ -182,11 +160,10 @@ __device__ __forceinline__ void apply_vac_body(const Grid &g, T sigma, const Cel
     }
 }
 
-template <class T, int KIND>
+template <class T>
 __global__ void __launch_bounds__(kThreads)
-k_apply(Grid g, Coefs<T> c, T sigma, const T *__restrict__ f, const T *__restrict__ x,
-        T *__restrict__ y) {
-    apply_body<T, KIND>(g, c, sigma, f, x, y, xcd_item());
+k_apply_K(Grid g, Coefs<T> c, const T *__restrict__ x, T *__restrict__ y) {
+    apply_k_body<T>(g, c, x, y, xcd_item());
 }
 
 // M x or f - M x at listed cell e (padded index p) from the cell's tabulated
@@ -268,51 +245,6 @@ k_apply_A(Grid g, Coefs<T> c, const T *__restrict__ x, T *__restrict__ y) {
 // A thread also refreshes the PMC ghost images of the value it updates; no
 // row of the same class reads those images except its own.
 // ---------------------------------------------------------------------------
-template <class T, int COMP, int NR>
-__device__ __forceinline__ void smooth_body_n(const Grid &g, const Coefs<T> &c, T sigma, int colour,
-                                              const VPtr<const T> &f, const VPtr<T> &x, int64_t t) {
-    const int nxh = (g.nx + 1) >> 1;
-    if (t >= (int64_t)nxh * g.ny * g.nz) return;
-    const int ih = (int)(t % nxh);
-    const int64_t r = t / nxh;
-    const int j = (int)(r % g.ny), k = (int)(r / g.ny);
-    const int i = 2 * ih + ((j + k + colour) & 1);
-    if (i >= g.nx) return;
-    const int64_t P = g.P, dy = g.sy, dz = g.sz;
-    const int64_t p = pidx(g, i, j, k);
-    const T ih2 = inv_h2_of<T>(g);
-    const uint8_t fl = c.flags[p];
-    if (!(fl & (kFaceActive << COMP))) return;
-    T nv[NR];
-    if (fl & (kFaceVacuum << COMP)) {
-        const T d = T(6) * ih2 - sigma;
-#pragma unroll
-        for (int q = 0; q < NR; ++q) {
-            const T *xc = x.p[q] + COMP * P;
-            const T xp = xc[p];
-            const T row = ih2 * vac_row<T>(xc, p, dy, dz) - sigma * xp;
-            nv[q] = xp + (f.p[q][COMP * P + p] - row) / d;
-        }
-    } else {
-        const T *a = COMP == 0 ? c.ax : (COMP == 1 ? c.ay : c.az);
-        const T d = diag_of<T>(c, COMP, p, dy, dz, ih2, sigma) +
-                    ih2 * pmc_diag_extra<T>(g, c.lx, c.ly, c.lz, COMP, i, j, k, p);
-#pragma unroll
-        for (int q = 0; q < NR; ++q) {
-            const T *X = x.p[q], *Y = X + P, *Z = X + 2 * P;
-            const T *xc = COMP == 0 ? X : (COMP == 1 ? Y : Z);
-            T row;
-            if (COMP == 0) row = row_x<T, true>(c, X, Y, Z, p, dy, dz);
-            else if (COMP == 1) row = row_y<T, true>(c, X, Y, Z, p, dy, dz);
-            else row = row_z<T, true>(c, X, Y, Z, p, dy, dz);
-            row = ih2 * row - sigma * a[p] * xc[p];
-            nv[q] = xc[p] + (f.p[q][COMP * P + p] - row) / d;
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < NR; ++q) put_face<T>(g, x.p[q] + COMP * P, COMP, i, j, k, p, nv[q]);
-}
-
 // The two parts of a class update: smooth_vac_n updates the class's vacuum
 // rows from their runs, smooth_cut_n entry e of the component's list of
 // non-vacuum rows.  Rows of one class do not read each other, so the parts
@@ -422,12 +354,6 @@ __device__ __forceinline__ void smooth_cut_n(const Grid &g, T sigma, const int32
     }
 #pragma unroll
     for (int q = 0; q < NR; ++q) put_face_at<T>(g, x.p[q] + COMP * P, COMP, p, nv[q]);
-}
-
-template <class T, int COMP>
-__device__ __forceinline__ void smooth_body(const Grid &g, const Coefs<T> &c, T sigma, int colour,
-                                            const T *__restrict__ f, T *__restrict__ x, int64_t t) {
-    smooth_body_n<T, COMP, 1>(g, c, sigma, colour, vptr1(f), vptr1(x), t);
 }
 
 // A class update from its two parts: the first ncb workgroups (a multiple of
@@ -1730,59 +1656,76 @@ __global__ void k_copy_masked(int64_t n, const double *__restrict__ in, const do
 
 // ---------------------------------------------------------------------------
 // Batched V-cycle steps (see BJob): the same bodies as the single-operator
-// kernels, the job found from the block index.
+// kernels.  A block finds its job in a table (one scalar load; a search over
+// the jobs' offsets took a dependent load per halving), and the XCDs, which
+// blocks reach round-robin, each take one run of logical blocks.
 // ---------------------------------------------------------------------------
-__device__ inline int find_job(const BJob *__restrict__ jobs, int nj, int64_t b) {
-    int lo = 0, hi = nj - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (jobs[mid].block0 <= b) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 template <int STEP, int COMP>
 __global__ void __launch_bounds__(kThreads)
-kb_step(const BJob *__restrict__ jobs, int nj, int colour) {
-    const BJob &J = jobs[find_job(jobs, nj, blockIdx.x)];
-    const int64_t lb = (int64_t)blockIdx.x - J.block0;
+kb_step(const BJob *__restrict__ jobs, const int32_t *__restrict__ job_of) {
+    const uint32_t L = blockIdx.x % kXcd * (gridDim.x / kXcd) + blockIdx.x / kXcd;
+    const int q = job_of[L];
+    if (q < 0) return;   // padding to a multiple of 8
+    const BJob &J = jobs[q];
+    const int64_t lb = (int64_t)L - J.block0;
     const int64_t item = lb * blockDim.x + threadIdx.x;
     using T = float;
     if (STEP == BS_ZERO) {
-        if (item < J.items) ((T *)J.out)[item] = T(0);
+        if (item < J.items) J.out[item] = T(0);
     } else if (STEP == BS_SMOOTH) {
-        smooth_body<T, COMP>(J.g, coefs_of((const T *)J.c, J.g.P), (T)J.sigma, colour, (const T *)J.in, (T *)J.out,
-                             item);
+        if (lb < J.ncut) {
+            if (item < J.n)
+                smooth_cut_n<T, COMP, 1>(J.g, J.sigma, J.cut, J.n, J.colour, J.w, J.pair, J.s, 0, vptr1(J.in),
+                                         vptr1(J.out), (uint32_t)item);
+        } else {
+            smooth_vac_n<T, COMP, 1>(J.g, J.sigma, vptr1(J.in), vptr1(J.out), (uint32_t)(item - J.ncut * blockDim.x),
+                                     J.runs, J.nruns, J.run_log);
+        }
     } else if (STEP == BS_RESID) {
-        apply_body<T, AK_RESID>(J.g, coefs_of((const T *)J.c, J.g.P), (T)J.sigma, (const T *)J.in,
-                                (const T *)J.aux, (T *)J.out, item);
+        if (lb < J.ncut) {
+            if (item < J.n)
+                apply_cut_tab<T, AK_RESID, T>(J.g, J.sigma, J.w, J.n, item, (uint32_t)J.cut[item], J.in, J.aux, J.out);
+        } else {
+            const uint32_t t = (uint32_t)(item - J.ncut * blockDim.x);
+            if (t >> J.run_log >= J.nruns) return;
+            const CellRun run = J.cells[t >> J.run_log];
+            const uint32_t lane = t & ((1u << J.run_log) - 1);
+            if ((run.visit >> lane) & 1) apply_vac_body<T, AK_RESID, T>(J.g, J.sigma, run, lane, J.in, J.aux, J.out);
+        }
     } else if (STEP == BS_RESTRICT) {
-        restrict_body<T>(J.g, J.gc, coefs_of((const T *)J.cc, J.gc.P), (const T *)J.in, (T *)J.out, item);
+        restrict_body<T>(J.g, J.gc, coefs_of(J.cc, J.gc.P), J.in, J.out, listed_item(J.gc, J.rows, J.nrows, item), J.xz);
     } else if (STEP == BS_PROLONG) {
-        prolong_body<T>(J.g, J.gc, coefs_of((const T *)J.c, J.g.P), coefs_of((const T *)J.cc, J.gc.P),
-                        (const T *)J.in, (T *)J.out, item);
+        prolong_body<T>(J.g, J.gc, coefs_of(J.c, J.g.P), coefs_of(J.cc, J.gc.P), J.in, J.out,
+                        listed_item(J.g, J.rows, J.nrows, item));
     } else {
-        coarse_body<T>(J.ncoarse, J.inv, J.idx, (const T *)J.in, (T *)J.out, (int)lb);
+        coarse_body<T>(J.ncoarse, J.inv, J.idx, J.in, J.out, (int)lb);
     }
+}
+
+__global__ void __launch_bounds__(kLdsThreads)
+kb_sweeps(const BJob *__restrict__ jobs) {
+    const BJob &J = jobs[blockIdx.x];
+    sweeps_lds_body<float, false>(J.g, J.sigma, J.lds, J.lds.w32, J.sweeps, J.reverse, !J.reverse, J.in, J.out,
+                                  reinterpret_cast<float *>(lds_raw));
 }
 
 }  // namespace
 
-void launch_batched(int step, int comp, int colour, const BJob *jobs, int njobs, int64_t nblocks, int tpb,
-                    hipStream_t s) {
+void launch_batched(int step, int comp, const BJob *jobs, const int32_t *job_of, int64_t nblocks, int tpb,
+                    size_t lds, hipStream_t s) {
     const dim3 grid((unsigned)nblocks), block((unsigned)(step == BS_COARSE ? kThreads : tpb));
     switch (step) {
-        case BS_ZERO: hipLaunchKernelGGL((kb_step<BS_ZERO, 0>), grid, block, 0, s, jobs, njobs, colour); break;
+        case BS_ZERO: hipLaunchKernelGGL((kb_step<BS_ZERO, 0>), grid, block, 0, s, jobs, job_of); break;
         case BS_SMOOTH:
-            if (comp == 0) hipLaunchKernelGGL((kb_step<BS_SMOOTH, 0>), grid, block, 0, s, jobs, njobs, colour);
-            else if (comp == 1) hipLaunchKernelGGL((kb_step<BS_SMOOTH, 1>), grid, block, 0, s, jobs, njobs, colour);
-            else hipLaunchKernelGGL((kb_step<BS_SMOOTH, 2>), grid, block, 0, s, jobs, njobs, colour);
+            if (comp == 0) hipLaunchKernelGGL((kb_step<BS_SMOOTH, 0>), grid, block, 0, s, jobs, job_of);
+            else if (comp == 1) hipLaunchKernelGGL((kb_step<BS_SMOOTH, 1>), grid, block, 0, s, jobs, job_of);
+            else hipLaunchKernelGGL((kb_step<BS_SMOOTH, 2>), grid, block, 0, s, jobs, job_of);
             break;
-        case BS_RESID: hipLaunchKernelGGL((kb_step<BS_RESID, 0>), grid, block, 0, s, jobs, njobs, colour); break;
-        case BS_RESTRICT: hipLaunchKernelGGL((kb_step<BS_RESTRICT, 0>), grid, block, 0, s, jobs, njobs, colour); break;
-        case BS_PROLONG: hipLaunchKernelGGL((kb_step<BS_PROLONG, 0>), grid, block, 0, s, jobs, njobs, colour); break;
-        default: hipLaunchKernelGGL((kb_step<BS_COARSE, 0>), grid, block, 0, s, jobs, njobs, colour); break;
+        case BS_RESID: hipLaunchKernelGGL((kb_step<BS_RESID, 0>), grid, block, 0, s, jobs, job_of); break;
+        case BS_RESTRICT: hipLaunchKernelGGL((kb_step<BS_RESTRICT, 0>), grid, block, 0, s, jobs, job_of); break;
+        case BS_PROLONG: hipLaunchKernelGGL((kb_step<BS_PROLONG, 0>), grid, block, 0, s, jobs, job_of); break;
+        case BS_SWEEPS: hipLaunchKernelGGL(kb_sweeps, grid, dim3(kLdsThreads), lds, s, jobs); break;
+        default: hipLaunchKernelGGL((kb_step<BS_COARSE, 0>), grid, block, 0, s, jobs, job_of); break;
     }
 }
 
@@ -1808,7 +1751,7 @@ void launch_apply(const Grid &g, const T *coef, T sigma, int kind, const T *f, c
         return;
     }
     const int64_t n = (int64_t)g.nx * g.ny * g.nz;
-    hipLaunchKernelGGL((k_apply<T, AK_K>), xcd_grid(n), dim3(kThreads), 0, s, g, coefs_of(coef, g.P), sigma, f, x, y);
+    hipLaunchKernelGGL((k_apply_K<T>), xcd_grid(n), dim3(kThreads), 0, s, g, coefs_of(coef, g.P), x, y);
 }
 
 template <class T>
