@@ -418,7 +418,9 @@ void vcycle(dm_op *op, int l, const T *f, T *x, hipStream_t s) {
     const Grid &g = L.g;
     const T sig = (T)op->sigma;
     const bool last = l == op->nlev() - 1, lds = !last && lds_level(g.P, L.n_act_faces, sizeof(T));
-    if (!lds) launch_zero<T>(3 * g.P, x, s);
+    // the iterate starts at zero: here on the finest level, on the coarser
+    // ones in the restriction that forms their right-hand side
+    if (l == 0 && !lds) launch_zero<T>(3 * g.P, x, s);
     if (last) {
         launch_coarse_solve<T>(op->nc, op->cinv, op->cidx, f, x, s);
         launch_mirror_faces<T>(g, x, s);
@@ -435,14 +437,16 @@ void vcycle(dm_op *op, int l, const T *f, T *x, hipStream_t s) {
                 launch_smooth<T>(g, sig, comp, f, x, s,
                                  L.cut_list(comp, col, col == 0 ? kPairFirst : kPairSecond, op->cut_s));
     T *r = Prec<T>::r(L);
-    launch_apply<T>(g, c, sig, AK_RESID, f, x, r, s, L.cut_cells());
+    // the residual and the transfers visit only the grid rows holding an
+    // active face: what they write stays zero on the others
+    launch_apply<T>(g, c, sig, AK_RESID, f, x, r, s, L.cut_cells_rows());
     Level &C = op->lv[l + 1];
     T *fc = Prec<T>::f(C), *xc = Prec<T>::x(C);
     const T *cc = Prec<T>::coef(C);
     // tilde form (eq. fullMat2): transfers A_c^1/2 R A_f^-1/2 and A_f^-1/2 P A_c^1/2
     const bool tilde = op->opt.tilde_transfers != 0;
     if (tilde) launch_scale_a<T>(3 * g.P, c, -1, r, s);
-    launch_restrict<T>(g, C.g, cc, r, fc, s);
+    launch_restrict_b<T>(g, C.g, cc, 1, vptr1<const T>(r), vptr1(fc), s, vptr1(xc), C.frows, C.nfrows);
     if (tilde) launch_scale_a<T>(3 * C.g.P, cc, +1, fc, s);
     vcycle<T>(op, l + 1, fc, xc, s);
     if (tilde) {
@@ -451,7 +455,7 @@ void vcycle(dm_op *op, int l, const T *f, T *x, hipStream_t s) {
         launch_prolong_add<T>(g, C.g, c, cc, xc, r, s);
         launch_add_scaled_a<T>(3 * g.P, c, r, x, s);
     } else {
-        launch_prolong_add<T>(g, C.g, c, cc, xc, x, s);
+        launch_prolong_add_b<T>(g, C.g, c, cc, 1, vptr1<const T>(xc), vptr1(x), s, L.frows, L.nfrows);
     }
     if (lds) launch_sweeps_lds<T>(g, sig, L.lds, op->opt.nu_post, 1, 0, 1, vptr1(f), vptr1(x), s);
     for (int it = 0; it < op->opt.nu_post && !lds; ++it)
