@@ -594,6 +594,34 @@ void launch_maxpy_mdot_norm(int nv, const double *V, int64_t ld, const double *c
 void launch_maxpy_mdot_norm(int nv, const float *V, int64_t ld, const double *c, double *w, int64_t n,
                             double *part, double *dout, hipStream_t s, const double *cscale = nullptr,
                             Span sp = {});
+// One system's part of a Gram--Schmidt step: basis columns V_i (i < nv), the
+// new column w, the update's coefficients c_i (times cscale_i if given) and
+// where its results go (device)
+template <class TV>
+struct BasisSys {
+    const TV *V;
+    double *w;
+    const double *c, *cscale;
+    double *dout;
+    int nv;
+};
+template <class TV>
+struct BasisArgs {
+    BasisSys<TV> s[kMaxRhs];
+};
+// The two passes of up to kMaxRhs systems, one launch each (and one for the
+// final sums): launch_mdot (without weights) and launch_maxpy_mdot_norm of
+// every system, nv <= kBasisMax; `part` as there
+constexpr int kBasisMax = 32;
+template <class TV>
+void launch_basis_dots(int nsys, const BasisArgs<TV> &A, int64_t ld, int64_t n, double *part, hipStream_t s,
+                       Span sp);
+template <class TV>
+void launch_basis_update(int nsys, const BasisArgs<TV> &A, int64_t ld, int64_t n, double *part, hipStream_t s,
+                         Span sp);
+// out_q = (TO) in_q for q < nr over the listed units of sp (all without)
+template <class TI, class TO>
+void launch_cast_b(int nr, const VPtr<const TI> &in, const VPtr<TO> &out, int64_t n, hipStream_t s, Span sp = {});
 // out = scale * (w - sum c_i V_i)
 void launch_maxpy_scale(int nv, const double *V, int64_t ld, const double *c, const double *w,
                         double scale, double *out, int64_t n, hipStream_t s);

@@ -654,6 +654,19 @@ __global__ void k_cast_units(const TI *__restrict__ in, TO *__restrict__ out, in
     }
 }
 
+// the casts of several vectors in one launch: grid row y takes vector y
+template <class TI, class TO>
+__global__ void __launch_bounds__(kThreads)
+k_cast_b(VPtr<const TI> in, VPtr<TO> out, int64_t n, const int32_t *__restrict__ units, int64_t nunits) {
+    const TI *__restrict__ a = in.p[blockIdx.y];
+    TO *__restrict__ b = out.p[blockIdx.y];
+    const int64_t cnt = units ? nunits * kSpanUnit : n;
+    for (int64_t it = (int64_t)blockIdx.x * kThreads + threadIdx.x; it < cnt; it += (int64_t)gridDim.x * kThreads) {
+        const int64_t e = units ? (int64_t)units[it / kSpanUnit] * kSpanUnit + it % kSpanUnit : it;
+        if (e < n) b[e] = (TO)a[e];
+    }
+}
+
 // Coarsest level: x[idx[r]] = sum_c inv[r, c] f[idx[c]] (FP64 arithmetic);
 // one row of the inverse serves every right-hand side
 template <class T, int NR>
@@ -1049,12 +1062,17 @@ __device__ __forceinline__ int64_t span_elem(const Span &sp, int64_t i) {
     return sp.u ? (int64_t)sp.u[i / per] * per + (i % per) : i;
 }
 
-// part[i][block] = partial sums of V_i . (w * wt) over the block's elements
+// part[i][block] = partial sums of V_i . (w * wt) over the block's elements;
+// grid row y takes system y of A (`rows` partial rows each)
 template <int VEC, class TV = double>
 __global__ void __launch_bounds__(kThreads)
-k_mdot(int nv, const TV *__restrict__ V, int64_t ld, const double *__restrict__ w,
-       const double *__restrict__ wt, int64_t n, double *__restrict__ part, Span sp) {
+k_mdot(BasisArgs<TV> A, int64_t ld, const double *__restrict__ wt, int64_t n, double *__restrict__ part0, int rows,
+       Span sp) {
     using O = Vec<VEC>;
+    const int nv = A.s[blockIdx.y].nv;
+    const TV *__restrict__ V = A.s[blockIdx.y].V;
+    const double *__restrict__ w = A.s[blockIdx.y].w;
+    double *__restrict__ part = part0 + (int64_t)blockIdx.y * rows * gridDim.x;
     const int64_t nvec = n / VEC, ldv = ld / VEC, cnt = span_count<VEC>(sp, nvec);
     for (int c0 = 0; c0 < nv; c0 += kChunk) {
         const int cn = min(kChunk, nv - c0);
@@ -1157,6 +1175,27 @@ k_mdot_final(int nblk, const double *__restrict__ part, double *__restrict__ out
         double t = 0.0;
         for (int u = 0; u < kThreads / 64; ++u) t += sh[u];
         out[v] = t;
+    }
+}
+
+// the final sums of k_mdot (extra = 0) and k_maxpy_mdot_norm (extra = 1):
+// block (v, y) sums partial row v of system y
+template <class TV>
+__global__ void __launch_bounds__(kThreads)
+k_basis_final(BasisArgs<TV> A, int nblk, const double *__restrict__ part, int rows, int extra) {
+    const int v = blockIdx.x;
+    if (v >= A.s[blockIdx.y].nv + extra) return;
+    const double *row = part + ((int64_t)blockIdx.y * rows + v) * nblk;
+    double s = 0.0;
+    for (int b = threadIdx.x; b < nblk; b += kThreads) s += row[b];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+    __shared__ double sh[kThreads / 64];
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int u = 0; u < kThreads / 64; ++u) t += sh[u];
+        A.s[blockIdx.y].dout[v] = t;
     }
 }
 
@@ -1462,10 +1501,13 @@ constexpr int kFuseMax = 32;
 // (144 VGPRs) stays faster than rereading (85).
 template <int VEC, int MAXV, bool REREAD, class TV = double>
 __global__ void __launch_bounds__(kThreads)
-k_maxpy_mdot_norm(int nv, const TV *__restrict__ V, int64_t ld, const double *__restrict__ c,
-                  const double *__restrict__ cscale, double *__restrict__ w, int64_t n, double *__restrict__ part,
-                  Span sp) {
+k_maxpy_mdot_norm(BasisArgs<TV> A, int64_t ld, int64_t n, double *__restrict__ part0, int rows, Span sp) {
     using O = Vec<VEC>;
+    const int nv = A.s[blockIdx.y].nv;
+    const TV *__restrict__ V = A.s[blockIdx.y].V;
+    const double *__restrict__ c = A.s[blockIdx.y].c, *__restrict__ cscale = A.s[blockIdx.y].cscale;
+    double *__restrict__ w = A.s[blockIdx.y].w;
+    double *__restrict__ part = part0 + (int64_t)blockIdx.y * rows * gridDim.x;
     __shared__ double cs[MAXV];
     for (int q = threadIdx.x; q < nv; q += kThreads) cs[q] = cscale ? c[q] * cscale[q] : c[q];
     __syncthreads();
@@ -2100,19 +2142,65 @@ inline void with_basis_width(int64_t n, int64_t ld, const TV *V, std::initialize
     f(std::integral_constant<int, 1>{});
 }
 
+// workgroups of a reduction over `items` grid-stride items: a short vector
+// takes no more than have an item (each further one would add a row of zeros
+// to sum and its own shuffles: 8.0 us per launch for the 16^3 grid's 8,700
+// pairs in 1,024 workgroups)
+inline int reduce_grid(int64_t items, int most = kReduceBlocks) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(most, ceil_div(items, kThreads)));
+}
+inline int64_t span_items(const Span &sp, int64_t n) { return sp.u ? sp.n * kSpanUnit : n; }
+
+template <class TV>
+void basis_dots(int nsys, const BasisArgs<TV> &A, int64_t ld, const double *wt, int64_t n, double *part,
+                hipStream_t s, Span sp) {
+    int rows = 0;
+    for (int q = 0; q < nsys; ++q) rows = std::max(rows, A.s[q].nv);
+    if (rows <= 0) return;
+    if (rows > 256 || (nsys > 1 && (rows + 1) * nsys > 256)) throw std::runtime_error("basis dots: too many vectors");
+    // the widest load that every system's pointers allow
+    int width = 4;
+    for (int q = 0; q < nsys; ++q)
+        with_basis_width(n, ld, A.s[q].V, {A.s[q].w, wt}, [&](auto w) { width = std::min(width, (int)decltype(w)::value); });
+    const int nb = reduce_grid(span_items(sp, n) / width);
+    const dim3 grid((unsigned)nb, (unsigned)nsys);
+    if (sizeof(TV) == 4 && width == 4)
+        hipLaunchKernelGGL((k_mdot<sizeof(TV) == 4 ? 4 : 2, TV>), grid, dim3(kThreads), 0, s, A, ld, wt, n, part, rows, sp);
+    else if (width >= 2)
+        hipLaunchKernelGGL((k_mdot<2, TV>), grid, dim3(kThreads), 0, s, A, ld, wt, n, part, rows, sp);
+    else
+        hipLaunchKernelGGL((k_mdot<1, TV>), grid, dim3(kThreads), 0, s, A, ld, wt, n, part, rows, sp);
+    hipLaunchKernelGGL(k_basis_final<TV>, dim3((unsigned)rows, (unsigned)nsys), dim3(kThreads), 0, s, A, nb,
+                       (const double *)part, rows, 0);
+}
+
 template <class TV>
 void launch_mdot_t(int nv, const TV *V, int64_t ld, const double *w, const double *wt, int64_t n, double *part,
                    double *dout, hipStream_t s, Span sp) {
-    if (nv <= 0) return;
     if (nv > 256) throw std::runtime_error("launch_mdot: more than 256 vectors");
-    with_basis_width(n, ld, V, {w, wt}, [&](auto width) {
-        constexpr int W = decltype(width)::value;
-        hipLaunchKernelGGL((k_mdot<W, TV>), dim3(kReduceBlocks), dim3(kThreads), 0, s, nv, V, ld, w, wt, n, part, sp);
-    });
-    hipLaunchKernelGGL(k_mdot_final, dim3(nv), dim3(kThreads), 0, s, (int)kReduceBlocks,
-                       (const double *)part, dout);
+    BasisArgs<TV> A{};
+    A.s[0] = {V, const_cast<double *>(w), nullptr, nullptr, dout, nv};
+    basis_dots<TV>(1, A, ld, wt, n, part, s, sp);
 }
 }  // namespace
+
+template <class TV>
+void launch_basis_dots(int nsys, const BasisArgs<TV> &A, int64_t ld, int64_t n, double *part, hipStream_t s,
+                       Span sp) {
+    basis_dots<TV>(nsys, A, ld, nullptr, n, part, s, sp);
+}
+template void launch_basis_dots<double>(int, const BasisArgs<double> &, int64_t, int64_t, double *, hipStream_t, Span);
+template void launch_basis_dots<float>(int, const BasisArgs<float> &, int64_t, int64_t, double *, hipStream_t, Span);
+
+template <class TI, class TO>
+void launch_cast_b(int nr, const VPtr<const TI> &in, const VPtr<TO> &out, int64_t n, hipStream_t s, Span sp) {
+    const dim3 grid(flat_grid(span_items(sp, n)).x, (unsigned)nr);
+    hipLaunchKernelGGL((k_cast_b<TI, TO>), grid, dim3(kThreads), 0, s, in, out, n, sp.u, sp.n);
+}
+template void launch_cast_b<double, double>(int, const VPtr<const double> &, const VPtr<double> &, int64_t, hipStream_t, Span);
+template void launch_cast_b<double, float>(int, const VPtr<const double> &, const VPtr<float> &, int64_t, hipStream_t, Span);
+template void launch_cast_b<float, double>(int, const VPtr<const float> &, const VPtr<double> &, int64_t, hipStream_t, Span);
+template void launch_cast_b<float, float>(int, const VPtr<const float> &, const VPtr<float> &, int64_t, hipStream_t, Span);
 
 void launch_mdot(int nv, const double *V, int64_t ld, const double *w, const double *wt,
                  int64_t n, double *part, double *dout, hipStream_t s, Span sp) {
@@ -2140,12 +2228,12 @@ void launch_mdot_multi(int nv, const double *V, int64_t ld, const double *W, int
     if (nv <= 0 || nw <= 0) return;
     if (nw > kMultiMax || nv * nw > 256) throw std::runtime_error("launch_mdot_multi: too many products");
     const bool v2 = vec2_ok(n, ld, {V, W, wt}) && (ldw % 2 == 0);
-    const dim3 g(kReduceBlocks), b(kThreads);
+    const int nb = reduce_grid(span_items(sp, n) / (v2 ? 2 : 1));
+    const dim3 g((unsigned)nb), b(kThreads);
     if (v2) DM_NW_SWITCH(nw, hipLaunchKernelGGL((k_mdot_multi<2, NW, CH>), g, b, 0, s, nv, V, ld, W, ldw, wt, n, part,
                                                 sp))
     else DM_NW_SWITCH(nw, hipLaunchKernelGGL((k_mdot_multi<1, NW, CH>), g, b, 0, s, nv, V, ld, W, ldw, wt, n, part, sp))
-    hipLaunchKernelGGL(k_mdot_final, dim3(nv * nw), dim3(kThreads), 0, s, (int)kReduceBlocks,
-                       (const double *)part, dout);
+    hipLaunchKernelGGL(k_mdot_final, dim3(nv * nw), dim3(kThreads), 0, s, nb, (const double *)part, dout);
 }
 
 void launch_maxpy_multi(int nv, const double *V, int64_t ld, const double *C, int nw, double *Y, int64_t ldy,
@@ -2217,36 +2305,67 @@ int reduce_blocks() {
 }
 
 namespace {
+// the fused update of nsys systems, nv <= 32: the basis held in registers, or
+// read twice where they do not fit
+template <class TV>
+void basis_update(int nsys, const BasisArgs<TV> &A, int64_t ld, int64_t n, double *part, hipStream_t s, Span sp) {
+    int nv = 0;
+    for (int q = 0; q < nsys; ++q) nv = std::max(nv, A.s[q].nv);
+    const int rows = nv + 1;
+    if (nv < 1 || nv > kBasisMax) throw std::runtime_error("basis update: 1 to 32 vectors");
+    int width = 4, nb = 0;
+    for (int q = 0; q < nsys; ++q)
+        with_basis_width(n, ld, A.s[q].V, {A.s[q].w}, [&](auto w) { width = std::min(width, (int)decltype(w)::value); });
+    auto fused = [&](auto kern, int most) {
+        nb = reduce_grid(span_items(sp, n) / width, most);
+        hipLaunchKernelGGL(kern, dim3((unsigned)nb, (unsigned)nsys), dim3(kThreads), 0, s, A, ld, n, part, rows, sp);
+    };
+    auto by_size = [&](auto w) {
+        constexpr int W = decltype(w)::value;
+        if (nv <= 8) fused(k_maxpy_mdot_norm<W, 8, false, TV>, reduce_blocks<k_maxpy_mdot_norm<W, 8, false, TV>>());
+        else if (nv <= 16) fused(k_maxpy_mdot_norm<W, 16, false, TV>, reduce_blocks<k_maxpy_mdot_norm<W, 16, false, TV>>());
+        else fused(k_maxpy_mdot_norm<W, 32, true, TV>, reduce_blocks<k_maxpy_mdot_norm<W, 32, true, TV>>());
+    };
+    if constexpr (sizeof(TV) == 4) {
+        if (width == 4) by_size(std::integral_constant<int, 4>{});
+    }
+    if (width < 4 || sizeof(TV) == 8) {
+        if (width >= 2) by_size(std::integral_constant<int, 2>{});
+        else by_size(std::integral_constant<int, 1>{});
+    }
+    hipLaunchKernelGGL(k_basis_final<TV>, dim3((unsigned)rows, (unsigned)nsys), dim3(kThreads), 0, s, A, nb,
+                       (const double *)part, rows, 1);
+}
+
 template <class TV>
 void launch_maxpy_mdot_norm_t(int nv, const TV *V, int64_t ld, const double *c, double *w, int64_t n,
                               double *part, double *dout, hipStream_t s, const double *cscale, Span sp) {
     if (nv < 1 || nv + 1 > 256) throw std::runtime_error("launch_maxpy_mdot_norm: nv out of range");
+    if (nv <= kBasisMax) {
+        BasisArgs<TV> A{};
+        A.s[0] = {V, w, c, cscale, dout, nv};
+        basis_update<TV>(1, A, ld, n, part, s, sp);
+        return;
+    }
+    // too many vectors to hold in registers: update w, then a second pass for
+    // the dots (the basis is read twice)
     const dim3 b(kThreads);
-    int nb = kReduceBlocks;
-    // one fused kernel for nv <= 32 (the basis held in registers)
-    auto fused = [&](auto kern, int blocks) {
-        nb = blocks;
-        hipLaunchKernelGGL(kern, dim3(nb), b, 0, s, nv, V, ld, c, cscale, w, n, part, sp);
-    };
     with_basis_width(n, ld, V, {w}, [&](auto width) {
         constexpr int W = decltype(width)::value;
-        if (nv <= 8) {
-            fused(k_maxpy_mdot_norm<W, 8, false, TV>, reduce_blocks<k_maxpy_mdot_norm<W, 8, false, TV>>());
-        } else if (nv <= 16) {
-            fused(k_maxpy_mdot_norm<W, 16, false, TV>, reduce_blocks<k_maxpy_mdot_norm<W, 16, false, TV>>());
-        } else if (nv <= 32) {
-            fused(k_maxpy_mdot_norm<W, 32, true, TV>, reduce_blocks<k_maxpy_mdot_norm<W, 32, true, TV>>());
-        } else {
-            // too many vectors to hold in registers: update w, then a second
-            // pass for the dots (the basis is read twice)
-            launch_maxpy_t<TV>(nv, V, ld, c, w, n, 0, s, cscale, sp);
-            hipLaunchKernelGGL((k_mdot_norm<W, TV>), dim3(kReduceBlocks), b, 0, s, nv, V, ld, (const double *)w, n,
-                               part, sp);
-        }
+        launch_maxpy_t<TV>(nv, V, ld, c, w, n, 0, s, cscale, sp);
+        hipLaunchKernelGGL((k_mdot_norm<W, TV>), dim3(kReduceBlocks), b, 0, s, nv, V, ld, (const double *)w, n, part, sp);
     });
-    hipLaunchKernelGGL(k_mdot_final, dim3(nv + 1), dim3(kThreads), 0, s, nb, (const double *)part, dout);
+    hipLaunchKernelGGL(k_mdot_final, dim3(nv + 1), dim3(kThreads), 0, s, (int)kReduceBlocks, (const double *)part, dout);
 }
 }  // namespace
+
+template <class TV>
+void launch_basis_update(int nsys, const BasisArgs<TV> &A, int64_t ld, int64_t n, double *part, hipStream_t s,
+                         Span sp) {
+    basis_update<TV>(nsys, A, ld, n, part, s, sp);
+}
+template void launch_basis_update<double>(int, const BasisArgs<double> &, int64_t, int64_t, double *, hipStream_t, Span);
+template void launch_basis_update<float>(int, const BasisArgs<float> &, int64_t, int64_t, double *, hipStream_t, Span);
 
 void launch_maxpy_mdot_norm(int nv, const double *V, int64_t ld, const double *c, double *w,
                             int64_t n, double *part, double *dout, hipStream_t s, const double *cscale,
@@ -2279,9 +2398,10 @@ void launch_dot_pairs(int nr, const VPtr<const double> &X, const VPtr<const doub
     }
     bool v2 = vec2_ok(n, 0, {wt});
     for (int q = 0; q < nr; ++q) v2 = v2 && vec2_ok(n, 0, {x.p[q], y.p[q]});
-    if (v2) hipLaunchKernelGGL(k_dot_pairs<2>, dim3(kReduceBlocks), dim3(kThreads), 0, s, x, y, wt, n, part, sp);
-    else hipLaunchKernelGGL(k_dot_pairs<1>, dim3(kReduceBlocks), dim3(kThreads), 0, s, x, y, wt, n, part, sp);
-    hipLaunchKernelGGL(k_mdot_final_strided, dim3(nr), dim3(kThreads), 0, s, (int)kReduceBlocks,
+    const int nb = reduce_grid(span_items(sp, n) / (v2 ? 2 : 1));
+    if (v2) hipLaunchKernelGGL(k_dot_pairs<2>, dim3(nb), dim3(kThreads), 0, s, x, y, wt, n, part, sp);
+    else hipLaunchKernelGGL(k_dot_pairs<1>, dim3(nb), dim3(kThreads), 0, s, x, y, wt, n, part, sp);
+    hipLaunchKernelGGL(k_mdot_final_strided, dim3(nr), dim3(kThreads), 0, s, nb,
                        (const double *)part, dout, dstride);
 }
 
@@ -2291,8 +2411,9 @@ void launch_cg_update(int nr, const VPtr<const double> &Pv, const VPtr<const dou
     if (nr < 1 || nr > kMaxRhs) throw std::runtime_error("launch_cg_update: 1 to 4 vectors");
     VPtr<const double> pv{};
     for (int q = 0; q < nr; ++q) pv.p[q] = Pv.p[q];
-    hipLaunchKernelGGL(k_cg_update, dim3(kReduceBlocks), dim3(kThreads), 0, s, pv, Qv, Psi, R, a, wt, n, part, sp);
-    hipLaunchKernelGGL(k_mdot_final_strided, dim3(nr), dim3(kThreads), 0, s, (int)kReduceBlocks,
+    const int nb = reduce_grid(span_items(sp, n));
+    hipLaunchKernelGGL(k_cg_update, dim3(nb), dim3(kThreads), 0, s, pv, Qv, Psi, R, a, wt, n, part, sp);
+    hipLaunchKernelGGL(k_mdot_final_strided, dim3(nr), dim3(kThreads), 0, s, nb,
                        (const double *)part, dout, dstride);
 }
 

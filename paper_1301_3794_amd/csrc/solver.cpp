@@ -75,6 +75,14 @@ VPtr<T> slots(T *base, int64_t stride, int nr) {
     return v;
 }
 
+// an array of nr pointers as a launch argument
+template <class T>
+VPtr<T> vptrs(int nr, T *const *v) {
+    VPtr<T> x{};
+    for (int q = 0; q < nr; ++q) x.p[q] = v[q];
+    return x;
+}
+
 double now_s() {
     return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
 }
@@ -914,9 +922,9 @@ void precondition_block(dm_op *op, int mode, int nr, const double *const *v, dou
         // the V-cycle reads f on active rows only, and z is zero outside the
         // listed units (written only here)
         const Span sp = op->vspan();
-        for (int q = 0; q < nr; ++q) launch_cast<double, float>(v[q], op->lv[0].bf32 + q * n, n, s, sp);
+        launch_cast_b<double, float>(nr, vptrs(nr, v), slots(op->lv[0].bf32, n, nr), n, s, sp);
         vcycle_block_graphed(op, 32, nr, s);
-        for (int q = 0; q < nr; ++q) launch_cast<float, double>(op->lv[0].bx32 + q * n, z[q], n, s, sp);
+        launch_cast_b<float, double>(nr, as_const(slots(op->lv[0].bx32, n, nr)), vptrs(nr, z), n, s, sp);
         if (mode == DM_SOLVE_FGMRES_MG32_LEARNED)
             for (int q = 0; q < nr; ++q) {
                 int none = 0;
@@ -924,9 +932,10 @@ void precondition_block(dm_op *op, int mode, int nr, const double *const *v, dou
             }
     } else {
         ensure_block(op, 64);
-        for (int q = 0; q < nr; ++q) launch_copy(n, v[q], op->lv[0].bf64 + q * n, s);
+        const Span sp = op->vspan();
+        launch_cast_b<double, double>(nr, vptrs(nr, v), slots(op->lv[0].bf64, n, nr), n, s, sp);
         vcycle_block_graphed(op, 64, nr, s);
-        for (int q = 0; q < nr; ++q) launch_copy(n, op->lv[0].bx64 + q * n, z[q], s);
+        launch_cast_b<double, double>(nr, as_const(slots(op->lv[0].bx64, n, nr)), vptrs(nr, z), n, s, sp);
     }
 }
 
@@ -940,9 +949,9 @@ void precondition_block_f32(dm_op *op, int nr, const TV *const *v, float *const 
     const int64_t n = op->n0();
     ensure_block(op, 32);
     const Span sp = op->vspan();
-    for (int q = 0; q < nr; ++q) launch_cast<TV, float>(v[q], op->lv[0].bf32 + q * n, n, s, sp);
+    launch_cast_b<TV, float>(nr, vptrs(nr, v), slots(op->lv[0].bf32, n, nr), n, s, sp);
     vcycle_block_graphed(op, 32, nr, s);
-    for (int q = 0; q < nr; ++q) launch_cast<float, float>(op->lv[0].bx32 + q * n, z[q], n, s, sp);
+    launch_cast_b<float, float>(nr, as_const(slots(op->lv[0].bx32, n, nr)), vptrs(nr, z), n, s, sp);
 }
 
 struct BlockRhs {
@@ -1126,16 +1135,43 @@ int fgmres_block(dm_op *op, int mode, int nb, const double *const *f, double *co
         // Gram--Schmidt as in fgmres(): (1) d = U^T w, (2) w -= U (sc^2 d)
         // fused with d2 = U^T w and |w|^2, every open system, one sync
         send_sc2();
+        // every system in one launch per pass while their bases together stay
+        // in the Infinity Cache between the passes (256 MB; half of it here,
+        // the rest holds what else the step streams) -- else system by
+        // system, so that each one's second pass finds its basis there
+        int64_t columns = 0;
+        int longest = 0;
         for (int r : act) {
-            const int j = st[r].j;
-            if (b32) {
-                launch_mdot(j + 1, Vc32(r, 0), ld, Fc(r, j + 1), nullptr, n, op->part, dres(r), s, sp);
-                launch_maxpy_mdot_norm(j + 1, Vc32(r, 0), ld, dres(r), Fc(r, j + 1), n, op->part, dres2(r), s,
-                                       dsc2(r), sp);
-            } else {
-                launch_mdot(j + 1, Vc(r, 0), ld, Vc(r, j + 1), nullptr, n, op->part, dres(r), s, sp);
-                launch_maxpy_mdot_norm(j + 1, Vc(r, 0), ld, dres(r), Vc(r, j + 1), n, op->part, dres2(r), s,
-                                       dsc2(r), sp);
+            columns += st[r].j + 1;
+            longest = std::max(longest, st[r].j + 1);
+        }
+        const int64_t column_bytes = (sp.u ? sp.n * kSpanUnit : n) * (b32 ? 4 : 8);
+        auto gram_schmidt = [&](auto base, const std::vector<int> &rs) {
+            using TV = std::remove_const_t<std::remove_pointer_t<decltype(base(0))>>;
+            BasisArgs<TV> D{}, U{};
+            for (size_t q = 0; q < rs.size(); ++q) {
+                const int r = rs[q], j = st[r].j;
+                D.s[q] = {base(r), Fc(r, j + 1), nullptr, nullptr, dres(r), j + 1};
+                U.s[q] = {base(r), Fc(r, j + 1), dres(r), dsc2(r), dres2(r), j + 1};
+            }
+            launch_basis_dots<TV>((int)rs.size(), D, ld, n, op->part, s, sp);
+            launch_basis_update<TV>((int)rs.size(), U, ld, n, op->part, s, sp);
+        };
+        if (na > 1 && longest <= kBasisMax && columns * column_bytes <= (128ll << 20)) {
+            if (b32) gram_schmidt([&](int r) { return Vc32(r, 0); }, act);
+            else gram_schmidt([&](int r) { return Vc(r, 0); }, act);
+        } else {
+            for (int r : act) {
+                const int j = st[r].j;
+                if (b32) {
+                    launch_mdot(j + 1, Vc32(r, 0), ld, Fc(r, j + 1), nullptr, n, op->part, dres(r), s, sp);
+                    launch_maxpy_mdot_norm(j + 1, Vc32(r, 0), ld, dres(r), Fc(r, j + 1), n, op->part, dres2(r), s,
+                                           dsc2(r), sp);
+                } else {
+                    launch_mdot(j + 1, Vc(r, 0), ld, Vc(r, j + 1), nullptr, n, op->part, dres(r), s, sp);
+                    launch_maxpy_mdot_norm(j + 1, Vc(r, 0), ld, dres(r), Vc(r, j + 1), n, op->part, dres2(r), s,
+                                           dsc2(r), sp);
+                }
             }
         }
         // dres2 follows dres: one copy brings both
