@@ -89,45 +89,57 @@ double now_s() {
 
 // Symmetric eigendecomposition of a small dense matrix by cyclic Jacobi
 // rotations.  a: n x n row-major (destroyed); w: eigenvalues; v: columns.
+// An off-diagonal entry that no longer changes either diagonal entry in
+// double precision (a hundred times over) is dropped, and the sweeps end when
+// none was left to rotate: 7 or 8 sweeps.  (A threshold on the off-diagonal
+// norm at the rounding level was often never met and all 100 sweeps ran: 17
+// ms for n = 44, twice per outer step.)  A rotation works on the contiguous
+// rows p and q and mirrors them into the columns; the vectors are kept as
+// rows until the end: 0.7 ms for n = 44.
 void jacobi_eig(std::vector<double> a, int n, std::vector<double> &w, std::vector<double> &v) {
-    v.assign((size_t)n * n, 0.0);
-    for (int i = 0; i < n; ++i) v[(size_t)i * n + i] = 1.0;
+    std::vector<double> vt((size_t)n * n, 0.0);
+    for (int i = 0; i < n; ++i) vt[(size_t)i * n + i] = 1.0;
+    auto rotate = [n](double *x, double *y, double c, double s) {
+        for (int k = 0; k < n; ++k) {
+            const double xk = x[k], yk = y[k];
+            x[k] = c * xk - s * yk;
+            y[k] = s * xk + c * yk;
+        }
+    };
     for (int sweep = 0; sweep < 100; ++sweep) {
-        double off = 0.0, tot = 0.0;
-        for (int i = 0; i < n; ++i)
-            for (int j = 0; j < n; ++j) {
-                const double x = a[(size_t)i * n + j] * a[(size_t)i * n + j];
-                tot += x;
-                if (i != j) off += x;
-            }
-        if (off <= 1e-32 * tot || off == 0.0) break;
+        bool rotated = false;
         for (int p = 0; p < n - 1; ++p)
             for (int q = p + 1; q < n; ++q) {
-                const double apq = a[(size_t)p * n + q];
+                double *ap = &a[(size_t)p * n], *aq = &a[(size_t)q * n];
+                const double apq = ap[q];
                 if (apq == 0.0) continue;
-                const double app = a[(size_t)p * n + p], aqq = a[(size_t)q * n + q];
+                const double app = ap[p], aqq = aq[q], g = 100.0 * std::fabs(apq);
+                if (std::fabs(app) + g == std::fabs(app) && std::fabs(aqq) + g == std::fabs(aqq)) {
+                    ap[q] = aq[p] = 0.0;
+                    continue;
+                }
+                rotated = true;
                 const double theta = (aqq - app) / (2.0 * apq);
                 const double t = (theta >= 0 ? 1.0 : -1.0) / (std::fabs(theta) + std::sqrt(theta * theta + 1.0));
                 const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
+                rotate(ap, aq, c, s);
+                ap[p] = app - t * apq;
+                aq[q] = aqq + t * apq;
+                ap[q] = aq[p] = 0.0;
                 for (int k = 0; k < n; ++k) {
-                    const double akp = a[(size_t)k * n + p], akq = a[(size_t)k * n + q];
-                    a[(size_t)k * n + p] = c * akp - s * akq;
-                    a[(size_t)k * n + q] = s * akp + c * akq;
+                    a[(size_t)k * n + p] = ap[k];
+                    a[(size_t)k * n + q] = aq[k];
                 }
-                for (int k = 0; k < n; ++k) {
-                    const double apk = a[(size_t)p * n + k], aqk = a[(size_t)q * n + k];
-                    a[(size_t)p * n + k] = c * apk - s * aqk;
-                    a[(size_t)q * n + k] = s * apk + c * aqk;
-                }
-                for (int k = 0; k < n; ++k) {
-                    const double vkp = v[(size_t)k * n + p], vkq = v[(size_t)k * n + q];
-                    v[(size_t)k * n + p] = c * vkp - s * vkq;
-                    v[(size_t)k * n + q] = s * vkp + c * vkq;
-                }
+                rotate(&vt[(size_t)p * n], &vt[(size_t)q * n], c, s);
             }
+        if (!rotated) break;
     }
     w.resize(n);
-    for (int i = 0; i < n; ++i) w[i] = a[(size_t)i * n + i];
+    v.resize((size_t)n * n);
+    for (int i = 0; i < n; ++i) {
+        w[i] = a[(size_t)i * n + i];
+        for (int k = 0; k < n; ++k) v[(size_t)k * n + i] = vt[(size_t)i * n + k];
+    }
 }
 
 void to_device_coef(dm_op *op, const double *h, int nv, hipStream_t s) {
