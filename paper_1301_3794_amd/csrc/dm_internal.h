@@ -625,27 +625,39 @@ void launch_cast_b(int nr, const VPtr<const TI> &in, const VPtr<TO> &out, int64_
 // out = scale * (w - sum c_i V_i)
 void launch_maxpy_scale(int nv, const double *V, int64_t ld, const double *c, const double *w,
                         double scale, double *out, int64_t n, hipStream_t s);
-// Per-vector scalars of a block launch, passed by value
-struct Coef4 {
-    double v[kMaxRhs] = {};
+// The scalars of up to kMaxRhs conjugate-gradient solves in lockstep, on the
+// device: the steps read and write them there, so that a whole iteration is
+// one graph and the host only looks at `act` between iterations
+struct CgState {
+    double rz[kMaxRhs], alpha[kMaxRhs], beta[kMaxRhs], stop[kMaxRhs];
+    int act[kMaxRhs], its[kMaxRhs];
 };
+// what the final sum of a reduction is turned into, for every active solve
+//   kCgAlpha: s = p . S p: alpha = rz / s and one more iteration, or the end of
+//             a solve whose s is not positive
+//   kCgCheck: s = |r|^2: the solve ends when sqrt(s) <= stop
+//   kCgBeta:  s = r . z: beta = s / rz (0 before the first iteration), rz = s
+enum CgStep { kCgAlpha = 0, kCgCheck, kCgBeta };
 // Block forms for the conjugate-gradient solves of the projection; each acts
-// on the vector slots q < nr whose first pointer is set, results to
-// dout[q * dstride] (device), `part` scratch of kMaxRhs * kReduceBlocks doubles:
-//   dot_pairs: dout[q] = X_q . (Y_q * wt)     (wt optional, read once)
-//   cg_update: psi_q += a_q p_q, r_q -= a_q q_q, dout[q] = r_q . (r_q * wt)
-//   xpby_b:    Y_q = X_q + b_q Y_q
+// on the vector slots q < nr, `part` scratch of kMaxRhs * kReduceBlocks doubles:
+//   dot_pairs: dout[q * dstride] = X_q . (Y_q * wt)     (wt optional, read once)
+//   cg_dot:    the same sums turned into scalars of st
+//   cg_update: psi_q += alpha p_q, r_q -= alpha q_q for the active solves, and
+//              |r_q|^2 (weights wt) checked against their stop
+//   cg_xpby:   Y_q = X_q + beta Y_q for the active solves
 //   sub_masked_b: X_q -= scale * val[q * stride] where mask != 0
-// The first three visit only the listed units of sp (the whole vectors
+// All but the last visit only the listed units of sp (the whole vectors
 // without a list): every vector they read is zero outside those units, and
 // what they write is left untouched there.
 void launch_dot_pairs(int nr, const VPtr<const double> &X, const VPtr<const double> &Y, const double *wt,
                       int64_t n, double *part, double *dout, int64_t dstride, hipStream_t s, Span sp = {});
+void launch_cg_dot(int nr, const VPtr<const double> &X, const VPtr<const double> &Y, const double *wt, int64_t n,
+                   double *part, CgStep step, CgState *st, hipStream_t s, Span sp);
 void launch_cg_update(int nr, const VPtr<const double> &Pv, const VPtr<const double> &Qv, const VPtr<double> &Psi,
-                      const VPtr<double> &R, const Coef4 &a, const double *wt, int64_t n, double *part, double *dout,
-                      int64_t dstride, hipStream_t s, Span sp = {});
-void launch_xpby_b(int nr, const VPtr<const double> &X, const Coef4 &b, const VPtr<double> &Y, int64_t n,
-                   hipStream_t s, Span sp = {});
+                      const VPtr<double> &R, const double *wt, int64_t n, double *part, CgState *st, hipStream_t s,
+                      Span sp);
+void launch_cg_xpby(int nr, const VPtr<const double> &X, const VPtr<double> &Y, int64_t n, const CgState *st,
+                    hipStream_t s, Span sp);
 void launch_sub_masked_b(int nr, int64_t n, const double *mask, const double *val, int64_t stride, double scale,
                          const VPtr<double> &X, hipStream_t s);
 // masked shift: x[n] -= scale * val[0] where mask[n] != 0 (val on device)

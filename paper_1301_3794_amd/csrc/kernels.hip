@@ -1261,15 +1261,49 @@ k_mdot_final_strided(int nblk, const double *__restrict__ part, double *__restri
     }
 }
 
-// One conjugate-gradient update of the vectors with Pv_q set:
+// block q: the sum of partial row q, turned into solve q's scalars (CgStep)
+__global__ void __launch_bounds__(kThreads)
+k_cg_final(CgStep step, int nblk, const double *__restrict__ part, CgState *st) {
+    const int q = blockIdx.x;
+    double s = 0.0;
+    for (int b = threadIdx.x; b < nblk; b += kThreads) s += part[(int64_t)q * nblk + b];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+    __shared__ double sh[kThreads / 64];
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x != 0 || !st->act[q]) return;
+    double t = 0.0;
+    for (int u = 0; u < kThreads / 64; ++u) t += sh[u];
+    if (step == kCgAlpha) {
+        if (t > 0.0) {
+            st->alpha[q] = st->rz[q] / t;
+            ++st->its[q];
+        } else {
+            st->act[q] = 0;
+        }
+    } else if (step == kCgCheck) {
+        if (sqrt(t) <= st->stop[q]) st->act[q] = 0;
+    } else {
+        st->beta[q] = st->its[q] == 0 ? 0.0 : t / st->rz[q];
+        st->rz[q] = t;
+    }
+}
+
+// One conjugate-gradient update of the active solves:
 //   psi_q += a_q p_q,  r_q -= a_q q_q,  part[q][block] = partial of r_q . (r_q * wt)
 // over the listed units of sp
 __global__ void __launch_bounds__(kThreads)
-k_cg_update(VPtr<const double> Pv, VPtr<const double> Qv, VPtr<double> Psi, VPtr<double> R, Coef4 a,
-            const double *__restrict__ wt, int64_t n, double *__restrict__ part, Span sp) {
-    double acc[kMaxRhs];
+k_cg_update(int nr, VPtr<const double> Pv, VPtr<const double> Qv, VPtr<double> Psi, VPtr<double> R,
+            const double *__restrict__ wt, int64_t n, double *__restrict__ part, const CgState *__restrict__ st,
+            Span sp) {
+    double acc[kMaxRhs], a[kMaxRhs];
+    bool on[kMaxRhs];
 #pragma unroll
-    for (int q = 0; q < kMaxRhs; ++q) acc[q] = 0.0;
+    for (int q = 0; q < kMaxRhs; ++q) {
+        acc[q] = 0.0;
+        on[q] = q < nr && st->act[q];
+        a[q] = on[q] ? st->alpha[q] : 0.0;
+    }
     const int64_t cnt = span_count<1>(sp, n);
     for (int64_t it = (int64_t)blockIdx.x * kThreads + threadIdx.x; it < cnt; it += (int64_t)gridDim.x * kThreads) {
         const int64_t e = span_elem<1>(sp, it);
@@ -1277,9 +1311,9 @@ k_cg_update(VPtr<const double> Pv, VPtr<const double> Qv, VPtr<double> Psi, VPtr
         const double w = wt[e];
 #pragma unroll
         for (int q = 0; q < kMaxRhs; ++q)
-            if (Pv.p[q]) {
-                Psi.p[q][e] += a.v[q] * Pv.p[q][e];
-                const double r = R.p[q][e] - a.v[q] * Qv.p[q][e];
+            if (on[q]) {
+                Psi.p[q][e] += a[q] * Pv.p[q][e];
+                const double r = R.p[q][e] - a[q] * Qv.p[q][e];
                 R.p[q][e] = r;
                 acc[q] += r * r * w;
             }
@@ -1300,16 +1334,23 @@ k_cg_update(VPtr<const double> Pv, VPtr<const double> Qv, VPtr<double> Psi, VPtr
     }
 }
 
-// Y_q = X_q + b_q Y_q for the vectors with Y_q set, over the listed units of sp
+// Y_q = X_q + beta_q Y_q for the active solves, over the listed units of sp
 __global__ void __launch_bounds__(kThreads)
-k_xpby_b(VPtr<const double> X, Coef4 b, VPtr<double> Y, int64_t n, Span sp) {
+k_cg_xpby(int nr, VPtr<const double> X, VPtr<double> Y, int64_t n, const CgState *__restrict__ st, Span sp) {
+    double b[kMaxRhs];
+    bool on[kMaxRhs];
+#pragma unroll
+    for (int q = 0; q < kMaxRhs; ++q) {
+        on[q] = q < nr && st->act[q];
+        b[q] = on[q] ? st->beta[q] : 0.0;
+    }
     const int64_t cnt = span_count<1>(sp, n);
     for (int64_t it = (int64_t)blockIdx.x * kThreads + threadIdx.x; it < cnt; it += (int64_t)gridDim.x * kThreads) {
         const int64_t e = span_elem<1>(sp, it);
         if (e >= n) continue;
 #pragma unroll
         for (int q = 0; q < kMaxRhs; ++q)
-            if (Y.p[q]) Y.p[q][e] = X.p[q][e] + b.v[q] * Y.p[q][e];
+            if (on[q]) Y.p[q][e] = X.p[q][e] + b[q] * Y.p[q][e];
     }
 }
 
@@ -2388,9 +2429,12 @@ void launch_maxpy_scale(int nv, const double *V, int64_t ld, const double *c, co
                            (const double *)nullptr, w, scale, out, n, 0, Span{});
 }
 
-void launch_dot_pairs(int nr, const VPtr<const double> &X, const VPtr<const double> &Y, const double *wt,
-                      int64_t n, double *part, double *dout, int64_t dstride, hipStream_t s, Span sp) {
-    if (nr < 1 || nr > kMaxRhs) throw std::runtime_error("launch_dot_pairs: 1 to 4 pairs");
+namespace {
+// the partial sums of launch_dot_pairs and launch_cg_dot; returns the number
+// of workgroups
+int dot_pairs_part(int nr, const VPtr<const double> &X, const VPtr<const double> &Y, const double *wt, int64_t n,
+                   double *part, hipStream_t s, Span sp) {
+    if (nr < 1 || nr > kMaxRhs) throw std::runtime_error("dot pairs: 1 to 4 pairs");
     VPtr<const double> x{}, y{};
     for (int q = 0; q < nr; ++q) {
         x.p[q] = X.p[q];
@@ -2401,27 +2445,35 @@ void launch_dot_pairs(int nr, const VPtr<const double> &X, const VPtr<const doub
     const int nb = reduce_grid(span_items(sp, n) / (v2 ? 2 : 1));
     if (v2) hipLaunchKernelGGL(k_dot_pairs<2>, dim3(nb), dim3(kThreads), 0, s, x, y, wt, n, part, sp);
     else hipLaunchKernelGGL(k_dot_pairs<1>, dim3(nb), dim3(kThreads), 0, s, x, y, wt, n, part, sp);
-    hipLaunchKernelGGL(k_mdot_final_strided, dim3(nr), dim3(kThreads), 0, s, nb,
-                       (const double *)part, dout, dstride);
+    return nb;
+}
+}  // namespace
+
+void launch_dot_pairs(int nr, const VPtr<const double> &X, const VPtr<const double> &Y, const double *wt,
+                      int64_t n, double *part, double *dout, int64_t dstride, hipStream_t s, Span sp) {
+    const int nb = dot_pairs_part(nr, X, Y, wt, n, part, s, sp);
+    hipLaunchKernelGGL(k_mdot_final_strided, dim3(nr), dim3(kThreads), 0, s, nb, (const double *)part, dout, dstride);
+}
+
+void launch_cg_dot(int nr, const VPtr<const double> &X, const VPtr<const double> &Y, const double *wt, int64_t n,
+                   double *part, CgStep step, CgState *st, hipStream_t s, Span sp) {
+    const int nb = dot_pairs_part(nr, X, Y, wt, n, part, s, sp);
+    hipLaunchKernelGGL(k_cg_final, dim3(nr), dim3(kThreads), 0, s, step, nb, (const double *)part, st);
 }
 
 void launch_cg_update(int nr, const VPtr<const double> &Pv, const VPtr<const double> &Qv, const VPtr<double> &Psi,
-                      const VPtr<double> &R, const Coef4 &a, const double *wt, int64_t n, double *part, double *dout,
-                      int64_t dstride, hipStream_t s, Span sp) {
+                      const VPtr<double> &R, const double *wt, int64_t n, double *part, CgState *st, hipStream_t s,
+                      Span sp) {
     if (nr < 1 || nr > kMaxRhs) throw std::runtime_error("launch_cg_update: 1 to 4 vectors");
-    VPtr<const double> pv{};
-    for (int q = 0; q < nr; ++q) pv.p[q] = Pv.p[q];
     const int nb = reduce_grid(span_items(sp, n));
-    hipLaunchKernelGGL(k_cg_update, dim3(nb), dim3(kThreads), 0, s, pv, Qv, Psi, R, a, wt, n, part, sp);
-    hipLaunchKernelGGL(k_mdot_final_strided, dim3(nr), dim3(kThreads), 0, s, nb,
-                       (const double *)part, dout, dstride);
+    hipLaunchKernelGGL(k_cg_update, dim3(nb), dim3(kThreads), 0, s, nr, Pv, Qv, Psi, R, wt, n, part,
+                       (const CgState *)st, sp);
+    hipLaunchKernelGGL(k_cg_final, dim3(nr), dim3(kThreads), 0, s, kCgCheck, nb, (const double *)part, st);
 }
 
-void launch_xpby_b(int nr, const VPtr<const double> &X, const Coef4 &b, const VPtr<double> &Y, int64_t n,
-                   hipStream_t s, Span sp) {
-    VPtr<double> y{};
-    for (int q = 0; q < nr && q < kMaxRhs; ++q) y.p[q] = Y.p[q];
-    hipLaunchKernelGGL(k_xpby_b, flat_grid(sp.u ? sp.n * kSpanUnit : n), dim3(kThreads), 0, s, X, b, y, n, sp);
+void launch_cg_xpby(int nr, const VPtr<const double> &X, const VPtr<double> &Y, int64_t n, const CgState *st,
+                    hipStream_t s, Span sp) {
+    hipLaunchKernelGGL(k_cg_xpby, flat_grid(span_items(sp, n)), dim3(kThreads), 0, s, nr, X, Y, n, st, sp);
 }
 
 void launch_sub_masked_b(int nr, int64_t n, const double *mask, const double *val, int64_t stride, double scale,

@@ -198,8 +198,10 @@ struct dm_op {
     hipGraphExec_t g_vb32[dm::kMaxRhs + 1] = {}, g_vb64[dm::kMaxRhs + 1] = {};
     // block projection: per-vector CG state (kMaxRhs * P each) and graphs
     double *pjb_g = nullptr, *pjb_psi = nullptr, *pjb_p = nullptr, *pjb_q = nullptr;
+    dm::CgState *pjb_st = nullptr, *pjb_hst = nullptr;   // the solves' scalars, device and pinned host
+    // one iteration of the conjugate gradients: its FP64 scalar V-cycle
     hipGraphExec_t g_svb[dm::kMaxRhs + 1] = {};
-    hipGraphExec_t g_svb32[dm::kMaxRhs + 1] = {};  // FP32 scalar block V-cycle with its casts
+    hipGraphExec_t g_svb32[dm::kMaxRhs + 1] = {};  // the same with the FP32 one and its casts
     std::vector<void *> allocs;  // everything to free
     int last_proj_iters = 0;
     // learned correction: the attached network (not owned) and its scratch
