@@ -622,6 +622,14 @@ void launch_basis_update(int nsys, const BasisArgs<TV> &A, int64_t ld, int64_t n
 // out_q = (TO) in_q for q < nr over the listed units of sp (all without)
 template <class TI, class TO>
 void launch_cast_b(int nr, const VPtr<const TI> &in, const VPtr<TO> &out, int64_t n, hipStream_t s, Span sp = {});
+// copies of several float vectors of their own lengths in one launch
+constexpr int kCopyMax = 64;
+struct CopyArgs {
+    const float *in[kCopyMax];
+    float *out[kCopyMax];
+    int64_t n[kCopyMax];
+};
+void launch_copy_many(int count, const CopyArgs &A, hipStream_t s);
 // out = scale * (w - sum c_i V_i)
 void launch_maxpy_scale(int nv, const double *V, int64_t ld, const double *c, const double *w,
                         double scale, double *out, int64_t n, hipStream_t s);

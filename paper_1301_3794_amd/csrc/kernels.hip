@@ -667,6 +667,14 @@ k_cast_b(VPtr<const TI> in, VPtr<TO> out, int64_t n, const int32_t *__restrict__
     }
 }
 
+// copies of several vectors in one launch: grid row y takes vector y
+__global__ void __launch_bounds__(kThreads) k_copy_many(CopyArgs A) {
+    const float *__restrict__ a = A.in[blockIdx.y];
+    float *__restrict__ b = A.out[blockIdx.y];
+    const int64_t n = A.n[blockIdx.y];
+    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < n; e += (int64_t)gridDim.x * kThreads) b[e] = a[e];
+}
+
 // Coarsest level: x[idx[r]] = sum_c inv[r, c] f[idx[c]] (FP64 arithmetic);
 // one row of the inverse serves every right-hand side
 template <class T, int NR>
@@ -2232,6 +2240,13 @@ void launch_basis_dots(int nsys, const BasisArgs<TV> &A, int64_t ld, int64_t n, 
 }
 template void launch_basis_dots<double>(int, const BasisArgs<double> &, int64_t, int64_t, double *, hipStream_t, Span);
 template void launch_basis_dots<float>(int, const BasisArgs<float> &, int64_t, int64_t, double *, hipStream_t, Span);
+
+void launch_copy_many(int count, const CopyArgs &A, hipStream_t s) {
+    if (count < 1 || count > kCopyMax) throw std::runtime_error("launch_copy_many: 1 to 64 vectors");
+    int64_t most = 0;
+    for (int q = 0; q < count; ++q) most = std::max(most, A.n[q]);
+    hipLaunchKernelGGL(k_copy_many, dim3(flat_grid(ceil_div(most, 4)).x, (unsigned)count), dim3(kThreads), 0, s, A);
+}
 
 template <class TI, class TO>
 void launch_cast_b(int nr, const VPtr<const TI> &in, const VPtr<TO> &out, int64_t n, hipStream_t s, Span sp) {
