@@ -2,7 +2,10 @@
 // and the dense FP64 inverses of the coarsest vector and scalar operators.
 #include <algorithm>
 #include <cmath>
+#include <exception>
+#include <functional>
 #include <numeric>
+#include <system_error>
 #include <thread>
 #include <unordered_map>
 
@@ -109,31 +112,73 @@ std::vector<double> to_coefs(const Grid &g, const std::vector<double> &fr, bool 
 
 }  // namespace
 
+// Every task, each on a thread of its own on a grid worth it; the first
+// exception of a task is thrown again here, and a task that gets no thread
+// runs on this one
+static void all_of(const Grid &g, const std::vector<std::function<void()>> &tasks) {
+    std::vector<std::exception_ptr> errs(tasks.size());
+    auto run = [&](size_t t) {
+        try {
+            tasks[t]();
+        } catch (...) {
+            errs[t] = std::current_exception();
+        }
+    };
+    std::vector<std::thread> th;
+    th.reserve(tasks.size());
+    for (size_t t = 0; t < tasks.size(); ++t) {
+        bool threaded = false;
+        if (g.P >= 20000 && t + 1 < tasks.size()) {
+            try {
+                th.emplace_back(run, t);
+                threaded = true;
+            } catch (const std::system_error &) {
+            }
+        }
+        if (!threaded) run(t);
+    }
+    for (auto &t : th) t.join();
+    for (auto &e : errs)
+        if (e) std::rethrow_exception(e);
+}
+
+// f(k0, k1) on the planes of the grid, split over tasks
+template <class F>
+static void over_planes(const Grid &g, F &&f) {
+    const int nt = std::max(1, std::min(16, g.nz));
+    std::vector<std::function<void()>> tasks;
+    for (int t = 0; t < nt; ++t)
+        tasks.push_back([&, t] { f((int)((int64_t)g.nz * t / nt), (int)((int64_t)g.nz * (t + 1) / nt)); });
+    all_of(g, tasks);
+}
+
 // row classes of every cell (kFaceActive / kFaceVacuum bits) from the
 // coefficient blocks ax ay az lx ly lz vinv of one level
 std::vector<uint8_t> row_flags(const Grid &g, const std::vector<double> &c) {
     const int64_t P = g.P;
     std::vector<uint8_t> fl(P, 0);
-    for (int k = 0; k < g.nz; ++k)
-        for (int j = 0; j < g.ny; ++j)
-            for (int i = 0; i < g.nx; ++i) {
-                const int64_t p = pidx(g, i, j, k);
-                const int idx[3] = {i, j, k};
-                bool vac = true;
-                for (int a = 0; a < 3; ++a)
-                    if (((g.pmc >> a) & 1) && idx[a] == 0) vac = false;
-                for (int dz = -1; dz <= 1 && vac; ++dz)
-                    for (int dy = -1; dy <= 1 && vac; ++dy)
-                        for (int dx = -1; dx <= 1 && vac; ++dx) {
-                            const int64_t q = p + dx + (int64_t)dy * g.sy + (int64_t)dz * g.sz;
-                            for (int b = 0; b < 7; ++b)
-                                if (c[b * P + q] != 1.0) { vac = false; break; }
-                        }
-                uint8_t f = 0;
-                for (int a = 0; a < 3; ++a)
-                    if (c[a * P + p] != 0.0) f |= (uint8_t)((kFaceActive << a) | (vac ? (kFaceVacuum << a) : 0));
-                fl[p] = f;
-            }
+    over_planes(g, [&](int k0, int k1) {
+        for (int k = k0; k < k1; ++k)
+            for (int j = 0; j < g.ny; ++j)
+                for (int i = 0; i < g.nx; ++i) {
+                    const int64_t p = pidx(g, i, j, k);
+                    const int idx[3] = {i, j, k};
+                    bool vac = true;
+                    for (int a = 0; a < 3; ++a)
+                        if (((g.pmc >> a) & 1) && idx[a] == 0) vac = false;
+                    for (int dz = -1; dz <= 1 && vac; ++dz)
+                        for (int dy = -1; dy <= 1 && vac; ++dy)
+                            for (int dx = -1; dx <= 1 && vac; ++dx) {
+                                const int64_t q = p + dx + (int64_t)dy * g.sy + (int64_t)dz * g.sz;
+                                for (int b = 0; b < 7; ++b)
+                                    if (c[b * P + q] != 1.0) { vac = false; break; }
+                            }
+                    uint8_t f = 0;
+                    for (int a = 0; a < 3; ++a)
+                        if (c[a * P + p] != 0.0) f |= (uint8_t)((kFaceActive << a) | (vac ? (kFaceVacuum << a) : 0));
+                    fl[p] = f;
+                }
+    });
     return fl;
 }
 
@@ -312,95 +357,113 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
         const bool small = lds_level(P, faces, sizeof(float));
         const int nxh = (L.g.nx + 1) >> 1;
         L.vrun_log = nxh <= 8 ? 3 : nxh <= 16 ? 4 : nxh <= 32 ? 5 : 6;
+        // the lists, each built by a task of its own: a component's cut rows, a
+        // class's runs (and its vacuum rows one by one on an LDS level), the
+        // cells with a cut row, the grid rows holding an active cell or face
+        std::vector<int32_t> cutv[3], vacv[6], cutc, arows, frows;
+        std::vector<VacRun> runv[6];
+        std::vector<CellRun> cruns;
+        L.crun_log = L.g.nx <= 8 ? 3 : L.g.nx <= 16 ? 4 : L.g.nx <= 32 ? 5 : 6;
+        std::vector<std::function<void()>> tasks;
         for (int comp = 0; comp < 3; ++comp) {
-            L.cut_off[comp] = (int64_t)cut.size();
+            tasks.push_back([&, comp] {
+                for (int k = 0; k < L.g.nz; ++k)
+                    for (int j = 0; j < L.g.ny; ++j)
+                        for (int i = 0; i < L.g.nx; ++i) {
+                            const int64_t p = pidx(L.g, i, j, k);
+                            if ((fl[p] & (kFaceActive << comp)) && !(fl[p] & (kFaceVacuum << comp)))
+                                cutv[comp].push_back((int32_t)p);
+                        }
+            });
+            for (int col = 0; col < 2; ++col)
+                tasks.push_back([&, comp, col] {
+                    const int q = 2 * comp + col;
+                    for (int k = 0; k < L.g.nz; ++k)
+                        for (int j = 0; j < L.g.ny; ++j) {
+                            const int i0 = (j + k + col) & 1;
+                            VacRun run{};
+                            for (int ih = 0; 2 * ih + i0 < L.g.nx; ++ih) {
+                                const int64_t p = pidx(L.g, 2 * ih + i0, j, k);
+                                const int lane = ih & 63;
+                                if (lane == 0) {
+                                    const int at[3] = {2 * ih + i0, j, k};
+                                    run = VacRun{(int32_t)p, ((L.g.pmc >> comp) & 1) && at[comp] == 1, 0};
+                                }
+                                if (fl[p] & (kFaceVacuum << comp)) {
+                                    run.mask |= 1ull << lane;
+                                    if (small) vacv[q].push_back((int32_t)p);
+                                }
+                                if ((lane == 63 || 2 * (ih + 1) + i0 >= L.g.nx) && run.mask) runv[q].push_back(run);
+                            }
+                        }
+                });
+        }
+        tasks.push_back([&] {
             for (int k = 0; k < L.g.nz; ++k)
                 for (int j = 0; j < L.g.ny; ++j)
                     for (int i = 0; i < L.g.nx; ++i) {
                         const int64_t p = pidx(L.g, i, j, k);
-                        if ((fl[p] & (kFaceActive << comp)) && !(fl[p] & (kFaceVacuum << comp)))
-                            cut.push_back((int32_t)p);
+                        if ((fl[p] & 7) & ~(fl[p] >> 3)) cutc.push_back((int32_t)p);
                     }
-            if (small) {
-                const auto first = cut.begin() + L.cut_off[comp];
-                const auto mid = std::stable_partition(first, cut.end(), [&](int32_t p) { return !odd_cell(L.g, p); });
-                L.lds.cut_off[2 * comp] = (int32_t)L.cut_off[comp];
-                L.lds.cut_off[2 * comp + 1] = (int32_t)(mid - cut.begin());
-            }
-            for (int col = 0; col < 2; ++col) {
-                L.vrun_off[2 * comp + col] = (int64_t)runs.size();
-                L.lds.vac_off[2 * comp + col] = (int32_t)vac.size();
-                for (int k = 0; k < L.g.nz; ++k)
-                    for (int j = 0; j < L.g.ny; ++j) {
-                        const int i0 = (j + k + col) & 1;
-                        VacRun run{};
-                        if (small)
-                            for (int i = i0; i < L.g.nx; i += 2)
-                                if (fl[pidx(L.g, i, j, k)] & (kFaceVacuum << comp))
-                                    vac.push_back((int32_t)pidx(L.g, i, j, k));
-                        for (int ih = 0; 2 * ih + i0 < L.g.nx; ++ih) {
-                            const int64_t p = pidx(L.g, 2 * ih + i0, j, k);
-                            const int lane = ih & 63;
-                            if (lane == 0) {
-                                const int at[3] = {2 * ih + i0, j, k};
-                                run = VacRun{(int32_t)p, ((L.g.pmc >> comp) & 1) && at[comp] == 1, 0};
-                            }
-                            if (fl[p] & (kFaceVacuum << comp)) run.mask |= 1ull << lane;
-                            if ((lane == 63 || 2 * (ih + 1) + i0 >= L.g.nx) && run.mask) runs.push_back(run);
+        });
+        tasks.push_back([&] {
+            for (int k = 0; k < L.g.nz; ++k)
+                for (int j = 0; j < L.g.ny; ++j) {
+                    bool any = false;
+                    for (int i = 0; i < L.g.nx && !any; ++i) any = c[6 * P + pidx(L.g, i, j, k)] != 0.0;
+                    if (any) arows.push_back((int32_t)(k * L.g.ny + j));
+                }
+        });
+        // the cells without a cut row as runs: every grid row, then those
+        // holding an active face
+        tasks.push_back([&] {
+            for (int k = 0; k < L.g.nz; ++k)
+                for (int j = 0; j < L.g.ny; ++j) {
+                    bool any = false;
+                    for (int i0 = 0; i0 < L.g.nx; i0 += 64) {
+                        CellRun run{};
+                        run.p = (int32_t)pidx(L.g, i0, j, k);
+                        run.pmc = ((L.g.pmc & 1) && i0 == 0 ? 1 : 0) |
+                                  (((L.g.pmc & 2) && j < 2) || ((L.g.pmc & 4) && k < 2) ? 2 : 0);
+                        for (int l = 0; l < 64 && i0 + l < L.g.nx; ++l) {
+                            const uint8_t f = fl[run.p + l];
+                            if (!((f & 7) & ~(f >> 3))) run.visit |= 1ull << l;
+                            for (int c = 0; c < 3; ++c)
+                                if (f & (kFaceActive << c)) run.act[c] |= 1ull << l;
                         }
+                        any = any || (run.act[0] | run.act[1] | run.act[2]);
+                        cruns.push_back(run);
                     }
+                    if (any) frows.push_back((int32_t)(k * L.g.ny + j));
+                }
+            L.ncrun = (int64_t)cruns.size();
+            const int64_t per = (L.g.nx + 63) / 64;   // runs per grid row
+            for (int32_t row : frows)
+                for (int64_t q = 0; q < per; ++q) cruns.push_back(CellRun(cruns[(size_t)(row * per + q)]));
+            L.nfrun = (int64_t)cruns.size() - L.ncrun;
+        });
+        all_of(L.g, tasks);
+        for (int comp = 0; comp < 3; ++comp) {
+            L.cut_off[comp] = (int64_t)cut.size();
+            if (small) {
+                const auto mid = std::stable_partition(cutv[comp].begin(), cutv[comp].end(),
+                                                       [&](int32_t p) { return !odd_cell(L.g, p); });
+                L.lds.cut_off[2 * comp] = (int32_t)cut.size();
+                L.lds.cut_off[2 * comp + 1] = (int32_t)(cut.size() + (mid - cutv[comp].begin()));
+            }
+            cut.insert(cut.end(), cutv[comp].begin(), cutv[comp].end());
+            for (int q = 2 * comp; q < 2 * comp + 2; ++q) {
+                L.vrun_off[q] = (int64_t)runs.size();
+                L.lds.vac_off[q] = (int32_t)vac.size();
+                runs.insert(runs.end(), runv[q].begin(), runv[q].end());
+                vac.insert(vac.end(), vacv[q].begin(), vacv[q].end());
             }
         }
         L.vrun_off[6] = (int64_t)runs.size();
         L.cut_off[3] = (int64_t)cut.size();
         L.lds.cut_off[6] = (int32_t)cut.size();
         L.lds.vac_off[6] = (int32_t)vac.size();
-        std::vector<int32_t> cutc;
-        for (int k = 0; k < L.g.nz; ++k)
-            for (int j = 0; j < L.g.ny; ++j)
-                for (int i = 0; i < L.g.nx; ++i) {
-                    const int64_t p = pidx(L.g, i, j, k);
-                    if ((fl[p] & 7) & ~(fl[p] >> 3)) cutc.push_back((int32_t)p);
-                }
         L.ncutc = (int64_t)cutc.size();
-        std::vector<int32_t> arows;
-        for (int k = 0; k < L.g.nz; ++k)
-            for (int j = 0; j < L.g.ny; ++j) {
-                bool any = false;
-                for (int i = 0; i < L.g.nx && !any; ++i) any = c[6 * P + pidx(L.g, i, j, k)] != 0.0;
-                if (any) arows.push_back((int32_t)(k * L.g.ny + j));
-            }
-        std::vector<int32_t> frows;
-        for (int k = 0; k < L.g.nz; ++k)
-            for (int j = 0; j < L.g.ny; ++j) {
-                bool any = false;
-                for (int i = 0; i < L.g.nx && !any; ++i) any = fl[pidx(L.g, i, j, k)] & 7;
-                if (any) frows.push_back((int32_t)(k * L.g.ny + j));
-            }
-        // the cells without a cut row as runs: every grid row, then those
-        // holding an active face
-        std::vector<CellRun> cruns;
-        L.crun_log = L.g.nx <= 8 ? 3 : L.g.nx <= 16 ? 4 : L.g.nx <= 32 ? 5 : 6;
-        auto add_cruns = [&](int64_t row) {
-            const int j = (int)(row % L.g.ny), k = (int)(row / L.g.ny);
-            for (int i0 = 0; i0 < L.g.nx; i0 += 64) {
-                CellRun run{};
-                run.p = (int32_t)pidx(L.g, i0, j, k);
-                run.pmc = ((L.g.pmc & 1) && i0 == 0 ? 1 : 0) |
-                          (((L.g.pmc & 2) && j < 2) || ((L.g.pmc & 4) && k < 2) ? 2 : 0);
-                for (int l = 0; l < 64 && i0 + l < L.g.nx; ++l) {
-                    const uint8_t f = fl[run.p + l];
-                    if (!((f & 7) & ~(f >> 3))) run.visit |= 1ull << l;
-                    for (int c = 0; c < 3; ++c)
-                        if (f & (kFaceActive << c)) run.act[c] |= 1ull << l;
-                }
-                cruns.push_back(run);
-            }
-        };
-        for (int64_t row = 0; row < (int64_t)L.g.ny * L.g.nz; ++row) add_cruns(row);
-        L.ncrun = (int64_t)cruns.size();
-        for (int32_t row : frows) add_cruns(row);
-        L.nfrun = (int64_t)cruns.size() - L.ncrun;
         L.crun = op->dalloc<CellRun>(cruns.size());
         DM_HIP(hipMemcpyAsync(L.crun, cruns.data(), cruns.size() * sizeof(CellRun), hipMemcpyHostToDevice, op->stream));
         // tabulated rows of the cut lists and of the cells with a cut row
