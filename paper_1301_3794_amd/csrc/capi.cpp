@@ -130,7 +130,7 @@ static void free_op(dm_op *op) {
     for (void *p : op->allocs) hipFree(p);
     if (op->hres) hipHostFree(op->hres);
     if (op->bk_hres) hipHostFree(op->bk_hres);
-    if (op->hres2) hipHostFree(op->hres2);
+    if (op->hsc2) hipHostFree(op->hsc2);   // hres2 lies inside hres
     if (op->ln_hflag) hipHostFree(op->ln_hflag);
     if (op->pjb_hst) hipHostFree(op->pjb_hst);
     if (op->bk_hsc2) hipHostFree(op->bk_hsc2);   // bk_hres2 lies inside bk_hres

@@ -641,8 +641,10 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
         }
     }
     op->part = op->dalloc<double>((size_t)kReduceBlocks * kMaxDots);
-    op->dres = op->dalloc<double>(kMaxDots);
-    DM_HIP(hipHostMalloc((void **)&op->hres, kMaxDots * sizeof(double), hipHostMallocDefault));
+    op->dres = op->dalloc<double>(2 * kMaxDots);
+    op->dres2 = op->dres + kMaxDots;
+    DM_HIP(hipHostMalloc((void **)&op->hres, 2 * kMaxDots * sizeof(double), hipHostMallocDefault));
+    op->hres2 = op->hres + kMaxDots;
     DM_HIP(hipStreamSynchronize(op->stream));
     // the scalar problem is singular (constants) unless a PMC plane pins psi
     op->s_floating = !(op->geom.bc_lo[0] == DM_BC_PMC || op->geom.bc_lo[1] == DM_BC_PMC ||

@@ -161,14 +161,16 @@ struct dm_op {
     double *wainv = nullptr;  // 3P, W / a
     // reductions
     double *part = nullptr;   // kReduceBlocks * kMaxDots
-    double *dres = nullptr;   // kMaxDots device results
-    double *hres = nullptr;   // kMaxDots pinned host results
+    // device results and their pinned host copy: kMaxDots, then kMaxDots more
+    // (dres2 / hres2) of FGMRES's second Gram--Schmidt pass, so that one copy
+    // brings both
+    double *dres = nullptr, *hres = nullptr, *dres2 = nullptr, *hres2 = nullptr;
     // Krylov workspaces (allocated on first use)
     int fg_m = 0;
     double *fg_V = nullptr, *fg_Z = nullptr, *fg_w = nullptr, *dcoef = nullptr;
-    // second-pass results of FGMRES's Gram--Schmidt (device / pinned host) and
-    // the squared column scales of its unnormalised basis (device)
-    double *dres2 = nullptr, *hres2 = nullptr, *sc2d = nullptr;
+    // the squared column scales of FGMRES's unnormalised basis: device, and
+    // their pinned host image
+    double *sc2d = nullptr, *hsc2 = nullptr;
     float *fg_f32 = nullptr, *fg_x32 = nullptr;
     double *gv_f64 = nullptr, *gv_x64 = nullptr;       // fixed in/out of the FP64 V-cycle graph
     hipGraphExec_t g_vc32 = nullptr, g_vc64 = nullptr, g_svc = nullptr;

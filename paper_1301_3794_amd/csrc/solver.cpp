@@ -194,7 +194,8 @@ int fgmres(dm_op *op, int mode, const double *f, double *x, double rtol, int max
     // c, c3, cx: coefficients of passes (2), (3) and of the update of x, each
     // in its own host array (a queued copy never reads an overwritten array)
     std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m), h(m + 1), h2(m + 1), c(m + 1),
-        c3(m + 1), cx(m + 1), sc(m + 1), sc2h(m + 1);
+        c3(m + 1), cx(m + 1), sc(m + 1);
+    double *sc2h = op->hsc2;   // pinned; an entry is rewritten only after later waits
     bool conv = false;
     while (true) {
         if (total == 0) launch_copy(n, f, V, s);
@@ -209,7 +210,7 @@ int fgmres(dm_op *op, int mode, const double *f, double *x, double rtol, int max
         if (total >= maxit) break;
         sc[0] = 1.0 / beta;
         sc2h[0] = sc[0] * sc[0];
-        DM_HIP(hipMemcpyAsync(op->sc2d, sc2h.data(), sizeof(double), hipMemcpyHostToDevice, s));
+        DM_HIP(hipMemcpyAsync(op->sc2d, sc2h, sizeof(double), hipMemcpyHostToDevice, s));
         std::fill(g.begin(), g.end(), 0.0);
         g[0] = beta;
         std::fill(H.begin(), H.end(), 0.0);
@@ -222,8 +223,7 @@ int fgmres(dm_op *op, int mode, const double *f, double *x, double rtol, int max
             // the device, fused with d2 = U^T w and |w|^2: one host sync
             launch_mdot(j + 1, V, n, w, nullptr, n, op->part, op->dres, s, sp);
             launch_maxpy_mdot_norm(j + 1, V, n, op->dres, w, n, op->part, op->dres2, s, op->sc2d, sp);
-            DM_HIP(hipMemcpyAsync(op->hres, op->dres, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
-            DM_HIP(hipMemcpyAsync(op->hres2, op->dres2, (j + 2) * sizeof(double), hipMemcpyDeviceToHost, s));
+            DM_HIP(hipMemcpyAsync(op->hres, op->dres, (kMaxDots + j + 2) * sizeof(double), hipMemcpyDeviceToHost, s));
             DM_HIP(hipStreamSynchronize(s));
             for (int i = 0; i <= j; ++i) h[i] = sc[i] * sc[j] * op->hres[i];   // true coefficients
             const double wn2 = op->hres2[j + 1] * sc[j] * sc[j];
@@ -248,7 +248,7 @@ int fgmres(dm_op *op, int mode, const double *f, double *x, double rtol, int max
             if (!std::isfinite(hn)) throw DmError{DM_ENAN, "FGMRES iterate is not finite"};
             sc[j + 1] = hn > 0.0 ? sc[j] / hn : 0.0;
             sc2h[j + 1] = sc[j + 1] * sc[j + 1];
-            DM_HIP(hipMemcpyAsync(op->sc2d + j + 1, &sc2h[j + 1], sizeof(double), hipMemcpyHostToDevice, s));
+            DM_HIP(hipMemcpyAsync(op->sc2d + j + 1, sc2h + j + 1, sizeof(double), hipMemcpyHostToDevice, s));
             for (int i = 0; i <= j; ++i) H[(size_t)i * m + j] = h[i];
             H[(size_t)(j + 1) * m + j] = hn;
             for (int i = 0; i < j; ++i) {
@@ -379,9 +379,8 @@ void ensure_krylov_small(dm_op *op) {
         op->gv_f64 = op->dalloc<double>(n);
         op->gv_x64 = op->dalloc<double>(n);
         op->dcoef = op->dalloc<double>(kMaxDots);
-        op->dres2 = op->dalloc<double>(kMaxDots);
         op->sc2d = op->dalloc<double>(kMaxDots);
-        DM_HIP(hipHostMalloc((void **)&op->hres2, kMaxDots * sizeof(double), hipHostMallocDefault));
+        DM_HIP(hipHostMalloc((void **)&op->hsc2, kMaxDots * sizeof(double), hipHostMallocDefault));
     }
 }
 
@@ -417,9 +416,9 @@ void precondition(dm_op *op, int mode, const double *v, double *z, hipStream_t s
             net_correct_patient(op, v, z, rejections ? rejections : &none, s);
         }
     } else {
-        launch_copy(n, v, op->gv_f64, s);
+        launch_cast_b<double, double>(1, vptr1(v), vptr1(op->gv_f64), n, s, op->vspan());
         vcycle_graphed(op, 64, s);
-        launch_copy(n, op->gv_x64, z, s);
+        launch_cast_b<double, double>(1, vptr1<const double>(op->gv_x64), vptr1(z), n, s, op->vspan());
     }
 }
 
