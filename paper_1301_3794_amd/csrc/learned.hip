@@ -6,10 +6,10 @@
 // A[l % 16][4 (l / 16) + 0..3], B[4 (l / 16) + 0..3][l % 16] and
 // D[4 (l / 16) + 0..3][l % 16].
 //
-// Convolution as 27 accumulated tile products: rows = 16 consecutive cells
-// along x, k = the 16 input channels at one tap, cols = the 16 output
-// channels.  A wavefront owns one 16-cell segment of an x-row; the weights
-// of the layer (27 x 16 x 16 bfloat16, 13.5 KB) sit in LDS.  The padding
+// Convolution as 27 accumulated tile products: rows = the 16 output channels,
+// k = the 16 input channels at one tap, cols = 16 consecutive cells along x.
+// A wavefront owns one 16-cell segment of an x-row; each lane keeps its
+// weights of the layer in registers.  The padding
 // layer of every activation buffer is zero, so taps that leave the grid read
 // zeros; cells past the ragged row end are neither read nor written.
 
