@@ -76,10 +76,9 @@ std::vector<HostStep> schedule(dm_batch *b) {
         J.cells = cl.cells;
         J.n = cl.n;
         J.nruns = (uint32_t)cl.nruns;
-        J.run_log = cl.run_log;
         J.colour = cl.colour;
         J.pair = cl.pair;
-        J.items = cl.nruns << cl.run_log;
+        J.items = cl.nruns << kRunLog;
     };
     // the smoothing sweeps of every member with a coarser level than d: one
     // launch of one workgroup per member where all of them fit LDS, else a
@@ -220,7 +219,8 @@ hipGraphExec_t capture(dm_batch *b, const std::vector<HostStep> &steps, int tpb)
             } else if (h.kind == BS_SWEEPS) {
                 lds = std::max(lds, (size_t)(3 * J.g.P) * sizeof(float));
             } else {
-                J.ncut = cdiv(J.n, tpb);
+                // the residual's cut part: a wave per component of 64 cells (apply_cut_part)
+                J.ncut = h.kind == BS_RESID ? cdiv(3 * 64 * cdiv(J.n, 64), tpb) : cdiv(J.n, tpb);
                 blocks = J.ncut + cdiv(J.items, tpb);
             }
             job_of.resize(job_of.size() + (size_t)blocks, (int32_t)q);

@@ -297,26 +297,36 @@ __host__ __device__ inline VPtr<const T> as_const(const VPtr<T> &x) {
     return v;
 }
 
-// Up to 64 consecutive cells of one colour in a grid row, for the smoother's
-// vacuum rows: lane l stands for padded index p + 2 l, and updates it where
-// bit l of the mask is set (the face there is a vacuum row of the class).
+// The stencil kernels take the vacuum rows and the cells without a cut row by
+// runs of 16 lanes along a grid row.  A run of one colour spans 32 cells, a
+// 128-byte line of FP32; a wider one leaves lanes idle at the row's end and
+// outside the cavity, and a narrower one reads more of the records (one load
+// of 8 or 16 bytes here).  Runs of 64 lanes (the row's last one and rows
+// of up to 32 narrower) with 64-bit masks: one sweep of 3 vectors at 128^3
+// 83.6 us, at 88 x 72 x 104 43.1 us, M x in FP64 at 72 x 80 x 64 29.3 us.
+// DM_RUN_FIGURES
+constexpr int kRunLog = 4, kRunLanes = 1 << kRunLog;
+
+// Consecutive cells of one colour in a grid row, for the smoother's vacuum
+// rows: lane l stands for padded index p + 2 l, and updates it where bit l of
+// the mask is set (the face there is a vacuum row of the class).
 // image: the run's faces (for component x its lane 0) have a PMC ghost image
 // two cells down their own axis, the only image a vacuum row can have (it
 // touches no symmetry plane).
-struct VacRun {
-    int32_t p, image;
-    uint64_t mask;
+struct alignas(8) VacRun {
+    int32_t p;
+    uint16_t mask, image;
 };
 
-// Up to 64 consecutive cells of a grid row, for the cells of an apply or
-// residual without a cut row: lane l stands for padded index p + l, is
-// visited where bit l of `visit` is set (the cell is in the grid and not in
-// the cut-cell list), and its face of component c is active (a vacuum row)
-// where bit l of act[c] is.  pmc: bit 0, lanes 0 and 1 may have PMC ghost
-// images; bit 1, every lane may.
-struct CellRun {
+// Consecutive cells of a grid row, for the cells of an apply or residual
+// without a cut row: lane l stands for padded index p + l, is visited where
+// bit l of `visit` is set (the cell is in the grid and not in the cut-cell
+// list), and its face of component c is active (a vacuum row) where bit l of
+// act[c] is.  pmc: bit 0, lanes 0 and 1 may have PMC ghost images; bit 1,
+// every lane may.
+struct alignas(16) CellRun {
     int32_t p, pmc;
-    uint64_t visit, act[3];
+    uint16_t visit, act[3];
 };
 
 // The rows of one smoother class (component and colour), or the cut cells of
@@ -327,13 +337,12 @@ struct ClassList {
     // residual: the cells with a cut row
     const int32_t *idx = nullptr;
     int64_t n = 0;
-    // apply and residual: the runs of the other cells, 2^run_log lanes per run
+    // apply and residual: the runs of the other cells
     const CellRun *cells = nullptr;
     int colour = 0;      // smoother: the class's colour
-    // smoother: the class's vacuum rows, 2^run_log lanes per run
+    // smoother: the class's vacuum rows
     const VacRun *runs = nullptr;
     int64_t nruns = 0;   // runs, or cells
-    int run_log = 6;
     // block smoother: below this many listed rows each vector gets its own
     // wavefront, else one thread per row loops over the vectors
     int64_t wave_split_max = 65536;
@@ -409,7 +418,7 @@ struct BJob {
     const CellRun *cells;
     int64_t n, ncut;
     uint32_t nruns;
-    int run_log, colour, pair;
+    int colour, pair;
     // transfers: the grid rows to visit
     const int32_t *rows;
     int64_t nrows;

@@ -139,17 +139,19 @@ __device__ __forceinline__ void apply_vac_body(const Grid &g, T sigma, const Cel
     const int64_t P = g.P, dy = g.sy, dz = g.sz;
     const uint32_t p = (uint32_t)run.p + lane;
     const T ih2 = inv_h2_of<T>(g);
-    T v[3];
+    T v[3] = {T(0), T(0), T(0)};
+    if (((run.act[0] | run.act[1] | run.act[2]) >> lane) & 1) {
+        // one branch for the three rows, so that all their loads are in flight
+        // together (every cell of the grid has its neighbours in the padding)
 #pragma unroll
-    for (int comp = 0; comp < 3; ++comp) {
-        const TX *C = x + comp * P;
-        v[comp] = T(0);
-        if ((run.act[comp] >> lane) & 1) {
+        for (int comp = 0; comp < 3; ++comp) {
+            const TX *C = x + comp * P;
             v[comp] = ih2 * vac_row<T, TX>(C, p, dy, dz) - sigma * T(C[p]);
             if (KIND == AK_RESID) v[comp] = f[comp * P + p] - v[comp];
+            if (!((run.act[comp] >> lane) & 1)) v[comp] = T(0);
         }
     }
-    if ((run.pmc & 2) || (run.pmc && lane < 2)) {
+    if (g.pmc && ((run.pmc & 2) || (run.pmc && lane < 2))) {
         put_face_at<T>(g, y, 0, p, v[0]);
         put_face_at<T>(g, y + P, 1, p, v[1]);
         put_face_at<T>(g, y + 2 * P, 2, p, v[2]);
@@ -166,32 +168,45 @@ k_apply_K(Grid g, Coefs<T> c, const T *__restrict__ x, T *__restrict__ y) {
     apply_k_body<T>(g, c, x, y, xcd_item());
 }
 
-// M x or f - M x at listed cell e (padded index p) from the cell's tabulated
-// rows W (3 x kCutW x ncut; see cut_term); inactive faces (a = 0) get 0
-template <class T, int KIND, class TX>
-__device__ __forceinline__ void apply_cut_tab(const Grid &g, T sigma, const T *__restrict__ W, int64_t ncut,
+// M x or f - M x at the face of component COMP of listed cell e (padded index
+// p) from its tabulated row in W (3 x kCutW x ncut; see cut_term); an
+// inactive face (a = 0) gets 0
+template <class T, int KIND, int COMP, class TX>
+__device__ __forceinline__ void apply_cut_row(const Grid &g, T sigma, const T *__restrict__ W, int64_t ncut,
                                               int64_t e, uint32_t p, const T *__restrict__ f,
                                               const TX *__restrict__ x, T *__restrict__ y) {
     const int64_t P = g.P, dy = g.sy, dz = g.sz;
-    T v[3];
+    const T *Wc = W + (int64_t)COMP * kCutW * ncut;
+    const T a = Wc[kCutTerms * ncut + e];
+    T v = T(0);
+    if (a != T(0)) {
+        T row = -sigma * a * T(x[COMP * P + p]);
 #pragma unroll
-    for (int comp = 0; comp < 3; ++comp) {
-        const T *Wc = W + (int64_t)comp * kCutW * ncut;
-        const T a = Wc[kCutTerms * ncut + e];
-        v[comp] = T(0);
-        if (a != T(0)) {
-            T row = -sigma * a * T(x[comp * P + p]);
-#pragma unroll
-            for (int t = 0; t < kCutTerms; ++t) {
-                const CutTerm ct = cut_term(comp, t);
-                row += Wc[t * ncut + e] * T(x[ct.comp * P + p + ct.di + ct.dj * dy + ct.dk * dz]);
-            }
-            v[comp] = KIND == AK_RESID ? f[comp * P + p] - row : row;
+        for (int t = 0; t < kCutTerms; ++t) {
+            const CutTerm ct = cut_term(COMP, t);
+            row += Wc[t * ncut + e] * T(x[ct.comp * P + p + ct.di + ct.dj * dy + ct.dk * dz]);
         }
+        v = KIND == AK_RESID ? f[COMP * P + p] - row : row;
     }
-    put_face_at<T>(g, y, 0, p, v[0]);
-    put_face_at<T>(g, y + P, 1, p, v[1]);
-    put_face_at<T>(g, y + 2 * P, 2, p, v[2]);
+    put_face_at<T>(g, y + COMP * P, COMP, p, v);
+}
+
+// entry i of the cut part: component i mod 3 of the 64 listed cells i / 3 of
+// a wave.  A row to a thread halves the loads that wait for one another: with
+// the three rows of a cell in a thread, each after the other's branch, the
+// cut part was the launch's tail (its workgroups last instead of first cost
+// 10%).
+template <class T, int KIND, class TX>
+__device__ __forceinline__ void apply_cut_part(const Grid &g, T sigma, const T *__restrict__ W,
+                                               const int32_t *__restrict__ cut, int64_t ncut, uint32_t i,
+                                               uint32_t lane, const T *__restrict__ f, const TX *__restrict__ x,
+                                               T *__restrict__ y) {
+    const uint32_t c = i / 3, comp = i - 3 * c, e = c * 64 + lane;
+    if (e >= ncut) return;
+    const uint32_t p = (uint32_t)cut[e];
+    if (comp == 0) apply_cut_row<T, KIND, 0, TX>(g, sigma, W, ncut, e, p, f, x, y);
+    else if (comp == 1) apply_cut_row<T, KIND, 1, TX>(g, sigma, W, ncut, e, p, f, x, y);
+    else apply_cut_row<T, KIND, 2, TX>(g, sigma, W, ncut, e, p, f, x, y);
 }
 
 // Block forms of apply, restriction and prolongation: wave q of a workgroup
@@ -208,20 +223,19 @@ __device__ __forceinline__ void apply_cut_tab(const Grid &g, T sigma, const T *_
 template <class T, int KIND, int NR, class TX = T>
 __global__ void __launch_bounds__(kThreads)
 k_apply_split(Grid g, T sigma, const int32_t *__restrict__ cut, int64_t ncut, uint32_t ncb, const T *__restrict__ W,
-              const CellRun *__restrict__ cells, uint32_t nruns, int run_log, VPtr<const T> f, VPtr<const TX> x,
+              const CellRun *__restrict__ cells, uint32_t nruns, VPtr<const T> f, VPtr<const TX> x,
               VPtr<T> y) {
     const uint32_t b = blockIdx.x;
     const int q = threadIdx.x >> 6;
     if (b < ncb) {
-        const uint32_t e = ((b % kXcd) * (ncb / kXcd) + b / kXcd) * 64 + (threadIdx.x & 63);
-        if (e >= ncut) return;
-        apply_cut_tab<T, KIND, TX>(g, sigma, W, ncut, e, (uint32_t)cut[e], f.p[q], x.p[q], y.p[q]);
+        const uint32_t L = (b % kXcd) * (ncb / kXcd) + b / kXcd;
+        apply_cut_part<T, KIND, TX>(g, sigma, W, cut, ncut, L, threadIdx.x & 63, f.p[q], x.p[q], y.p[q]);
     } else {
         const uint32_t bv = b - ncb, nvb = gridDim.x - ncb;
         const uint32_t t = ((bv % kXcd) * (nvb / kXcd) + bv / kXcd) * 64 + (threadIdx.x & 63);
-        if (t >> run_log >= nruns) return;
-        const CellRun run = cells[t >> run_log];
-        const uint32_t lane = t & ((1u << run_log) - 1);
+        if (t >> kRunLog >= nruns) return;
+        const CellRun run = cells[t >> kRunLog];
+        const uint32_t lane = t & (kRunLanes - 1);
         if (!((run.visit >> lane) & 1)) return;
         apply_vac_body<T, KIND, TX>(g, sigma, run, lane, f.p[q], x.p[q], y.p[q]);
     }
@@ -261,12 +275,11 @@ k_apply_A(Grid g, Coefs<T> c, const T *__restrict__ x, T *__restrict__ y) {
 // and 516 us for the whole V-cycle at 128^3; the runs take 2.67 and 476 us.
 template <class T, int COMP, int NR>
 __device__ __forceinline__ void smooth_vac_n(const Grid &g, T sigma, const VPtr<const T> &f, const VPtr<T> &x,
-                                             uint32_t t, const VacRun *__restrict__ runs, uint32_t nruns,
-                                             int run_log) {
-    const uint32_t r = t >> run_log;
+                                             uint32_t t, const VacRun *__restrict__ runs, uint32_t nruns) {
+    const uint32_t r = t >> kRunLog;
     if (r >= nruns) return;
     const VacRun run = runs[r];
-    const uint32_t lane = t & ((1u << run_log) - 1);
+    const uint32_t lane = t & (kRunLanes - 1);
     if (!((run.mask >> lane) & 1)) return;
     const int64_t P = g.P, dy = g.sy, dz = g.sz;
     const uint32_t p = (uint32_t)run.p + 2 * lane;
@@ -372,7 +385,7 @@ struct SmoothArgs {
     const VacRun *runs;
     int64_t n;
     uint32_t nruns, ncb;
-    int run_log, colour, pair, wave_split;
+    int colour, pair, wave_split;
 };
 
 template <class T, int COMP, int NR>
@@ -394,7 +407,7 @@ k_smooth_split(Grid g, T sigma, SmoothArgs<T> A, VPtr<const T> f, VPtr<T> x) {
     } else {
         const uint32_t bv = b - A.ncb, nvb = gridDim.x - A.ncb;
         const uint32_t L = (bv % kXcd) * (nvb / kXcd) + bv / kXcd;
-        smooth_vac_n<T, COMP, NR>(g, sigma, f, x, L * kThreads + threadIdx.x, A.runs, A.nruns, A.run_log);
+        smooth_vac_n<T, COMP, NR>(g, sigma, f, x, L * kThreads + threadIdx.x, A.runs, A.nruns);
     }
 }
 
@@ -1770,17 +1783,17 @@ kb_step(const BJob *__restrict__ jobs, const int32_t *__restrict__ job_of) {
                                          vptr1(J.out), (uint32_t)item);
         } else {
             smooth_vac_n<T, COMP, 1>(J.g, J.sigma, vptr1(J.in), vptr1(J.out), (uint32_t)(item - J.ncut * blockDim.x),
-                                     J.runs, J.nruns, J.run_log);
+                                     J.runs, J.nruns);
         }
     } else if (STEP == BS_RESID) {
         if (lb < J.ncut) {
-            if (item < J.n)
-                apply_cut_tab<T, AK_RESID, T>(J.g, J.sigma, J.w, J.n, item, (uint32_t)J.cut[item], J.in, J.aux, J.out);
+            apply_cut_part<T, AK_RESID, T>(J.g, J.sigma, J.w, J.cut, J.n, (uint32_t)(item >> 6), (uint32_t)(item & 63),
+                                           J.in, J.aux, J.out);
         } else {
             const uint32_t t = (uint32_t)(item - J.ncut * blockDim.x);
-            if (t >> J.run_log >= J.nruns) return;
-            const CellRun run = J.cells[t >> J.run_log];
-            const uint32_t lane = t & ((1u << J.run_log) - 1);
+            if (t >> kRunLog >= J.nruns) return;
+            const CellRun run = J.cells[t >> kRunLog];
+            const uint32_t lane = t & (kRunLanes - 1);
             if ((run.visit >> lane) & 1) apply_vac_body<T, AK_RESID, T>(J.g, J.sigma, run, lane, J.in, J.aux, J.out);
         }
     } else if (STEP == BS_RESTRICT) {
@@ -1891,29 +1904,29 @@ void launch_apply_b(const Grid &g, T sigma, int kind, int nr, const VPtr<const T
                     const VPtr<const T> &x, const VPtr<T> &y, hipStream_t s, ClassList cut) {
     if (kind != AK_M && kind != AK_RESID) throw std::runtime_error("block apply: M or residual only");
     if (cut.n > 0 && !cut_weights<T>(cut)) throw std::runtime_error("apply: cut-cell list without its row table");
-    const uint32_t ncb = (uint32_t)(ceil_div(ceil_div(cut.n, 64), kXcd) * kXcd);
-    const int64_t nvb = ceil_div(ceil_div(cut.nruns << cut.run_log, 64), kXcd) * kXcd;
+    const uint32_t ncb = (uint32_t)(ceil_div(3 * ceil_div(cut.n, 64), kXcd) * kXcd);
+    const int64_t nvb = ceil_div(ceil_div(cut.nruns << kRunLog, 64), kXcd) * kXcd;
     const dim3 grid((unsigned)(ncb + nvb));
     if (kind == AK_M)
         DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<T, AK_M, NR>), grid, dim3(64 * NR), 0, s, g, sigma, cut.idx,
                                             cut.n, ncb, cut_weights<T>(cut), cut.cells, (uint32_t)cut.nruns,
-                                            cut.run_log, f, x, y))
+                                            f, x, y))
     else
         DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<T, AK_RESID, NR>), grid, dim3(64 * NR), 0, s, g, sigma,
                                             cut.idx, cut.n, ncb, cut_weights<T>(cut), cut.cells, (uint32_t)cut.nruns,
-                                            cut.run_log, f, x, y))
+                                            f, x, y))
 }
 
 void launch_apply_m_f32in(const Grid &g, double sigma, int nr, const VPtr<const float> &x,
                          const VPtr<double> &y, hipStream_t s, ClassList cut) {
     if (cut.n > 0 && !cut.w64) throw std::runtime_error("apply: cut-cell list without its row table");
-    const uint32_t ncb = (uint32_t)(ceil_div(ceil_div(cut.n, 64), kXcd) * kXcd);
-    const int64_t nvb = ceil_div(ceil_div(cut.nruns << cut.run_log, 64), kXcd) * kXcd;
+    const uint32_t ncb = (uint32_t)(ceil_div(3 * ceil_div(cut.n, 64), kXcd) * kXcd);
+    const int64_t nvb = ceil_div(ceil_div(cut.nruns << kRunLog, 64), kXcd) * kXcd;
     const dim3 grid((unsigned)(ncb + nvb));
     const VPtr<const double> f{};
     DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<double, AK_M, NR, float>), grid, dim3(64 * NR), 0, s, g, sigma,
                                         cut.idx, cut.n, ncb, cut_weights<double>(cut), cut.cells, (uint32_t)cut.nruns,
-                                        cut.run_log, f, x, y))
+                                            f, x, y))
 }
 
 template <class T>
@@ -1929,11 +1942,10 @@ void launch_smooth_b(const Grid &g, T sigma, int comp, int nr, const VPtr<const 
     A.n = cl.n;
     A.colour = cl.colour;
     A.nruns = (uint32_t)cl.nruns;
-    A.run_log = cl.run_log;
     A.pair = cl.pair;
     A.wave_split = nr > 1 && cl.n < cl.wave_split_max;
     A.ncb = (uint32_t)(ceil_div(ceil_div(cl.n, A.wave_split ? 64 : kThreads), kXcd) * kXcd);
-    const int64_t nvb = ceil_div(ceil_div(cl.nruns << cl.run_log, kThreads), kXcd) * kXcd;
+    const int64_t nvb = ceil_div(ceil_div(cl.nruns << kRunLog, kThreads), kXcd) * kXcd;
     const dim3 grid((unsigned)(A.ncb + nvb));
     if (grid.x == 0) return;   // no active face of the class on this level
     if (comp == 0)

@@ -356,14 +356,12 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
         for (const uint8_t f : fl) faces += (f & 1) + ((f >> 1) & 1) + ((f >> 2) & 1);
         const bool small = lds_level(P, faces, sizeof(float));
         const int nxh = (L.g.nx + 1) >> 1;
-        L.vrun_log = nxh <= 8 ? 3 : nxh <= 16 ? 4 : nxh <= 32 ? 5 : 6;
         // the lists, each built by a task of its own: a component's cut rows, a
         // class's runs (and its vacuum rows one by one on an LDS level), the
         // cells with a cut row, the grid rows holding an active cell or face
         std::vector<int32_t> cutv[3], vacv[6], cutc, arows, frows;
         std::vector<VacRun> runv[6];
         std::vector<CellRun> cruns;
-        L.crun_log = L.g.nx <= 8 ? 3 : L.g.nx <= 16 ? 4 : L.g.nx <= 32 ? 5 : 6;
         std::vector<std::function<void()>> tasks;
         for (int comp = 0; comp < 3; ++comp) {
             tasks.push_back([&, comp] {
@@ -384,16 +382,16 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
                             VacRun run{};
                             for (int ih = 0; 2 * ih + i0 < L.g.nx; ++ih) {
                                 const int64_t p = pidx(L.g, 2 * ih + i0, j, k);
-                                const int lane = ih & 63;
+                                const int lane = ih & (kRunLanes - 1);
                                 if (lane == 0) {
                                     const int at[3] = {2 * ih + i0, j, k};
-                                    run = VacRun{(int32_t)p, ((L.g.pmc >> comp) & 1) && at[comp] == 1, 0};
+                                    run = VacRun{(int32_t)p, 0, (uint16_t)(((L.g.pmc >> comp) & 1) && at[comp] == 1)};
                                 }
                                 if (fl[p] & (kFaceVacuum << comp)) {
-                                    run.mask |= 1ull << lane;
+                                    run.mask |= (uint16_t)(1u << lane);
                                     if (small) vacv[q].push_back((int32_t)p);
                                 }
-                                if ((lane == 63 || 2 * (ih + 1) + i0 >= L.g.nx) && run.mask) runv[q].push_back(run);
+                                if ((lane == kRunLanes - 1 || 2 * (ih + 1) + i0 >= L.g.nx) && run.mask) runv[q].push_back(run);
                             }
                         }
                 });
@@ -420,16 +418,16 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
             for (int k = 0; k < L.g.nz; ++k)
                 for (int j = 0; j < L.g.ny; ++j) {
                     bool any = false;
-                    for (int i0 = 0; i0 < L.g.nx; i0 += 64) {
+                    for (int i0 = 0; i0 < L.g.nx; i0 += kRunLanes) {
                         CellRun run{};
                         run.p = (int32_t)pidx(L.g, i0, j, k);
                         run.pmc = ((L.g.pmc & 1) && i0 == 0 ? 1 : 0) |
                                   (((L.g.pmc & 2) && j < 2) || ((L.g.pmc & 4) && k < 2) ? 2 : 0);
-                        for (int l = 0; l < 64 && i0 + l < L.g.nx; ++l) {
+                        for (int l = 0; l < kRunLanes && i0 + l < L.g.nx; ++l) {
                             const uint8_t f = fl[run.p + l];
-                            if (!((f & 7) & ~(f >> 3))) run.visit |= 1ull << l;
+                            if (!((f & 7) & ~(f >> 3))) run.visit |= (uint16_t)(1u << l);
                             for (int c = 0; c < 3; ++c)
-                                if (f & (kFaceActive << c)) run.act[c] |= 1ull << l;
+                                if (f & (kFaceActive << c)) run.act[c] |= (uint16_t)(1u << l);
                         }
                         any = any || (run.act[0] | run.act[1] | run.act[2]);
                         cruns.push_back(run);
@@ -437,7 +435,7 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
                     if (any) frows.push_back((int32_t)(k * L.g.ny + j));
                 }
             L.ncrun = (int64_t)cruns.size();
-            const int64_t per = (L.g.nx + 63) / 64;   // runs per grid row
+            const int64_t per = (L.g.nx + kRunLanes - 1) / kRunLanes;   // runs per grid row
             for (int32_t row : frows)
                 for (int64_t q = 0; q < per; ++q) cruns.push_back(CellRun(cruns[(size_t)(row * per + q)]));
             L.nfrun = (int64_t)cruns.size() - L.ncrun;

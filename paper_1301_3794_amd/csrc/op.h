@@ -32,10 +32,9 @@ struct Level {
     int32_t *cut = nullptr;
     int64_t cut_off[4] = {};
     // vacuum rows of class 2 c + colour as runs: vrun[vrun_off[q] ..
-    // vrun_off[q+1]), 2^vrun_log lanes each
+    // vrun_off[q+1])
     VacRun *vrun = nullptr;
     int64_t vrun_off[7] = {};
-    int vrun_log = 6;
     // LDS levels (lds_level in FP32): the cut list above is sorted by colour
     // within each component, and lds names every class's rows
     LdsRows lds;
@@ -46,17 +45,15 @@ struct Level {
     double *cellw64 = nullptr;
     float *cellw32 = nullptr;
     // runs of the cells of every grid row (ncrun of them), then of the rows
-    // holding an active face only (nfrun); 2^crun_log lanes each
+    // holding an active face only (nfrun)
     CellRun *crun = nullptr;
     int64_t ncrun = 0, nfrun = 0;
-    int crun_log = 6;
     ClassList cut_cells() const {
         ClassList cl;
         cl.idx = cutc;
         cl.n = ncutc;
         cl.cells = crun;
         cl.nruns = ncrun;
-        cl.run_log = crun_log;
         cl.w64 = cellw64;
         cl.w32 = cellw32;
         return cl;
@@ -92,7 +89,6 @@ struct Level {
         const int q = 2 * comp + colour;
         cl.runs = vrun ? vrun + vrun_off[q] : nullptr;
         cl.nruns = vrun_off[q + 1] - vrun_off[q];
-        cl.run_log = vrun_log;
         cl.wave_split_max = cut_wave_split;
         if (cutw64) cl.w64 = cutw64 + kCutW * cut_off[comp];
         if (cutw32) cl.w32 = cutw32 + kCutW * cut_off[comp];
