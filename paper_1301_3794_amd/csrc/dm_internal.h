@@ -301,10 +301,9 @@ __host__ __device__ inline VPtr<const T> as_const(const VPtr<T> &x) {
 // runs of 16 lanes along a grid row.  A run of one colour spans 32 cells, a
 // 128-byte line of FP32; a wider one leaves lanes idle at the row's end and
 // outside the cavity, and a narrower one reads more of the records (one load
-// of 8 or 16 bytes here).  Runs of 64 lanes (the row's last one and rows
-// of up to 32 narrower) with 64-bit masks: one sweep of 3 vectors at 128^3
-// 83.6 us, at 88 x 72 x 104 43.1 us, M x in FP64 at 72 x 80 x 64 29.3 us.
-// DM_RUN_FIGURES
+// of 8 or 16 bytes here).  Runs of 64 lanes (narrower where a row had fewer)
+// with 64-bit masks took 83.6 us for one sweep of 3 vectors at 128^3 and 43.1
+// at 88 x 72 x 104; these take 79.1 and 39.8.
 constexpr int kRunLog = 4, kRunLanes = 1 << kRunLog;
 
 // Consecutive cells of one colour in a grid row, for the smoother's vacuum
@@ -337,8 +336,10 @@ struct ClassList {
     // residual: the cells with a cut row
     const int32_t *idx = nullptr;
     int64_t n = 0;
-    // apply and residual: the runs of the other cells
+    // apply and residual: the runs of the other cells to visit, or (cells
+    // null) the class bytes of the level, for every other cell of the grid
     const CellRun *cells = nullptr;
+    const uint8_t *flags = nullptr;
     int colour = 0;      // smoother: the class's colour
     // smoother: the class's vacuum rows
     const VacRun *runs = nullptr;

@@ -126,21 +126,21 @@ __device__ __forceinline__ void put_face_at(const Grid &g, T *arr, int comp, uin
     put_face<T>(g, arr, comp, (int)(rr - jj * sy) - 1, (int)jj - 1, (int)kk - 1, (int64_t)p, v);
 }
 
-// M x or f - M x at lane `lane` of a run of cells whose
-// active rows are all vacuum rows (the other cells are listed and run the
-// full body): the same values, written the same way, zeros on the inactive
-// components included.  (K alone has no vacuum shortcut: its rows keep the
-// cross terms.)
+// M x or f - M x at the cell of padded index p whose active rows are all
+// vacuum rows (the other cells are listed and run the full body): the same
+// values, written the same way, zeros on the inactive components included.
+// act: bit c, the face of component c is active; image: the cell may have PMC
+// ghost images.  (K alone has no vacuum shortcut: its rows keep the cross
+// terms.)
 template <class T, int KIND, class TX = T>
-__device__ __forceinline__ void apply_vac_body(const Grid &g, T sigma, const CellRun &run, uint32_t lane,
+__device__ __forceinline__ void apply_vac_body(const Grid &g, T sigma, uint32_t act, bool image, uint32_t p,
                                                const T *__restrict__ f, const TX *__restrict__ x,
                                                T *__restrict__ y) {
     static_assert(KIND == AK_M || KIND == AK_RESID, "vacuum rows of M only");
     const int64_t P = g.P, dy = g.sy, dz = g.sz;
-    const uint32_t p = (uint32_t)run.p + lane;
     const T ih2 = inv_h2_of<T>(g);
     T v[3] = {T(0), T(0), T(0)};
-    if (((run.act[0] | run.act[1] | run.act[2]) >> lane) & 1) {
+    if (act) {
         // one branch for the three rows, so that all their loads are in flight
         // together (every cell of the grid has its neighbours in the padding)
 #pragma unroll
@@ -148,10 +148,10 @@ __device__ __forceinline__ void apply_vac_body(const Grid &g, T sigma, const Cel
             const TX *C = x + comp * P;
             v[comp] = ih2 * vac_row<T, TX>(C, p, dy, dz) - sigma * T(C[p]);
             if (KIND == AK_RESID) v[comp] = f[comp * P + p] - v[comp];
-            if (!((run.act[comp] >> lane) & 1)) v[comp] = T(0);
+            if (!((act >> comp) & 1)) v[comp] = T(0);
         }
     }
-    if (g.pmc && ((run.pmc & 2) || (run.pmc && lane < 2))) {
+    if (g.pmc && image) {
         put_face_at<T>(g, y, 0, p, v[0]);
         put_face_at<T>(g, y + P, 1, p, v[1]);
         put_face_at<T>(g, y + 2 * P, 2, p, v[2]);
@@ -160,6 +160,15 @@ __device__ __forceinline__ void apply_vac_body(const Grid &g, T sigma, const Cel
         (y + P)[p] = v[1];
         (y + 2 * P)[p] = v[2];
     }
+}
+
+// the same at lane `lane` of a run, where the run visits the cell
+template <class T, int KIND, class TX = T>
+__device__ __forceinline__ void apply_run(const Grid &g, T sigma, const CellRun &run, uint32_t lane,
+                                          const T *__restrict__ f, const TX *__restrict__ x, T *__restrict__ y) {
+    if (!((run.visit >> lane) & 1)) return;
+    const uint32_t act = ((run.act[0] >> lane) & 1) | ((run.act[1] >> lane) & 1) << 1 | ((run.act[2] >> lane) & 1) << 2;
+    apply_vac_body<T, KIND, TX>(g, sigma, act, (run.pmc & 2) || (run.pmc && lane < 2), (uint32_t)run.p + lane, f, x, y);
 }
 
 template <class T>
@@ -209,6 +218,18 @@ __device__ __forceinline__ void apply_cut_part(const Grid &g, T sigma, const T *
     else apply_cut_row<T, KIND, 2, TX>(g, sigma, W, ncut, e, p, f, x, y);
 }
 
+// the cut cells (their rows' table W), and the runs of the others or, without
+// them, the cells' class bytes
+template <class T>
+struct ApplyArgs {
+    const int32_t *cut;
+    const T *W;
+    const CellRun *cells;
+    const uint8_t *flags;
+    int64_t ncut;
+    uint32_t ncb, nruns;
+};
+
 // Block forms of apply, restriction and prolongation: wave q of a workgroup
 // applies the one-vector body to vector q of the workgroup's 64 cells (see
 // wave_item), so every lane keeps the register budget of the one-vector
@@ -218,26 +239,32 @@ __device__ __forceinline__ void apply_cut_part(const Grid &g, T sigma, const T *
 
 // The block apply in two parts, as the smoother's class updates: the first
 // ncb workgroups (a multiple of 8) take the cut-cell list (full body), the
-// rest all cells, skipping listed ones (vacuum rows only); wave q of a
-// workgroup takes vector q of 64 entries in either part.
+// rest the other cells, those of the listed runs or, without a list, every
+// cell of the grid by its class byte; wave q of a workgroup takes vector q of
+// 64 entries in either part.  (A run's record is 16 bytes for each lane of
+// the load, a class byte one: over the whole grid the runs were 1.5 to 3%
+// slower, FP64 at 104 x 88 x 80 and 128 x 128 x 96; they pay where they leave
+// rows out.)
 template <class T, int KIND, int NR, class TX = T>
 __global__ void __launch_bounds__(kThreads)
-k_apply_split(Grid g, T sigma, const int32_t *__restrict__ cut, int64_t ncut, uint32_t ncb, const T *__restrict__ W,
-              const CellRun *__restrict__ cells, uint32_t nruns, VPtr<const T> f, VPtr<const TX> x,
-              VPtr<T> y) {
+k_apply_split(Grid g, T sigma, ApplyArgs<T> A, VPtr<const T> f, VPtr<const TX> x, VPtr<T> y) {
     const uint32_t b = blockIdx.x;
     const int q = threadIdx.x >> 6;
-    if (b < ncb) {
-        const uint32_t L = (b % kXcd) * (ncb / kXcd) + b / kXcd;
-        apply_cut_part<T, KIND, TX>(g, sigma, W, cut, ncut, L, threadIdx.x & 63, f.p[q], x.p[q], y.p[q]);
+    if (b < A.ncb) {
+        const uint32_t L = (b % kXcd) * (A.ncb / kXcd) + b / kXcd;
+        apply_cut_part<T, KIND, TX>(g, sigma, A.W, A.cut, A.ncut, L, threadIdx.x & 63, f.p[q], x.p[q], y.p[q]);
+        return;
+    }
+    const uint32_t bv = b - A.ncb, nvb = gridDim.x - A.ncb;
+    const uint32_t t = ((bv % kXcd) * (nvb / kXcd) + bv / kXcd) * 64 + (threadIdx.x & 63);
+    if (A.cells) {
+        if (t >> kRunLog >= A.nruns) return;
+        apply_run<T, KIND, TX>(g, sigma, A.cells[t >> kRunLog], t & (kRunLanes - 1), f.p[q], x.p[q], y.p[q]);
     } else {
-        const uint32_t bv = b - ncb, nvb = gridDim.x - ncb;
-        const uint32_t t = ((bv % kXcd) * (nvb / kXcd) + bv / kXcd) * 64 + (threadIdx.x & 63);
-        if (t >> kRunLog >= nruns) return;
-        const CellRun run = cells[t >> kRunLog];
-        const uint32_t lane = t & (kRunLanes - 1);
-        if (!((run.visit >> lane) & 1)) return;
-        apply_vac_body<T, KIND, TX>(g, sigma, run, lane, f.p[q], x.p[q], y.p[q]);
+        int i, j, k;
+        if (!cell_of(g, t, i, j, k)) return;
+        const uint32_t p = (uint32_t)pidx(g, i, j, k), fl = A.flags[p];
+        if (!((fl & 7) & ~(fl >> 3))) apply_vac_body<T, KIND, TX>(g, sigma, fl & 7, true, p, f.p[q], x.p[q], y.p[q]);
     }
 }
 
@@ -1794,7 +1821,7 @@ kb_step(const BJob *__restrict__ jobs, const int32_t *__restrict__ job_of) {
             if (t >> kRunLog >= J.nruns) return;
             const CellRun run = J.cells[t >> kRunLog];
             const uint32_t lane = t & (kRunLanes - 1);
-            if ((run.visit >> lane) & 1) apply_vac_body<T, AK_RESID, T>(J.g, J.sigma, run, lane, J.in, J.aux, J.out);
+            apply_run<T, AK_RESID, T>(J.g, J.sigma, run, lane, J.in, J.aux, J.out);
         }
     } else if (STEP == BS_RESTRICT) {
         restrict_body<T>(J.g, J.gc, coefs_of(J.cc, J.gc.P), J.in, J.out, listed_item(J.gc, J.rows, J.nrows, item), J.xz);
@@ -1899,34 +1926,47 @@ void launch_prolong_add(const Grid &gf, const Grid &gc, const T *coef_f, const T
         default: throw std::runtime_error("block of more than 4 vectors"); \
     }
 
+namespace {
+template <class T>
+ApplyArgs<T> apply_args(const Grid &g, const ClassList &cut, dim3 &grid) {
+    if (cut.n > 0 && !cut_weights<T>(cut)) throw std::runtime_error("apply: cut-cell list without its row table");
+    if (!cut.cells && !cut.flags) throw std::runtime_error("apply: neither runs nor class bytes");
+    ApplyArgs<T> A;
+    A.cut = cut.idx;
+    A.W = cut_weights<T>(cut);
+    A.cells = cut.cells;
+    A.flags = cut.flags;
+    A.ncut = cut.n;
+    A.ncb = (uint32_t)(ceil_div(3 * ceil_div(cut.n, 64), kXcd) * kXcd);
+    A.nruns = (uint32_t)cut.nruns;
+    const int64_t items = cut.cells ? cut.nruns << kRunLog : (int64_t)g.nx * g.ny * g.nz;
+    grid = dim3((unsigned)(A.ncb + ceil_div(ceil_div(items, 64), kXcd) * kXcd));
+    return A;
+}
+}  // namespace
+
 template <class T>
 void launch_apply_b(const Grid &g, T sigma, int kind, int nr, const VPtr<const T> &f,
                     const VPtr<const T> &x, const VPtr<T> &y, hipStream_t s, ClassList cut) {
     if (kind != AK_M && kind != AK_RESID) throw std::runtime_error("block apply: M or residual only");
-    if (cut.n > 0 && !cut_weights<T>(cut)) throw std::runtime_error("apply: cut-cell list without its row table");
-    const uint32_t ncb = (uint32_t)(ceil_div(3 * ceil_div(cut.n, 64), kXcd) * kXcd);
-    const int64_t nvb = ceil_div(ceil_div(cut.nruns << kRunLog, 64), kXcd) * kXcd;
-    const dim3 grid((unsigned)(ncb + nvb));
+    dim3 grid;
+    const ApplyArgs<T> A = apply_args<T>(g, cut, grid);
+    if (grid.x == 0) return;   // no listed cell
     if (kind == AK_M)
-        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<T, AK_M, NR>), grid, dim3(64 * NR), 0, s, g, sigma, cut.idx,
-                                            cut.n, ncb, cut_weights<T>(cut), cut.cells, (uint32_t)cut.nruns,
-                                            f, x, y))
+        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<T, AK_M, NR>), grid, dim3(64 * NR), 0, s, g, sigma, A, f, x, y))
     else
-        DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<T, AK_RESID, NR>), grid, dim3(64 * NR), 0, s, g, sigma,
-                                            cut.idx, cut.n, ncb, cut_weights<T>(cut), cut.cells, (uint32_t)cut.nruns,
-                                            f, x, y))
+        DM_NR_SWITCH(nr,
+                     hipLaunchKernelGGL((k_apply_split<T, AK_RESID, NR>), grid, dim3(64 * NR), 0, s, g, sigma, A, f, x, y))
 }
 
 void launch_apply_m_f32in(const Grid &g, double sigma, int nr, const VPtr<const float> &x,
                          const VPtr<double> &y, hipStream_t s, ClassList cut) {
-    if (cut.n > 0 && !cut.w64) throw std::runtime_error("apply: cut-cell list without its row table");
-    const uint32_t ncb = (uint32_t)(ceil_div(3 * ceil_div(cut.n, 64), kXcd) * kXcd);
-    const int64_t nvb = ceil_div(ceil_div(cut.nruns << kRunLog, 64), kXcd) * kXcd;
-    const dim3 grid((unsigned)(ncb + nvb));
+    dim3 grid;
+    const ApplyArgs<double> A = apply_args<double>(g, cut, grid);
+    if (grid.x == 0) return;   // no listed cell
     const VPtr<const double> f{};
-    DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<double, AK_M, NR, float>), grid, dim3(64 * NR), 0, s, g, sigma,
-                                        cut.idx, cut.n, ncb, cut_weights<double>(cut), cut.cells, (uint32_t)cut.nruns,
-                                            f, x, y))
+    DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<double, AK_M, NR, float>), grid, dim3(64 * NR), 0, s, g, sigma, A,
+                                        f, x, y))
 }
 
 template <class T>

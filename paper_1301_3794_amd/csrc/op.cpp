@@ -412,11 +412,12 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
                     if (any) arows.push_back((int32_t)(k * L.g.ny + j));
                 }
         });
-        // the cells without a cut row as runs: every grid row, then those
-        // holding an active face
+        // the cells without a cut row of the grid rows holding an active face,
+        // as runs
         tasks.push_back([&] {
             for (int k = 0; k < L.g.nz; ++k)
                 for (int j = 0; j < L.g.ny; ++j) {
+                    const size_t row0 = cruns.size();
                     bool any = false;
                     for (int i0 = 0; i0 < L.g.nx; i0 += kRunLanes) {
                         CellRun run{};
@@ -433,12 +434,9 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
                         cruns.push_back(run);
                     }
                     if (any) frows.push_back((int32_t)(k * L.g.ny + j));
+                    else cruns.resize(row0);
                 }
             L.ncrun = (int64_t)cruns.size();
-            const int64_t per = (L.g.nx + kRunLanes - 1) / kRunLanes;   // runs per grid row
-            for (int32_t row : frows)
-                for (int64_t q = 0; q < per; ++q) cruns.push_back(CellRun(cruns[(size_t)(row * per + q)]));
-            L.nfrun = (int64_t)cruns.size() - L.ncrun;
         });
         all_of(L.g, tasks);
         for (int comp = 0; comp < 3; ++comp) {
@@ -463,7 +461,9 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
         L.lds.vac_off[6] = (int32_t)vac.size();
         L.ncutc = (int64_t)cutc.size();
         L.crun = op->dalloc<CellRun>(cruns.size());
-        DM_HIP(hipMemcpyAsync(L.crun, cruns.data(), cruns.size() * sizeof(CellRun), hipMemcpyHostToDevice, op->stream));
+        if (!cruns.empty())
+            DM_HIP(hipMemcpyAsync(L.crun, cruns.data(), cruns.size() * sizeof(CellRun), hipMemcpyHostToDevice,
+                                  op->stream));
         // tabulated rows of the cut lists and of the cells with a cut row
         {
             std::vector<double> tab, ctab;

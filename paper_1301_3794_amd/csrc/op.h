@@ -44,16 +44,14 @@ struct Level {
     // tabulated rows of the cells in cutc (3 components x kCutW per cell)
     double *cellw64 = nullptr;
     float *cellw32 = nullptr;
-    // runs of the cells of every grid row (ncrun of them), then of the rows
-    // holding an active face only (nfrun)
+    // runs of the cells of the grid rows holding an active face
     CellRun *crun = nullptr;
-    int64_t ncrun = 0, nfrun = 0;
+    int64_t ncrun = 0;
     ClassList cut_cells() const {
         ClassList cl;
         cl.idx = cutc;
         cl.n = ncutc;
-        cl.cells = crun;
-        cl.nruns = ncrun;
+        cl.flags = reinterpret_cast<const uint8_t *>(coef64 + 7 * g.P);   // row classes, after the 7 blocks
         cl.w64 = cellw64;
         cl.w32 = cellw32;
         return cl;
@@ -68,8 +66,8 @@ struct Level {
     // that stay zero on the other rows (the block V-cycle's residual)
     ClassList cut_cells_rows() const {
         ClassList cl = cut_cells();
-        cl.cells = crun + ncrun;
-        cl.nruns = nfrun;
+        cl.cells = crun;
+        cl.nruns = ncrun;
         return cl;
     }
     // the block smoother's threshold for one wave per vector (dm_options)
