@@ -1,6 +1,6 @@
-"""The row runs of the stencil kernels at every run width and at row ends:
-grids whose rows take 8, 16, 32 or 64 lanes per run, rows of several runs,
-and odd rows (the coarser level), against the oracle.
+"""The row runs of the stencil kernels (16 lanes each) at row ends: rows
+shorter than a run, of one, of several and ending a lane or two into the
+next, and odd rows (the coarser level), against the oracle.
 
 Tolerances (norm-wise, as in test_gpu_parity.py): FP64 1e-12, FP32 2e-5.
 """
