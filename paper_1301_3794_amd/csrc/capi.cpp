@@ -105,6 +105,54 @@ void fill_ghosts(const Level &L, int prec, const void *v, bool cells, hipStream_
     else launch_mirror_faces<float>(L.g, (float *)v, s);
 }
 
+// Whether every vector lies in the memory of `device`, where a copy kernel can
+// take it in place
+template <class V>
+bool all_on(int device, int count, const V *const *v) {
+    for (int q = 0; q < count; ++q) {
+        hipPointerAttribute_t a{};
+        if (hipPointerGetAttributes(&a, v[q]) != hipSuccess) {
+            (void)hipGetLastError();   // plain host memory
+            return false;
+        }
+        if (a.type != hipMemoryTypeDevice || a.device != device) return false;
+    }
+    return true;
+}
+
+// `run`, a V-cycle from the slots at fin to those at xout, on the caller's
+// vectors f and x.  One launch each way copies them (f on the units holding an
+// active row, as the rest is not read, x whole); vectors elsewhere, in host
+// memory or on another device, go through the runtime's copies, since a kernel
+// that read them in place would fault.
+template <class T, class Run>
+void between_buffers(dm_op *op, int nr, const void *const *f, void *const *x, T *fin, T *xout, hipStream_t s,
+                     Run &&run) {
+    const int64_t n = op->n0();
+    const int prec = 8 * (int)sizeof(T);
+    VPtr<const T> F{}, XO{};
+    VPtr<T> FI{}, X{};
+    for (int q = 0; q < nr; ++q) {
+        F.p[q] = (const T *)f[q];
+        FI.p[q] = fin + q * n;
+        XO.p[q] = xout + q * n;
+        X.p[q] = (T *)x[q];
+    }
+    if (all_on(op->device, nr, f)) {
+        for (int q = 0; q < nr; ++q) fill_ghosts(op->lv[0], prec, f[q], false, s);
+        launch_cast_b<T, T>(nr, F, FI, n, s, op->vspan());
+    } else {
+        for (int q = 0; q < nr; ++q) {
+            DM_HIP(hipMemcpyAsync(FI.p[q], F.p[q], n * sizeof(T), hipMemcpyDefault, s));
+            fill_ghosts(op->lv[0], prec, FI.p[q], false, s);
+        }
+    }
+    run();
+    if (all_on(op->device, nr, x)) launch_cast_b<T, T>(nr, XO, X, n, s);
+    else
+        for (int q = 0; q < nr; ++q) DM_HIP(hipMemcpyAsync(X.p[q], XO.p[q], n * sizeof(T), hipMemcpyDefault, s));
+}
+
 int auto_levels(const int d[3]) {
     int l = 1, n[3] = {d[0], d[1], d[2]};
     while (n[0] % 2 == 0 && n[1] % 2 == 0 && n[2] % 2 == 0 &&
@@ -413,20 +461,11 @@ int dm_vcycle(dm_op *op, int prec, const void *f, void *x, void *stream) {
     if (!op || !f || !x) return fail(DM_EINVAL, "NULL argument");
     if (prec != 64 && prec != 32) return fail(DM_EINVAL, "prec must be 64 or 32");
     return on_device(op, stream, [&](hipStream_t s) -> int {
-        fill_ghosts(op->lv[0], prec, f, false, s);
         // through the solver's captured V-cycle graph, between its fixed buffers
         ensure_krylov_small(op);
-        const int64_t n = op->n0();
-        // the V-cycle reads f on active rows only; x is copied whole
-        if (prec == 64) {
-            launch_cast_b<double, double>(1, vptr1((const double *)f), vptr1(op->gv_f64), n, s, op->vspan());
-            vcycle_graphed(op, prec, s);
-            launch_cast_b<double, double>(1, vptr1((const double *)op->gv_x64), vptr1((double *)x), n, s);
-        } else {
-            launch_cast_b<float, float>(1, vptr1((const float *)f), vptr1(op->fg_f32), n, s, op->vspan());
-            vcycle_graphed(op, prec, s);
-            launch_cast_b<float, float>(1, vptr1((const float *)op->fg_x32), vptr1((float *)x), n, s);
-        }
+        auto run = [&] { vcycle_graphed(op, prec, s); };
+        if (prec == 64) between_buffers(op, 1, &f, &x, op->gv_f64, op->gv_x64, s, run);
+        else between_buffers(op, 1, &f, &x, op->fg_f32, op->fg_x32, s, run);
         return DM_OK;
     });
 }
@@ -440,26 +479,9 @@ int dm_vcycle_block(dm_op *op, int prec, int nrhs, const void *const *f, void *c
         if (!f[q] || !x[q]) return fail(DM_EINVAL, "NULL vector in the block");
     return on_device(op, stream, [&](hipStream_t s) -> int {
         ensure_block(op, prec);
-        const int64_t n = op->n0();
-        for (int q = 0; q < nrhs; ++q) fill_ghosts(op->lv[0], prec, f[q], false, s);
-        // one launch each way: f on the units holding an active row (the rest
-        // is not read), x whole
-        auto cycle = [&](auto *fin, auto *xout) {
-            using T = std::remove_pointer_t<decltype(fin)>;
-            VPtr<const T> F{}, XI{};
-            VPtr<T> FI{}, X{};
-            for (int q = 0; q < nrhs; ++q) {
-                F.p[q] = (const T *)f[q];
-                FI.p[q] = fin + q * n;
-                XI.p[q] = xout + q * n;
-                X.p[q] = (T *)x[q];
-            }
-            launch_cast_b<T, T>(nrhs, F, FI, n, s, op->vspan());
-            vcycle_block_graphed(op, prec, nrhs, s);
-            launch_cast_b<T, T>(nrhs, XI, X, n, s);
-        };
-        if (prec == 64) cycle(op->lv[0].bf64, op->lv[0].bx64);
-        else cycle(op->lv[0].bf32, op->lv[0].bx32);
+        auto run = [&] { vcycle_block_graphed(op, prec, nrhs, s); };
+        if (prec == 64) between_buffers(op, nrhs, f, x, op->lv[0].bf64, op->lv[0].bx64, s, run);
+        else between_buffers(op, nrhs, f, x, op->lv[0].bf32, op->lv[0].bx32, s, run);
         return DM_OK;
     });
 }
@@ -663,22 +685,26 @@ int dm_batch_vcycle(dm_batch *b, const float *const *f_dev, float *const *x_dev,
         for (size_t i = 0; i < count; ++i)
             if (!f_dev[i] || !x_dev[i]) return fail(DM_EINVAL, "NULL member vector");
         // every member's vector in one launch per 64 (a copy call per member
-        // each way took as long as a quarter of the fused V-cycle of 16)
-        auto copies = [&](auto &&ends) {
+        // each way took as long as a quarter of the fused V-cycle of 16);
+        // vectors outside the device's memory by the runtime's copies
+        auto copies = [&](bool in_place, auto &&ends) {
             for (size_t i0 = 0; i0 < count; i0 += kCopyMax) {
                 CopyArgs A{};
                 const size_t m = std::min<size_t>(kCopyMax, count - i0);
                 for (size_t q = 0; q < m; ++q) ends(b->ops[i0 + q], i0 + q, A.in[q], A.out[q], A.n[q]);
-                launch_copy_many((int)m, A, s);
+                if (in_place) launch_copy_many((int)m, A, s);
+                else
+                    for (size_t q = 0; q < m; ++q)
+                        DM_HIP(hipMemcpyAsync(A.out[q], A.in[q], A.n[q] * sizeof(float), hipMemcpyDefault, s));
             }
         };
-        copies([&](dm_op *op, size_t i, const float *&in, float *&out, int64_t &n) {
+        copies(all_on(b->device, (int)count, f_dev), [&](dm_op *op, size_t i, const float *&in, float *&out, int64_t &n) {
             in = f_dev[i];
             out = op->fg_f32;
             n = op->n0();
         });
         DM_HIP(hipGraphLaunch(b->graph, s));
-        copies([&](dm_op *op, size_t i, const float *&in, float *&out, int64_t &n) {
+        copies(all_on(b->device, (int)count, x_dev), [&](dm_op *op, size_t i, const float *&in, float *&out, int64_t &n) {
             in = op->fg_x32;
             out = x_dev[i];
             n = op->n0();
