@@ -305,6 +305,9 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
     for (int a = 0; a < 3; ++a)
         if (op->geom.bc_lo[a] == DM_BC_PMC) pmc |= 1 << a;
     Grid g0 = make_grid(op->dims[0], op->dims[1], op->dims[2], op->h, pmc);
+    // before anything is sized or indexed by it: the row lists and the kernels'
+    // index arithmetic are 32-bit (coarser levels are smaller)
+    if (g0.P > INT32_MAX) throw DmError{DM_EINVAL, "grid too large for 32-bit row lists"};
     std::vector<double> fr;
     if (op->geom.kind == DM_GEOM_USER) {
         fr.assign(user_frac, user_frac + 7 * g0.P);
@@ -421,11 +424,12 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
                     bool any = false;
                     for (int i0 = 0; i0 < L.g.nx; i0 += kRunLanes) {
                         CellRun run{};
-                        run.p = (int32_t)pidx(L.g, i0, j, k);
+                        const int64_t p0 = pidx(L.g, i0, j, k);
+                        run.p = (int32_t)p0;
                         run.pmc = ((L.g.pmc & 1) && i0 == 0 ? 1 : 0) |
                                   (((L.g.pmc & 2) && j < 2) || ((L.g.pmc & 4) && k < 2) ? 2 : 0);
                         for (int l = 0; l < kRunLanes && i0 + l < L.g.nx; ++l) {
-                            const uint8_t f = fl[run.p + l];
+                            const uint8_t f = fl[p0 + l];
                             if (!((f & 7) & ~(f >> 3))) run.visit |= (uint16_t)(1u << l);
                             for (int c = 0; c < 3; ++c)
                                 if (f & (kFaceActive << c)) run.act[c] |= (uint16_t)(1u << l);
@@ -502,7 +506,6 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
             DM_HIP(hipMemcpyAsync(L.cutc, cutc.data(), cutc.size() * sizeof(int32_t), hipMemcpyHostToDevice,
                                   op->stream));
         }
-        if (P > INT32_MAX) throw DmError{DM_EINVAL, "grid too large for 32-bit row lists"};
         if (!cut.empty()) {
             for (int32_t &p : cut)
                 if (odd_cell(L.g, p)) p |= INT32_MIN;
