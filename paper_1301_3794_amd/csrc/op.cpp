@@ -2,15 +2,13 @@
 // and the dense FP64 inverses of the coarsest vector and scalar operators.
 #include <algorithm>
 #include <cmath>
-#include <exception>
 #include <functional>
 #include <numeric>
-#include <system_error>
-#include <thread>
 #include <unordered_map>
 
 #include "geometry.h"
 #include "op.h"
+#include "tasks.h"
 
 namespace dm {
 
@@ -112,34 +110,9 @@ std::vector<double> to_coefs(const Grid &g, const std::vector<double> &fr, bool 
 
 }  // namespace
 
-// Every task, each on a thread of its own on a grid worth it; the first
-// exception of a task is thrown again here, and a task that gets no thread
-// runs on this one
+// every task, on threads on a grid worth them
 static void all_of(const Grid &g, const std::vector<std::function<void()>> &tasks) {
-    std::vector<std::exception_ptr> errs(tasks.size());
-    auto run = [&](size_t t) {
-        try {
-            tasks[t]();
-        } catch (...) {
-            errs[t] = std::current_exception();
-        }
-    };
-    std::vector<std::thread> th;
-    th.reserve(tasks.size());
-    for (size_t t = 0; t < tasks.size(); ++t) {
-        bool threaded = false;
-        if (g.P >= 20000 && t + 1 < tasks.size()) {
-            try {
-                th.emplace_back(run, t);
-                threaded = true;
-            } catch (const std::system_error &) {
-            }
-        }
-        if (!threaded) run(t);
-    }
-    for (auto &t : th) t.join();
-    for (auto &e : errs)
-        if (e) std::rethrow_exception(e);
+    run_tasks(g.P >= 20000, tasks);
 }
 
 // f(k0, k1) on the planes of the grid, split over tasks
@@ -256,11 +229,7 @@ static void refine_vacuum_flags(const Grid &g, const std::vector<double> &c, std
                     }
                 }
     };
-    const int nt = std::max(1, std::min(16, g.nz));
-    std::vector<std::thread> th;
-    for (int t = 0; t < nt; ++t)
-        th.emplace_back(work, (int)((int64_t)g.nz * t / nt), (int)((int64_t)g.nz * (t + 1) / nt));
-    for (auto &t : th) t.join();
+    over_planes(g, work);
 }
 
 // The tables of a level: its components' cut lists (component c's rows,
@@ -288,9 +257,9 @@ static void cut_tables(const Grid &g, const std::vector<double> &c, const std::v
                 tab_row(g, c, cg, comp, cells[e], cells_tab.data() + (size_t)comp * kCutW * nc + e, nc);
         }
     };
-    std::vector<std::thread> th;
-    for (int q = 0; q < 3 * kParts + 3; ++q) th.emplace_back(work, q);
-    for (auto &t : th) t.join();
+    std::vector<std::function<void()>> tasks;
+    for (int q = 0; q < 3 * kParts + 3; ++q) tasks.push_back([&, q] { work(q); });
+    all_of(g, tasks);
 }
 
 // whether a padded index is that of a cell of colour 1
