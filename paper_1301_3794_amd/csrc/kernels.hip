@@ -86,11 +86,33 @@ __device__ inline T inv_h2_of(const Grid &g) {
 // ---------------------------------------------------------------------------
 // y = M x, y = K x, or r = f - M x
 // ---------------------------------------------------------------------------
+// The rows below are formed in several kernels (launched class updates, sweeps
+// in LDS, apply and residual, one vector or a block), and a value may not
+// depend on which of them formed it: where a product and a sum may or may not
+// be contracted, the fused multiply-add is written out, with the row's largest
+// term as the product that is not rounded.  (Left to the compiler, the sweeps
+// in LDS rounded w_0 x_p of a cut row first: 4% more error in the FP32 V-cycle
+// of the 16^3 sphere.)
+__device__ inline float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ inline double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // 7-point vacuum row of component array C at p (no 1/h^2)
 template <class T, class TX = T>
 __device__ inline T vac_row(const TX *C, int64_t p, int64_t dy, int64_t dz) {
-    return T(6) * T(C[p]) - (T(C[p - 1]) + T(C[p + 1])) - (T(C[p - dy]) + T(C[p + dy])) -
+    return fused(T(6), T(C[p]), -(T(C[p - 1]) + T(C[p + 1]))) - (T(C[p - dy]) + T(C[p + dy])) -
            (T(C[p - dz]) + T(C[p + dz]));
+}
+
+// the vacuum row of M at p, whose value is xp
+template <class T, class TX = T>
+__device__ inline T vac_row_m(const TX *C, int64_t p, int64_t dy, int64_t dz, T ih2, T sigma, T xp) {
+    return fused(ih2, vac_row<T, TX>(C, p, dy, dz), -(sigma * xp));
+}
+
+// the centre terms of a tabulated row: w_0 x_p - sigma a x_p
+template <class T>
+__device__ inline T centre_terms(T w0, T sigma, T a, T xp) {
+    return fused(w0, xp, -(sigma * a * xp));
 }
 
 // y = K x: rows keep their curl-curl cross terms (no vacuum shortcut)
@@ -146,7 +168,7 @@ __device__ __forceinline__ void apply_vac_body(const Grid &g, T sigma, uint32_t 
 #pragma unroll
         for (int comp = 0; comp < 3; ++comp) {
             const TX *C = x + comp * P;
-            v[comp] = ih2 * vac_row<T, TX>(C, p, dy, dz) - sigma * T(C[p]);
+            v[comp] = vac_row_m<T, TX>(C, p, dy, dz, ih2, sigma, T(C[p]));
             if (KIND == AK_RESID) v[comp] = f[comp * P + p] - v[comp];
             if (!((act >> comp) & 1)) v[comp] = T(0);
         }
@@ -189,9 +211,9 @@ __device__ __forceinline__ void apply_cut_row(const Grid &g, T sigma, const T *_
     const T a = Wc[kCutTerms * ncut + e];
     T v = T(0);
     if (a != T(0)) {
-        T row = -sigma * a * T(x[COMP * P + p]);
+        T row = centre_terms(Wc[e], sigma, a, T(x[COMP * P + p]));
 #pragma unroll
-        for (int t = 0; t < kCutTerms; ++t) {
+        for (int t = 1; t < kCutTerms; ++t) {
             const CutTerm ct = cut_term(COMP, t);
             row += Wc[t * ncut + e] * T(x[ct.comp * P + p + ct.di + ct.dj * dy + ct.dk * dz]);
         }
@@ -312,13 +334,13 @@ __device__ __forceinline__ void smooth_vac_n(const Grid &g, T sigma, const VPtr<
     const int64_t P = g.P, dy = g.sy, dz = g.sz;
     const uint32_t p = (uint32_t)run.p + 2 * lane;
     const T ih2 = inv_h2_of<T>(g);
-    const T d = T(6) * ih2 - sigma;
+    const T d = fused(T(6), ih2, -sigma);
     T nv[NR];
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
         const T *xc = x.p[q] + COMP * P;
         const T xp = xc[p];
-        const T row = ih2 * vac_row<T>(xc, p, dy, dz) - sigma * xp;
+        const T row = vac_row_m<T>(xc, p, dy, dz, ih2, sigma, xp);
         nv[q] = xp + (f.p[q][COMP * P + p] - row) / d;
     }
 #pragma unroll
@@ -378,15 +400,15 @@ __device__ __forceinline__ void smooth_cut_n(const Grid &g, T sigma, const int32
 #pragma unroll
     for (int t = 0; t < kCutOwn; ++t) w[t] = W[t * n + e];
     const T a = W[kCutTerms * n + e];
-    const T d = W[(kCutTerms + 1) * n + e] - sigma * a;
+    const T d = fused(-sigma, a, W[(kCutTerms + 1) * n + e]);
     T nv[NR];
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
         const T *X = x.p[q];
         const T xs = (X + COMP * P)[p];
-        T row = -sigma * a * xs;
+        T row = centre_terms(w[0], sigma, a, xs);
 #pragma unroll
-        for (int t = 0; t < kCutOwn; ++t) {
+        for (int t = 1; t < kCutOwn; ++t) {
             const CutTerm ct = cut_term(COMP, t);
             row += w[t] * (X + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz))[p];
         }
@@ -475,22 +497,21 @@ __device__ __forceinline__ void lds_update(const Grid &g, T sigma, T ih2, T dvac
     const T xp = xc[p];
     T nv;
     if (cut) {
-        T cross = T(0), row = -sigma * r.a * xp;
+        T cross = T(0), row = centre_terms(r.w[0], sigma, r.a, xp);
 #pragma unroll
         for (int u = kCutOwn; u < kCutTerms; ++u) {
             const CutTerm ct = cut_term(COMP, u);
             cross += r.w[u] * xs[(int)p + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz)];
         }
 #pragma unroll
-        for (int u = 0; u < kCutOwn; ++u) {
+        for (int u = 1; u < kCutOwn; ++u) {
             const CutTerm ct = cut_term(COMP, u);
             row += r.w[u] * xs[(int)p + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz)];
         }
         row += cross;
-        nv = xp + (fv - row) / (r.d - sigma * r.a);
+        nv = xp + (fv - row) / fused(-sigma, r.a, r.d);
     } else {
-        const T row = ih2 * vac_row<T>(xc, p, dy, dz) - sigma * xp;
-        nv = xp + (fv - row) / dvac;
+        nv = xp + (fv - vac_row_m<T>(xc, p, dy, dz, ih2, sigma, xp)) / dvac;
     }
     if (PMC) put_face_at<T>(g, xc, COMP, p, nv);
     else xc[p] = nv;
@@ -501,7 +522,7 @@ __device__ __forceinline__ void sweeps_lds_body(const Grid &g, T sigma, const Ld
                                                 int sweeps, int reverse, int zero, const T *__restrict__ f,
                                                 T *__restrict__ x, T *xs) {
     const int P = (int)g.P, n3 = 3 * P;
-    const T ih2 = inv_h2_of<T>(g), dvac = T(6) * ih2 - sigma;
+    const T ih2 = inv_h2_of<T>(g), dvac = fused(T(6), ih2, -sigma);
     const int tid = threadIdx.x;
     for (int e = tid; e < n3; e += kLdsThreads) xs[e] = zero ? T(0) : x[e];
     auto load_p = [&](int q, int t) __attribute__((always_inline)) -> uint32_t {
