@@ -4,11 +4,12 @@
 // launches (kernels.hip, launch_batched): at depth d every member that still
 // has a coarser level smooths, forms its residual and restricts; a member
 // whose coarsest level is d solves it there; on the way up the members
-// prolong and post-smooth.  Each member's sequence of operations is exactly
-// its own V-cycle's, so the results are those of the single-operator
-// V-cycle; only the launches are shared.  The fused sequence is recorded in
-// one HIP graph, for the block size (64, 128 or 256 threads) that the
-// autotuner timed fastest.
+// prolong and post-smooth.  Each member takes the steps of its own V-cycle
+// in their order; only the launches are shared.  Its values do not depend on
+// the other members (LDS sweeps and launches round alike), and differ from
+// those of its own FP32 V-cycle by rounding: the cut rows are summed in FP64
+// from FP64 tables here.  The fused sequence is recorded in one HIP graph,
+// for the block size (64, 128 or 256 threads) that the autotuner timed fastest.
 //
 // dm_batch_eigs runs every member's eigensolve on its own host thread and
 // stream; at each FP32 preconditioner call the threads meet, and the last to
@@ -70,8 +71,8 @@ std::vector<HostStep> schedule(dm_batch *b) {
     // the rows of a class update or of the residual
     auto rows = [&](BJob &J, const ClassList &cl) {
         J.cut = cl.idx;
-        J.w = cl.w32;
-        J.s = static_cast<float *>(cl.s);
+        J.w = cl.w64;
+        J.s = static_cast<double *>(cl.s);
         J.runs = cl.runs;
         J.cells = cl.cells;
         J.n = cl.n;

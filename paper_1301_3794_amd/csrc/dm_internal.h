@@ -411,10 +411,11 @@ struct BJob {
     const double *inv;    // coarsest dense inverse (coarse)
     const int64_t *idx;   // its active-face index (coarse)
     // smooth and residual: the class's or the level's rows (ClassList); the
-    // cut part takes the job's first ncut blocks, the runs the others
+    // cut part, with its FP64 table and sums, takes the job's first ncut
+    // blocks, the runs the others
     const int32_t *cut;
-    const float *w;
-    float *s;
+    const double *w;
+    double *s;
     const VacRun *runs;
     const CellRun *cells;
     int64_t n, ncut;
