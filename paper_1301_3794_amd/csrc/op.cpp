@@ -110,19 +110,19 @@ std::vector<double> to_coefs(const Grid &g, const std::vector<double> &fr, bool 
 
 }  // namespace
 
-// every task, on threads on a grid worth them
+// every task, on threads on a grid worth them (the tables below are, on any)
 static void all_of(const Grid &g, const std::vector<std::function<void()>> &tasks) {
     run_tasks(g.P >= 20000, tasks);
 }
 
 // f(k0, k1) on the planes of the grid, split over tasks
 template <class F>
-static void over_planes(const Grid &g, F &&f) {
+static std::vector<std::function<void()>> over_planes(const Grid &g, F &f) {
     const int nt = std::max(1, std::min(16, g.nz));
     std::vector<std::function<void()>> tasks;
     for (int t = 0; t < nt; ++t)
         tasks.push_back([&, t] { f((int)((int64_t)g.nz * t / nt), (int)((int64_t)g.nz * (t + 1) / nt)); });
-    all_of(g, tasks);
+    return tasks;
 }
 
 // row classes of every cell (kFaceActive / kFaceVacuum bits) from the
@@ -130,7 +130,7 @@ static void over_planes(const Grid &g, F &&f) {
 std::vector<uint8_t> row_flags(const Grid &g, const std::vector<double> &c) {
     const int64_t P = g.P;
     std::vector<uint8_t> fl(P, 0);
-    over_planes(g, [&](int k0, int k1) {
+    auto work = [&](int k0, int k1) {
         for (int k = k0; k < k1; ++k)
             for (int j = 0; j < g.ny; ++j)
                 for (int i = 0; i < g.nx; ++i) {
@@ -151,7 +151,8 @@ std::vector<uint8_t> row_flags(const Grid &g, const std::vector<double> &c) {
                         if (c[a * P + p] != 0.0) f |= (uint8_t)((kFaceActive << a) | (vac ? (kFaceVacuum << a) : 0));
                     fl[p] = f;
                 }
-    });
+    };
+    all_of(g, over_planes(g, work));
     return fl;
 }
 
@@ -229,7 +230,7 @@ static void refine_vacuum_flags(const Grid &g, const std::vector<double> &c, std
                     }
                 }
     };
-    over_planes(g, work);
+    run_tasks(true, over_planes(g, work));
 }
 
 // The tables of a level: its components' cut lists (component c's rows,
@@ -259,7 +260,7 @@ static void cut_tables(const Grid &g, const std::vector<double> &c, const std::v
     };
     std::vector<std::function<void()>> tasks;
     for (int q = 0; q < 3 * kParts + 3; ++q) tasks.push_back([&, q] { work(q); });
-    all_of(g, tasks);
+    run_tasks(true, tasks);
 }
 
 // whether a padded index is that of a cell of colour 1
