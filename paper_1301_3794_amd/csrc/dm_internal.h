@@ -297,14 +297,21 @@ __host__ __device__ inline VPtr<const T> as_const(const VPtr<T> &x) {
     return v;
 }
 
-// The stencil kernels take the vacuum rows and the cells without a cut row by
-// runs of 16 lanes along a grid row.  A run of one colour spans 32 cells, a
-// 128-byte line of FP32; a wider one leaves lanes idle at the row's end and
-// outside the cavity, and a narrower one reads more of the records (one load
-// of 8 or 16 bytes here).  Runs of 64 lanes (narrower where a row had fewer)
-// with 64-bit masks took 83.6 us for one sweep of 3 vectors at 128^3 and 43.1
-// at 88 x 72 x 104; these take 79.1 and 39.8.
-constexpr int kRunLog = 4, kRunLanes = 1 << kRunLog;
+// The smoother takes the vacuum rows, and the V-cycle's residual and the block
+// products the cells without a cut row, by runs of 8 lanes along a grid row (a
+// whole-grid apply or residual walks class bytes instead, see k_apply_split).
+// A wider run leaves lanes idle at the row's end and outside the cavity, a
+// narrower one reads more of the records (one load of 8 or 16 bytes here).
+// One sweep, in us, with runs of
+//                                         8     16     32 lanes
+//   FP32, 3 vectors, 128^3             77.8   80.6   84.5
+//   FP32, 3 vectors, 88 x 72 x 104     41.9   42.9   44.2
+//   FP64, 4 vectors, 16 x 128 x 128    46.0   51.7   65.1
+//   FP64, 1 vector, 8 x 128 x 256      24.4   28.4   37.0
+//   FP32, 4 vectors, 48 x 48 x 512     91.8   90.0   90.2   (quarter 9-cell)
+// (walking listed grid rows by class bytes, 47.4 and 25.5 in the third and
+// fourth line); runs of 64 lanes took 4.5% longer than 16 at 128^3.
+constexpr int kRunLog = 3, kRunLanes = 1 << kRunLog;
 
 // Consecutive cells of one colour in a grid row, for the smoother's vacuum
 // rows: lane l stands for padded index p + 2 l, and updates it where bit l of

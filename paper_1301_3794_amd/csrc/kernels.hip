@@ -322,7 +322,7 @@ k_apply_A(Grid g, Coefs<T> c, const T *__restrict__ x, T *__restrict__ y) {
 // then the cell's class byte, then the values, with 64-bit divisions in
 // between) took 2.98 us per launch on the 32^3 level of one vector's V-cycle
 // and 516 us for the whole V-cycle at 128^3; the runs took 2.67 and 476 us (now
-// 444, with narrower runs and the small levels in LDS).
+// 435, with narrower runs and the small levels in LDS).
 template <class T, int COMP, int NR>
 __device__ __forceinline__ void smooth_vac_n(const Grid &g, T sigma, const VPtr<const T> &f, const VPtr<T> &x,
                                              uint32_t t, const VacRun *__restrict__ runs, uint32_t nruns) {
