@@ -223,21 +223,19 @@ __device__ __forceinline__ void apply_cut_row(const Grid &g, T sigma, const TW *
 }
 
 // entry i of the cut part: component i mod 3 of the 64 listed cells i / 3 of
-// a wave.  A row to a thread halves the loads that wait for one another: with
-// the three rows of a cell in a thread, each after the other's branch, the
-// cut part was the launch's tail (its workgroups last instead of first cost
-// 10%).
+// a wave, or (not split) the rows of the 64 listed cells i, one after the
+// other (see kApplySplit)
 template <class T, int KIND, class TX, class TW>
 __device__ __forceinline__ void apply_cut_part(const Grid &g, T sigma, const TW *__restrict__ W,
-                                               const int32_t *__restrict__ cut, int64_t ncut, uint32_t i,
+                                               const int32_t *__restrict__ cut, int64_t ncut, bool split, uint32_t i,
                                                uint32_t lane, const T *__restrict__ f, const TX *__restrict__ x,
                                                T *__restrict__ y) {
-    const uint32_t c = i / 3, comp = i - 3 * c, e = c * 64 + lane;
+    const uint32_t c = split ? i / 3 : i, comp = i - 3 * c, e = c * 64 + lane;
     if (e >= ncut) return;
     const uint32_t p = (uint32_t)cut[e];
-    if (comp == 0) apply_cut_row<T, KIND, 0, TX, TW>(g, sigma, W, ncut, e, p, f, x, y);
-    else if (comp == 1) apply_cut_row<T, KIND, 1, TX, TW>(g, sigma, W, ncut, e, p, f, x, y);
-    else apply_cut_row<T, KIND, 2, TX, TW>(g, sigma, W, ncut, e, p, f, x, y);
+    if (!split || comp == 0) apply_cut_row<T, KIND, 0, TX, TW>(g, sigma, W, ncut, e, p, f, x, y);
+    if (!split || comp == 1) apply_cut_row<T, KIND, 1, TX, TW>(g, sigma, W, ncut, e, p, f, x, y);
+    if (!split || comp == 2) apply_cut_row<T, KIND, 2, TX, TW>(g, sigma, W, ncut, e, p, f, x, y);
 }
 
 // the cut cells (their rows' table W), and the runs of the others or, without
@@ -249,7 +247,7 @@ struct ApplyArgs {
     const CellRun *cells;
     const uint8_t *flags;
     int64_t ncut;
-    uint32_t ncb, nruns;
+    uint32_t ncb, nruns, split;
 };
 
 // Block forms of apply, restriction and prolongation: wave q of a workgroup
@@ -274,7 +272,7 @@ k_apply_split(Grid g, T sigma, ApplyArgs<T> A, VPtr<const T> f, VPtr<const TX> x
     const int q = threadIdx.x >> 6;
     if (b < A.ncb) {
         const uint32_t L = (b % kXcd) * (A.ncb / kXcd) + b / kXcd;
-        apply_cut_part<T, KIND, TX, T>(g, sigma, A.W, A.cut, A.ncut, L, threadIdx.x & 63, f.p[q], x.p[q], y.p[q]);
+        apply_cut_part<T, KIND, TX, T>(g, sigma, A.W, A.cut, A.ncut, A.split, L, threadIdx.x & 63, f.p[q], x.p[q], y.p[q]);
         return;
     }
     const uint32_t bv = b - A.ncb, nvb = gridDim.x - A.ncb;
@@ -1842,7 +1840,7 @@ kb_step(const BJob *__restrict__ jobs, const int32_t *__restrict__ job_of) {
         }
     } else if (STEP == BS_RESID) {
         if (lb < J.ncut) {
-            apply_cut_part<T, AK_RESID, T, double>(J.g, J.sigma, J.w, J.cut, J.n, (uint32_t)(item >> 6),
+            apply_cut_part<T, AK_RESID, T, double>(J.g, J.sigma, J.w, J.cut, J.n, true, (uint32_t)(item >> 6),
                                                    (uint32_t)(item & 63), J.in, J.aux, J.out);
         } else {
             const uint32_t t = (uint32_t)(item - J.ncut * blockDim.x);
@@ -1955,8 +1953,21 @@ void launch_prolong_add(const Grid &gf, const Grid &gc, const T *coef_f, const T
     }
 
 namespace {
+// A single vector's whole-grid product or residual gives each listed cell's
+// rows to three threads below this many cut cells, and to one from there on:
+// a short list is bound by its dependent loads, a long one by memory, and one
+// thread's rows share their lines.  In us, split against not: residual FP32
+// 2.56 and 3.24 for 5,606 cut cells (32^3), 4.59 and 4.66 for 22,688 (64^3),
+// 5.61 and 5.48 for 28,730 (72^3), 9.07 and 8.60 for 41,906 (32 x 32 x 336
+// quarter), 21.3 and 19.5 for 99,127 (48 x 48 x 512); FP64 9.28 and 9.32 for
+// 28,730, 17.0 and 16.2 for 77,407 (16 x 128 x 256).  Several vectors share
+// the tables' lines between their waves: split at every length (FP64, three
+// vectors, 48 x 48 x 512: 86.6 and 89.8), as are the V-cycle's residuals,
+// most of whose levels are short.
+constexpr int64_t kApplySplit = 1 << 15;
+
 template <class T>
-ApplyArgs<T> apply_args(const Grid &g, const ClassList &cut, dim3 &grid) {
+ApplyArgs<T> apply_args(const Grid &g, const ClassList &cut, int nr, dim3 &grid) {
     if (cut.n > 0 && !cut_weights<T>(cut)) throw std::runtime_error("apply: cut-cell list without its row table");
     if (!cut.cells && !cut.flags) throw std::runtime_error("apply: neither runs nor class bytes");
     ApplyArgs<T> A;
@@ -1965,7 +1976,8 @@ ApplyArgs<T> apply_args(const Grid &g, const ClassList &cut, dim3 &grid) {
     A.cells = cut.cells;
     A.flags = cut.flags;
     A.ncut = cut.n;
-    A.ncb = (uint32_t)(ceil_div(3 * ceil_div(cut.n, 64), kXcd) * kXcd);
+    A.split = nr > 1 || cut.cells || cut.n < kApplySplit;
+    A.ncb = (uint32_t)(ceil_div((A.split ? 3 : 1) * ceil_div(cut.n, 64), kXcd) * kXcd);
     A.nruns = (uint32_t)cut.nruns;
     const int64_t items = cut.cells ? cut.nruns << kRunLog : (int64_t)g.nx * g.ny * g.nz;
     grid = dim3((unsigned)(A.ncb + ceil_div(ceil_div(items, 64), kXcd) * kXcd));
@@ -1978,7 +1990,7 @@ void launch_apply_b(const Grid &g, T sigma, int kind, int nr, const VPtr<const T
                     const VPtr<const T> &x, const VPtr<T> &y, hipStream_t s, ClassList cut) {
     if (kind != AK_M && kind != AK_RESID) throw std::runtime_error("block apply: M or residual only");
     dim3 grid;
-    const ApplyArgs<T> A = apply_args<T>(g, cut, grid);
+    const ApplyArgs<T> A = apply_args<T>(g, cut, nr, grid);
     if (grid.x == 0) return;   // no listed cell
     if (kind == AK_M)
         DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<T, AK_M, NR>), grid, dim3(64 * NR), 0, s, g, sigma, A, f, x, y))
@@ -1990,7 +2002,7 @@ void launch_apply_b(const Grid &g, T sigma, int kind, int nr, const VPtr<const T
 void launch_apply_m_f32in(const Grid &g, double sigma, int nr, const VPtr<const float> &x,
                          const VPtr<double> &y, hipStream_t s, ClassList cut) {
     dim3 grid;
-    const ApplyArgs<double> A = apply_args<double>(g, cut, grid);
+    const ApplyArgs<double> A = apply_args<double>(g, cut, nr, grid);
     if (grid.x == 0) return;   // no listed cell
     const VPtr<const double> f{};
     DM_NR_SWITCH(nr, hipLaunchKernelGGL((k_apply_split<double, AK_M, NR, float>), grid, dim3(64 * NR), 0, s, g, sigma, A,

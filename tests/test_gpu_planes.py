@@ -83,7 +83,7 @@ def test_rows_beside_planes(nh, axes):
             with dm.Operator(geom, nh, h, SIGMA, levels=2, krylov_basis_f32=basis32) as sop:
                 xs = [sop.face_tensor() for _ in fs]
                 infos = sop.solve_block([dev(f, nh, torch.float64) for f in fs], xs, mode=mode, rtol=1e-9)
-                w = np.sqrt(1.0 / vc.exts[0].mult)   # the norm of the library: half of a face in a plane is owned
+                w = np.sqrt(vc.exts[0].mult)   # the norm of the library: half of a face in a plane is owned
                 for f, x, info in zip(fs, xs, infos):
                     assert info["status"] == 0
                     res = (f - L.M @ back(x, nh)) * w
