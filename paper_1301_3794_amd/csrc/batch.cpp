@@ -46,7 +46,7 @@ LevelBufs bufs(dm_op *op, int l) {
 int64_t cells(const Grid &g) { return (int64_t)g.nx * g.ny * g.nz; }
 
 // whether member op smooths its level l in LDS when the whole depth does
-bool lds_at(dm_op *op, int l) { return lds_level(op->lv[l].g.P, op->lv[l].n_act_faces, sizeof(float)); }
+bool lds_at(dm_op *op, int l) { return lds_level(op->lv[l].g.P, op->lv[l].n_act_faces, sizeof(float), false); }
 
 // the fused V-cycle as a list of batched steps
 std::vector<HostStep> schedule(dm_batch *b) {

@@ -393,13 +393,27 @@ struct LdsRows {
 };
 constexpr int64_t kLdsBytes = 160 * 1024;
 // Whether a level of P padded elements per block and `faces` active faces runs
-// its sweeps this way (elem: bytes per value): its iterate fits, and its rows
-// are few enough that one CU's loads of their weights beat six launches per
-// sweep over the whole chip.  Per class update, a launch takes 2.7 us whatever
-// the size; one CU takes 1.5 us (FP32) or 2.3 us (FP64) for the 5,664 faces of
-// the 16^3 sphere, and 3.1 us (FP32) for the 15,400 of a 22 x 18 x 26 level.
-inline bool lds_level(int64_t P, int64_t faces, size_t elem) {
-    return 3 * P * (int64_t)elem <= kLdsBytes && faces <= (elem == 4 ? 10240 : 6656);
+// its sweeps this way (elem: bytes per value; planes: it has symmetry planes):
+// its iterate fits, and its rows are few enough that one CU's loads of their
+// weights beat six launches per sweep over the whole chip.  A launched class
+// takes 2.7 us whatever the size, 4.0 with planes (ghost images); one CU takes
+// 1.5 us (FP32) or 2.3 us (FP64) for the 5,664 faces of the 16^3 sphere, and
+// longer where most rows are cut.  V-cycles of two levels in us, the finer one
+// in LDS against launched:
+//   FP32           6,480 faces (16^3, ellipsoid) 62.7, 81.6; 9,552 (8 x 8 x 64,
+//                  9-cell, most rows cut) 76.3, 82.1; 13,512 (10 x 10 x 64,
+//                  9-cell) 103, 91
+//   FP32, planes   4,028 (6 x 6 x 64, 9-cell, nearly all rows cut) 108, 122;
+//                  7,807 (16 x 14 x 12, ellipsoid) 110, 120; 8,229 (8 x 8 x 84,
+//                  9-cell) 132, 128; 10,032 (18 x 16 x 12, ellipsoid) 121, 120
+//   FP64           6,480 80.9, 85.5; 7,480 (16 x 14 x 12) 79, 86; 9,552 115, 87
+//   FP64, planes   4,028 119, 126; 6,469 (16 x 14 x 10) 109, 126; 8,722
+//                  (6 x 6 x 96, 9-cell) 164, 132
+// (P is at most 6,826 in FP64, so its limit on faces is reached by box-like
+// levels only.)
+inline bool lds_level(int64_t P, int64_t faces, size_t elem, bool planes) {
+    const int64_t most = elem == 8 ? 6656 : planes ? 8000 : 10240;
+    return 3 * P * (int64_t)elem <= kLdsBytes && faces <= most;
 }
 
 // ---------------------------------------------------------------------------

@@ -436,7 +436,7 @@ void vcycle(dm_op *op, int l, const T *f, T *x, hipStream_t s) {
     Level &L = op->lv[l];
     const Grid &g = L.g;
     const T sig = (T)op->sigma;
-    const bool last = l == op->nlev() - 1, lds = !last && lds_level(g.P, L.n_act_faces, sizeof(T));
+    const bool last = l == op->nlev() - 1, lds = !last && lds_level(g.P, L.n_act_faces, sizeof(T), g.pmc != 0);
     // the iterate starts at zero: here on the finest level, on the coarser
     // ones in the restriction that forms their right-hand side
     if (l == 0 && !lds) launch_zero<T>(3 * g.P, x, s);
@@ -499,7 +499,7 @@ void vcycle_b(dm_op *op, int l, int nr, hipStream_t s) {
     const VPtr<T> F = slots(BPrec<T>::f(L), n3, nr), X = slots(BPrec<T>::x(L), n3, nr);
     // the iterate starts at zero: here on the finest level, on the coarser
     // ones in the restriction that forms their right-hand side
-    const bool last = l == op->nlev() - 1, lds = !last && lds_level(g.P, L.n_act_faces, sizeof(T));
+    const bool last = l == op->nlev() - 1, lds = !last && lds_level(g.P, L.n_act_faces, sizeof(T), g.pmc != 0);
     if (l == 0 && !lds) launch_zero<T>(nr * n3, BPrec<T>::x(L), s);
     if (last) {
         launch_coarse_solve_b<T>(op->nc, op->cinv, op->cidx, nr, as_const(F), X, s);
