@@ -360,16 +360,16 @@ int dm_apply(dm_op *op, int which, int prec, int level, const void *x, void *y, 
         fill_ghosts(L, prec, x, which == DM_APPLY_DT || which == DM_APPLY_S, s);
         switch (which) {
             case DM_APPLY_M:
-            case DM_APPLY_K: {
-                const int kind = which == DM_APPLY_M ? AK_M : AK_K;
                 if (prec == 64)
-                    launch_apply<double>(L.g, L.coef64, op->sigma, kind, nullptr, (const double *)x, (double *)y, s,
-                                         L.cut_cells());
+                    launch_apply<double>(L.g, op->sigma, AK_M, nullptr, (const double *)x, (double *)y, s, L.cut_cells());
                 else
-                    launch_apply<float>(L.g, L.coef32, (float)op->sigma, kind, nullptr, (const float *)x, (float *)y, s,
+                    launch_apply<float>(L.g, (float)op->sigma, AK_M, nullptr, (const float *)x, (float *)y, s,
                                         L.cut_cells());
                 break;
-            }
+            case DM_APPLY_K:
+                if (prec == 64) launch_apply_K<double>(L.g, L.coef64, (const double *)x, (double *)y, s);
+                else launch_apply_K<float>(L.g, L.coef32, (const float *)x, (float *)y, s);
+                break;
             case DM_APPLY_A:
                 if (prec == 64) launch_apply_A_t<double>(L.g, L.coef64, (const double *)x, (double *)y, s);
                 else launch_apply_A_t<float>(L.g, L.coef32, (const float *)x, (float *)y, s);
@@ -398,10 +398,10 @@ int dm_residual(dm_op *op, int prec, int level, const void *f, const void *x, vo
         const Level &L = op->lv[level];
         fill_ghosts(L, prec, x, false, s);
         if (prec == 64)
-            launch_apply<double>(L.g, L.coef64, op->sigma, AK_RESID, (const double *)f, (const double *)x, (double *)r, s,
+            launch_apply<double>(L.g, op->sigma, AK_RESID, (const double *)f, (const double *)x, (double *)r, s,
                                  L.cut_cells());
         else
-            launch_apply<float>(L.g, L.coef32, (float)op->sigma, AK_RESID, (const float *)f, (const float *)x, (float *)r, s,
+            launch_apply<float>(L.g, (float)op->sigma, AK_RESID, (const float *)f, (const float *)x, (float *)r, s,
                                 L.cut_cells());
         return DM_OK;
     });
@@ -976,8 +976,8 @@ static int time_kernel_impl(dm_op *op, int kernel, int prec, int level, int nrhs
                     case DM_KERNEL_APPLY:
                     case DM_KERNEL_RESIDUAL: {
                         const int kind = kernel == DM_KERNEL_APPLY ? AK_M : AK_RESID;
-                        if (prec == 64) launch_apply<double>(L.g, L.coef64, op->sigma, kind, (double *)f, (double *)x, (double *)y, s, L.cut_cells());
-                        else launch_apply<float>(L.g, L.coef32, (float)op->sigma, kind, (float *)f, (float *)x, (float *)y, s, L.cut_cells());
+                        if (prec == 64) launch_apply<double>(L.g, op->sigma, kind, (double *)f, (double *)x, (double *)y, s, L.cut_cells());
+                        else launch_apply<float>(L.g, (float)op->sigma, kind, (float *)f, (float *)x, (float *)y, s, L.cut_cells());
                         break;
                     }
                     case DM_KERNEL_SMOOTH:

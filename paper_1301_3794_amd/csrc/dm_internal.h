@@ -275,7 +275,7 @@ __host__ __device__ constexpr CutTerm cut_term(int comp, int t) {
 // ---------------------------------------------------------------------------
 // Kernel launchers (kernels.hip).  All take a stream; none synchronise.
 // ---------------------------------------------------------------------------
-enum ApplyKind { AK_M = 0, AK_K = 1, AK_RESID = 2 };
+enum ApplyKind { AK_M = 0, AK_RESID = 1 };
 
 // Block solves: up to kMaxRhs vectors of one level, passed by value as an
 // array of device pointers (any subset of a block, no stride assumed).
@@ -476,12 +476,13 @@ struct Span {
 };
 
 // the block forms of the V-cycle's kernels: nr (1..kMaxRhs) vectors per
-// launch, each coefficient loaded once for all of them
-// with a cut-cell list (cells with an active non-vacuum row) the launch runs
-// as two parts, the listed cells and the vacuum-only rest (M and residual)
+// launch, each coefficient loaded once for all of them.
+// Apply (AK_M) and residual (AK_RESID) run as two parts, the cells listed in
+// `cut` (those with an active non-vacuum row) and the vacuum-only rest by
+// runs or class bytes (Level::cut_cells_rows, Level::cut_cells).
 template <class T>
 void launch_apply_b(const Grid &g, T sigma, int kind, int nr, const VPtr<const T> &f,
-                    const VPtr<const T> &x, const VPtr<T> &y, hipStream_t s, ClassList cut = {});
+                    const VPtr<const T> &x, const VPtr<T> &y, hipStream_t s, const ClassList &cut);
 // one class update: `cl` holds the class's rows (Level::cut_list)
 template <class T>
 void launch_smooth_b(const Grid &g, T sigma, int comp, int nr, const VPtr<const T> &f, const VPtr<T> &x,
@@ -507,8 +508,11 @@ void launch_coarse_solve_b(int n, const double *inv, const int64_t *idx, int nr,
                            const VPtr<T> &x, hipStream_t s);
 
 template <class T>
-void launch_apply(const Grid &g, const T *coef, T sigma, int kind, const T *f, const T *x, T *y,
-                  hipStream_t s, ClassList cut = {});
+void launch_apply(const Grid &g, T sigma, int kind, const T *f, const T *x, T *y, hipStream_t s,
+                  const ClassList &cut);
+// y = K x, whose rows keep the cross terms that cancel in M's vacuum rows
+template <class T>
+void launch_apply_K(const Grid &g, const T *coef, const T *x, T *y, hipStream_t s);
 template <class T>
 void launch_smooth(const Grid &g, T sigma, int comp, const T *f, T *x, hipStream_t s, const ClassList &cl);
 template <class T>
@@ -583,7 +587,7 @@ void launch_axpy(int64_t n, double a, const double *x, double *y, hipStream_t s)
 // cut-cell list of the level (the split form), and with its rows leaves y
 // untouched on the other rows
 void launch_apply_m_f32in(const Grid &g, double sigma, int nr, const VPtr<const float> &x,
-                          const VPtr<double> &y, hipStream_t s, ClassList cut);
+                          const VPtr<double> &y, hipStream_t s, const ClassList &cut);
 void launch_axpby(int64_t n, double a, const double *x, double b, double *y, hipStream_t s);
 void launch_scale(int64_t n, double a, double *x, hipStream_t s);
 template <class T>

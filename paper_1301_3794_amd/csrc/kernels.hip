@@ -1901,12 +1901,13 @@ inline dim3 flat_grid(int64_t n) {
 // launchers
 // ---------------------------------------------------------------------------
 template <class T>
-void launch_apply(const Grid &g, const T *coef, T sigma, int kind, const T *f, const T *x, T *y,
-                  hipStream_t s, ClassList cut) {
-    if (kind == AK_M || kind == AK_RESID) {
-        launch_apply_b<T>(g, sigma, kind, 1, vptr1(f), vptr1(x), vptr1(y), s, cut);
-        return;
-    }
+void launch_apply(const Grid &g, T sigma, int kind, const T *f, const T *x, T *y, hipStream_t s,
+                  const ClassList &cut) {
+    launch_apply_b<T>(g, sigma, kind, 1, vptr1(f), vptr1(x), vptr1(y), s, cut);
+}
+
+template <class T>
+void launch_apply_K(const Grid &g, const T *coef, const T *x, T *y, hipStream_t s) {
     const int64_t n = (int64_t)g.nx * g.ny * g.nz;
     hipLaunchKernelGGL((k_apply_K<T>), xcd_grid(n), dim3(kThreads), 0, s, g, coefs_of(coef, g.P), x, y);
 }
@@ -1987,7 +1988,7 @@ ApplyArgs<T> apply_args(const Grid &g, const ClassList &cut, int nr, dim3 &grid)
 
 template <class T>
 void launch_apply_b(const Grid &g, T sigma, int kind, int nr, const VPtr<const T> &f,
-                    const VPtr<const T> &x, const VPtr<T> &y, hipStream_t s, ClassList cut) {
+                    const VPtr<const T> &x, const VPtr<T> &y, hipStream_t s, const ClassList &cut) {
     if (kind != AK_M && kind != AK_RESID) throw std::runtime_error("block apply: M or residual only");
     dim3 grid;
     const ApplyArgs<T> A = apply_args<T>(g, cut, nr, grid);
@@ -2000,7 +2001,7 @@ void launch_apply_b(const Grid &g, T sigma, int kind, int nr, const VPtr<const T
 }
 
 void launch_apply_m_f32in(const Grid &g, double sigma, int nr, const VPtr<const float> &x,
-                         const VPtr<double> &y, hipStream_t s, ClassList cut) {
+                         const VPtr<double> &y, hipStream_t s, const ClassList &cut) {
     dim3 grid;
     const ApplyArgs<double> A = apply_args<double>(g, cut, nr, grid);
     if (grid.x == 0) return;   // no listed cell
@@ -2631,7 +2632,7 @@ template void launch_add_scaled_a<float>(int64_t, const float *, const float *, 
 // explicit instantiations
 #define DM_BLOCK_INST(T)                                                                                   \
     template void launch_apply_b<T>(const Grid &, T, int, int, const VPtr<const T> &,                            \
-                                    const VPtr<const T> &, const VPtr<T> &, hipStream_t, ClassList);              \
+                                    const VPtr<const T> &, const VPtr<T> &, hipStream_t, const ClassList &);      \
     template void launch_smooth_b<T>(const Grid &, T, int, int, const VPtr<const T> &, const VPtr<T> &,          \
                                      hipStream_t, const ClassList &);                                             \
     template void launch_sweeps_lds<T>(const Grid &, T, const LdsRows &, int, int, int, int,                     \
@@ -2646,10 +2647,12 @@ template void launch_add_scaled_a<float>(int64_t, const float *, const float *, 
 DM_BLOCK_INST(double)
 DM_BLOCK_INST(float)
 #undef DM_BLOCK_INST
-template void launch_apply<double>(const Grid &, const double *, double, int, const double *,
-                                   const double *, double *, hipStream_t, ClassList);
-template void launch_apply<float>(const Grid &, const float *, float, int, const float *,
-                                  const float *, float *, hipStream_t, ClassList);
+template void launch_apply<double>(const Grid &, double, int, const double *, const double *, double *, hipStream_t,
+                                   const ClassList &);
+template void launch_apply<float>(const Grid &, float, int, const float *, const float *, float *, hipStream_t,
+                                  const ClassList &);
+template void launch_apply_K<double>(const Grid &, const double *, const double *, double *, hipStream_t);
+template void launch_apply_K<float>(const Grid &, const float *, const float *, float *, hipStream_t);
 template void launch_apply_A_t<float>(const Grid &, const float *, const float *, float *, hipStream_t);
 template void launch_apply_A_t<double>(const Grid &, const double *, const double *, double *, hipStream_t);
 template void launch_smooth<double>(const Grid &, double, int, const double *, double *, hipStream_t,

@@ -199,7 +199,7 @@ int fgmres(dm_op *op, int mode, const double *f, double *x, double rtol, int max
     bool conv = false;
     while (true) {
         if (total == 0) launch_copy(n, f, V, s);
-        else launch_apply<double>(L.g, L.coef64, op->sigma, AK_RESID, f, x, V, s, L.cut_cells());
+        else launch_apply<double>(L.g, op->sigma, AK_RESID, f, x, V, s, L.cut_cells());
         const double beta = std::sqrt(dot1(op, V, V, nullptr, n, s, sp));
         if (!std::isfinite(beta)) throw DmError{DM_ENAN, "FGMRES residual is not finite"};
         rel = beta / bnorm;
@@ -218,7 +218,7 @@ int fgmres(dm_op *op, int mode, const double *f, double *x, double rtol, int max
         for (; j < m;) {
             double *uj = V + (int64_t)j * n, *zj = Z + (int64_t)j * n, *w = V + (int64_t)(j + 1) * n;
             precondition(op, mode, uj, zj, s, &learned_rejections);
-            launch_apply<double>(L.g, L.coef64, op->sigma, AK_M, nullptr, zj, w, s, L.cut_cells());
+            launch_apply<double>(L.g, op->sigma, AK_M, nullptr, zj, w, s, L.cut_cells());
             // (1) d = U^T w, then (2) w -= U c with c_i = sc_i^2 d_i formed on
             // the device, fused with d2 = U^T w and |w|^2: one host sync
             launch_mdot(j + 1, V, n, w, nullptr, n, op->part, op->dres, s, sp);
@@ -306,7 +306,7 @@ int pcg_work(dm_op *op, const double *f, double *x, double rtol, int maxit, dm_s
     double rel = 1.0;
     bool conv = false;
     while (it < maxit) {
-        launch_apply<double>(L.g, L.coef64, op->sigma, AK_M, nullptr, p, q, s, L.cut_cells());
+        launch_apply<double>(L.g, op->sigma, AK_M, nullptr, p, q, s, L.cut_cells());
         const double pq = dot1(op, p, q, op->wface, n, s);
         if (!(pq > 0.0)) throw DmError{pq == pq ? DM_EBREAKDOWN : DM_ENAN,
                                        "PCG: operator not positive definite at this shift"};
@@ -326,7 +326,7 @@ int pcg_work(dm_op *op, const double *f, double *x, double rtol, int maxit, dm_s
         rz = rz2;
     }
     // true residual
-    launch_apply<double>(L.g, L.coef64, op->sigma, AK_RESID, f, x, r, s, L.cut_cells());
+    launch_apply<double>(L.g, op->sigma, AK_RESID, f, x, r, s, L.cut_cells());
     rel = std::sqrt(dot1(op, r, r, op->wface, n, s)) / bnorm;
     if (info) {
         info->iterations = it;
@@ -458,7 +458,7 @@ void vcycle(dm_op *op, int l, const T *f, T *x, hipStream_t s) {
     T *r = Prec<T>::r(L);
     // the residual and the transfers visit only the grid rows holding an
     // active face: what they write stays zero on the others
-    launch_apply<T>(g, c, sig, AK_RESID, f, x, r, s, L.cut_cells_rows());
+    launch_apply<T>(g, sig, AK_RESID, f, x, r, s, L.cut_cells_rows());
     Level &C = op->lv[l + 1];
     T *fc = Prec<T>::f(C), *xc = Prec<T>::x(C);
     const T *cc = Prec<T>::coef(C);
@@ -1356,7 +1356,7 @@ int eigs(dm_op *op, int k, double tol, uint64_t seed, const dm_eig_options &opt,
     std::vector<double> GK((size_t)cap * cap, 0.0);
     auto Gat = [&](int r, int c) -> double & { return GK[(size_t)r * cap + c]; };
     auto add_gk = [&](int q) {
-        launch_apply<double>(L.g, L.coef64, 0.0, AK_K, nullptr, V + (size_t)q * n, t2, s);
+        launch_apply_K<double>(L.g, L.coef64, V + (size_t)q * n, t2, s);
         dots(op, q + 1, V, n, t2, wk, n, s, vsp);
         for (int i = 0; i <= q; ++i) Gat(i, q) = Gat(q, i) = op->hres[i];
     };
@@ -1479,7 +1479,7 @@ int eigs(dm_op *op, int k, double tol, uint64_t seed, const dm_eig_options &opt,
             }
             // V^T K V: the block's K images against the whole basis, one pass
             for (int c = 0; c < b; ++c)
-                launch_apply<double>(L.g, L.coef64, 0.0, AK_K, nullptr, Vn + (size_t)c * n, op->eg_KV + (size_t)c * n,
+                launch_apply_K<double>(L.g, L.coef64, Vn + (size_t)c * n, op->eg_KV + (size_t)c * n,
                                      s);
             multi_dots(cur + b, op->eg_KV, b, wk);
             for (int c = 0; c < b; ++c)
@@ -1541,7 +1541,7 @@ int eigs(dm_op *op, int k, double tol, uint64_t seed, const dm_eig_options &opt,
         std::vector<double> yk(std::max(mm, nb));
         combine(nb, k, RB, [&](int r, int i) { return Z[(size_t)r * nb + wanted[i]]; }, vsp);
         for (int i = 0; i < k; ++i) {
-            launch_apply<double>(L.g, L.coef64, 0.0, AK_K, nullptr, RB + (size_t)i * n, RK + (size_t)i * n, s);
+            launch_apply_K<double>(L.g, L.coef64, RB + (size_t)i * n, RK + (size_t)i * n, s);
             launch_apply_A(L.g, L.coef64, RB + (size_t)i * n, RA + (size_t)i * n, s);
             launch_mdot(1, RB + (size_t)i * n, 0, RK + (size_t)i * n, wk, n, op->part, op->dres + 2 * i, s, vsp);
             launch_mdot(1, RB + (size_t)i * n, 0, RB + (size_t)i * n, a, n, op->part, op->dres + 2 * i + 1, s, vsp);
