@@ -1601,8 +1601,6 @@ k_maxpy_f32(int nv, const float *__restrict__ V, int64_t ld, const double *__res
 //   w' = w - sum_i c_i V_i      (written back to w)
 //   part rows 0..nv-1: V_i . w', row nv: |w'|^2
 // One read of the basis (held in registers) serves the update and the dots.
-constexpr int kFuseMax = 32;
-
 // REREAD: the basis values are loaded a second time for the dot products
 // instead of being held in registers (more vectors than registers allow; the
 // second load is served by the L2 or the Infinity Cache).  Measured: for 32

@@ -328,7 +328,6 @@ void build_hierarchy(dm_op *op, const double *user_frac) {
         int64_t faces = 0;
         for (const uint8_t f : fl) faces += (f & 1) + ((f >> 1) & 1) + ((f >> 2) & 1);
         const bool small = lds_level(P, faces, sizeof(float), L.g.pmc != 0);
-        const int nxh = (L.g.nx + 1) >> 1;
         // the lists, each built by a task of its own: a component's cut rows, a
         // class's runs (and its vacuum rows one by one on an LDS level), the
         // cells with a cut row, the grid rows holding an active cell or face

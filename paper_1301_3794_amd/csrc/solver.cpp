@@ -776,7 +776,6 @@ int project_block(dm_op *op, int nr, const double *const *b, double *const *out,
                        Q = slots(op->pjb_q, P, nr), R = slots(L.bsf, P, nr), Z = slots(L.bsx, P, nr);
     VPtr<const double> B{};
     for (int q = 0; q < nr; ++q) B.p[q] = b[q];
-    auto dres = [&](int q) { return op->bk_dres + (int64_t)q * kMaxDots; };
     auto hres = [&](int q) { return op->bk_hres + (int64_t)q * kMaxDots; };
     auto fetch = [&]() {
         DM_HIP(hipMemcpyAsync(op->bk_hres, op->bk_dres, (size_t)nr * kMaxDots * sizeof(double),
