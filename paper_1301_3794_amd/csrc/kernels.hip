@@ -1,7 +1,9 @@
 // HIP kernels of the Dey--Mittra eigensolver (gfx950, wave64).
 //
-// Stencil kernels map one thread to one cell (i,j,k); the cell owns its three
-// low faces b_x[i,j,k], b_y[i,j,k], b_z[i,j,k].  Blocks are remapped so that
+// A cell (i,j,k) owns its three low faces b_x[i,j,k], b_y[i,j,k], b_z[i,j,k].
+// Transfers, K and the scalar kernels map one thread to one cell; the smoother
+// and M take listed cut rows and, beside them, runs of vacuum rows or, over
+// the whole grid, cells by class byte.  Blocks are remapped so that
 // each of the 8 XCDs (which receive workgroups round-robin) works on one
 // contiguous slab of the grid and keeps its stencil neighbours in its own L2.
 // The stencil path is memory bound: no MFMA here.
@@ -258,13 +260,13 @@ struct ApplyArgs {
 // vectors to neighbouring lanes split every load of a wave over NR arrays.)
 
 // The block apply in two parts, as the smoother's class updates: the first
-// ncb workgroups (a multiple of 8) take the cut-cell list (full body), the
+// ncb workgroups (a multiple of 8) take the cut-cell list, the
 // rest the other cells, those of the listed runs or, without a list, every
 // cell of the grid by its class byte; wave q of a workgroup takes vector q of
 // 64 entries in either part.  (A run's record is 16 bytes for each lane of
-// the load, a class byte one: over the whole grid the runs were 1.5 to 3%
-// slower, FP64 at 104 x 88 x 80 and 128 x 128 x 96; they pay where they leave
-// rows out.)
+// the load, a class byte one: over the whole grid runs of 16 lanes were 1.5 to
+// 3% slower, FP64 at 104 x 88 x 80 and 128 x 128 x 96; runs pay where they
+// leave rows out.)
 template <class T, int KIND, int NR, class TX = T>
 __global__ void __launch_bounds__(kThreads)
 k_apply_split(Grid g, T sigma, ApplyArgs<T> A, VPtr<const T> f, VPtr<const TX> x, VPtr<T> y) {
