@@ -100,9 +100,9 @@ VCYCLE_BYTES_PER_CELL = 359.0 * 8.0 / 7.0
 # 256 MiB device copy): bytes per sweep of the six class launches, per
 # workload and block size, for the kernels as they are now (None where no
 # counter run of the current kernels exists).  Summaries under profiles/.
-SWEEP_TRAFFIC_BYTES = {"sphere128_3": 378987202,   # profiles/block_sweep_sphere128_hbm_traffic.md
-                       "ninecell_1": 787306872,    # profiles/sweep_ninecell_96x96x1024_hbm_traffic.md
-                       "ninecell_2": 1521106074}
+SWEEP_TRAFFIC_BYTES = {"sphere128_3": 385660108,   # profiles/block_sweep_sphere128_hbm_traffic.md
+                       "ninecell_1": 793442748,    # profiles/sweep_ninecell_96x96x1024_hbm_traffic.md
+                       "ninecell_2": 1525503787}
 
 
 def log(msg):
