@@ -8,7 +8,7 @@
 // in their order; only the launches are shared.  Its values do not depend on
 // the other members (LDS sweeps and launches round alike), and differ from
 // those of its own FP32 V-cycle by rounding: the cut rows are summed in FP64
-// from FP64 tables here.  The fused sequence is recorded in one HIP graph,
+// here, from centre weights in FP64.  The fused sequence is recorded in one HIP graph,
 // for the block size (64, 128 or 256 threads) that the autotuner timed fastest.
 //
 // dm_batch_eigs runs every member's eigensolve on its own host thread and
@@ -71,8 +71,9 @@ std::vector<HostStep> schedule(dm_batch *b) {
     // the rows of a class update or of the residual
     auto rows = [&](BJob &J, const ClassList &cl) {
         J.cut = cl.idx;
-        J.w = cl.w64;
-        J.s = static_cast<double *>(cl.s);
+        J.w = cl.w32;
+        J.w0 = cl.w64;
+        J.s = static_cast<float *>(cl.s);
         J.runs = cl.runs;
         J.cells = cl.cells;
         J.n = cl.n;

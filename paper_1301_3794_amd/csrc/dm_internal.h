@@ -432,11 +432,12 @@ struct BJob {
     const double *inv;    // coarsest dense inverse (coarse)
     const int64_t *idx;   // its active-face index (coarse)
     // smooth and residual: the class's or the level's rows (ClassList); the
-    // cut part, with its FP64 table and sums, takes the job's first ncut
-    // blocks, the runs the others
+    // cut part takes the job's first ncut blocks, the runs the others; w0 is
+    // the FP64 table, for its centre weights
     const int32_t *cut;
-    const double *w;
-    double *s;
+    const float *w;
+    const double *w0;
+    float *s;
     const VacRun *runs;
     const CellRun *cells;
     int64_t n, ncut;

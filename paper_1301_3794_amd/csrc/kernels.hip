@@ -111,6 +111,15 @@ __device__ inline T vac_row_m(const TX *C, int64_t p, int64_t dy, int64_t dz, T 
     return fused(ih2, vac_row<T, TX>(C, p, dy, dz), -(sigma * xp));
 }
 
+// A table of cut rows as the kernels take it (kCutW x n, term-major; see
+// cut_term): the weights in the vectors' type, the centre ones (w0, the term 0
+// of a table of the same layout) in the type of the sums.
+template <class T, class TA>
+struct CutTab {
+    const T *w;
+    const TA *w0;
+};
+
 // the centre terms of a tabulated row: w_0 x_p - sigma a x_p
 template <class T>
 __device__ inline T centre_terms(T w0, T sigma, T a, T xp) {
@@ -202,24 +211,25 @@ k_apply_K(Grid g, Coefs<T> c, const T *__restrict__ x, T *__restrict__ y) {
 }
 
 // M x or f - M x at the face of component COMP of listed cell e (padded index
-// p) from its tabulated row in W (3 x kCutW x ncut; see cut_term), summed in
-// the table's type; an inactive face (a = 0) gets 0
-template <class T, int KIND, int COMP, class TX, class TW>
-__device__ __forceinline__ void apply_cut_row(const Grid &g, T sigma, const TW *__restrict__ W, int64_t ncut,
+// p) from its tabulated row in W (3 x kCutW x ncut; see CutTab), summed in TA;
+// an inactive face (a = 0) gets 0
+template <class T, int KIND, int COMP, class TX, class TA>
+__device__ __forceinline__ void apply_cut_row(const Grid &g, T sigma, const CutTab<T, TA> &W, int64_t ncut,
                                               int64_t e, uint32_t p, const T *__restrict__ f,
                                               const TX *__restrict__ x, T *__restrict__ y) {
     const int64_t P = g.P, dy = g.sy, dz = g.sz;
-    const TW *Wc = W + (int64_t)COMP * kCutW * ncut;
-    const TW a = Wc[kCutTerms * ncut + e];
+    const int64_t off = (int64_t)COMP * kCutW * ncut;
+    const T *__restrict__ Wc = W.w + off;
+    const T a = Wc[kCutTerms * ncut + e];
     T v = T(0);
-    if (a != TW(0)) {
-        TW row = centre_terms(Wc[e], TW(sigma), a, TW(x[COMP * P + p]));
+    if (a != T(0)) {
+        TA row = centre_terms((W.w0 + off)[e], TA(sigma), TA(a), TA(x[COMP * P + p]));
 #pragma unroll
         for (int t = 1; t < kCutTerms; ++t) {
             const CutTerm ct = cut_term(COMP, t);
-            row += Wc[t * ncut + e] * TW(x[ct.comp * P + p + ct.di + ct.dj * dy + ct.dk * dz]);
+            row += TA(Wc[t * ncut + e]) * TA(x[ct.comp * P + p + ct.di + ct.dj * dy + ct.dk * dz]);
         }
-        v = T(KIND == AK_RESID ? TW(f[COMP * P + p]) - row : row);
+        v = T(KIND == AK_RESID ? TA(f[COMP * P + p]) - row : row);
     }
     put_face_at<T>(g, y + COMP * P, COMP, p, v);
 }
@@ -227,17 +237,17 @@ __device__ __forceinline__ void apply_cut_row(const Grid &g, T sigma, const TW *
 // entry i of the cut part: component i mod 3 of the 64 listed cells i / 3 of
 // a wave, or (not split) the rows of the 64 listed cells i, one after the
 // other (see kApplySplit)
-template <class T, int KIND, class TX, class TW>
-__device__ __forceinline__ void apply_cut_part(const Grid &g, T sigma, const TW *__restrict__ W,
+template <class T, int KIND, class TX, class TA>
+__device__ __forceinline__ void apply_cut_part(const Grid &g, T sigma, const CutTab<T, TA> &W,
                                                const int32_t *__restrict__ cut, int64_t ncut, bool split, uint32_t i,
                                                uint32_t lane, const T *__restrict__ f, const TX *__restrict__ x,
                                                T *__restrict__ y) {
     const uint32_t c = split ? i / 3 : i, comp = i - 3 * c, e = c * 64 + lane;
     if (e >= ncut) return;
     const uint32_t p = (uint32_t)cut[e];
-    if (!split || comp == 0) apply_cut_row<T, KIND, 0, TX, TW>(g, sigma, W, ncut, e, p, f, x, y);
-    if (!split || comp == 1) apply_cut_row<T, KIND, 1, TX, TW>(g, sigma, W, ncut, e, p, f, x, y);
-    if (!split || comp == 2) apply_cut_row<T, KIND, 2, TX, TW>(g, sigma, W, ncut, e, p, f, x, y);
+    if (!split || comp == 0) apply_cut_row<T, KIND, 0, TX, TA>(g, sigma, W, ncut, e, p, f, x, y);
+    if (!split || comp == 1) apply_cut_row<T, KIND, 1, TX, TA>(g, sigma, W, ncut, e, p, f, x, y);
+    if (!split || comp == 2) apply_cut_row<T, KIND, 2, TX, TA>(g, sigma, W, ncut, e, p, f, x, y);
 }
 
 // the cut cells (their rows' table W), and the runs of the others or, without
@@ -274,7 +284,7 @@ k_apply_split(Grid g, T sigma, ApplyArgs<T> A, VPtr<const T> f, VPtr<const TX> x
     const int q = threadIdx.x >> 6;
     if (b < A.ncb) {
         const uint32_t L = (b % kXcd) * (A.ncb / kXcd) + b / kXcd;
-        apply_cut_part<T, KIND, TX, T>(g, sigma, A.W, A.cut, A.ncut, A.split, L, threadIdx.x & 63, f.p[q], x.p[q], y.p[q]);
+        apply_cut_part<T, KIND, TX, T>(g, sigma, CutTab<T, T>{A.W, A.W}, A.cut, A.ncut, A.split, L, threadIdx.x & 63, f.p[q], x.p[q], y.p[q]);
         return;
     }
     const uint32_t bv = b - A.ncb, nvb = gridDim.x - A.ncb;
@@ -353,21 +363,22 @@ __device__ __forceinline__ void smooth_vac_n(const Grid &g, T sigma, const VPtr<
 }
 
 // entry e of the component's cut list (n entries, the colour in the sign bit)
-// from its tabulated row W (kCutW x n, term-major; see cut_term), for the
-// update of colour `colour` paired as `pair` says (see ClassList): the row is
+// from its tabulated row (kCutW x n; see CutTab), for the update of colour
+// `colour` paired as `pair` says (see ClassList): the row is
 // -sigma a x_f + (own-component terms) + (cross-component terms), the latter
 // summed first, inline or taken from S (n per vector, vector q0 + q).  The
 // weights are loaded once for the NR vectors, those that every entry takes
-// before the index they do not depend on; the sums are in the table's type.
-// (The list keeps both colours in
-// index order: sorted by colour, the first update of a pair walked the
+// before the index they do not depend on; the sums are in TA, the cross sums
+// rounded to T whether they are stored or not.  (The list keeps both colours
+// in index order: sorted by colour, the first update of a pair walked the
 // surface twice, 16.5 -> 21.5 us per launch at 128^3 for 3 vectors.)
-template <class T, int COMP, int NR, class TW = T>
+template <class T, int COMP, int NR, class TA>
 __device__ __forceinline__ void smooth_cut_n(const Grid &g, T sigma, const int32_t *__restrict__ cut, int64_t n,
-                                             int colour, const TW *__restrict__ W, int pair, TW *__restrict__ S,
+                                             int colour, const CutTab<T, TA> &tab, int pair, T *__restrict__ S,
                                              int q0, const VPtr<const T> &f, const VPtr<T> &x, uint32_t e) {
     const int64_t P = g.P, dy = g.sy, dz = g.sz;
-    TW w[kCutTerms], cross[NR];
+    const T *__restrict__ W = tab.w;
+    T w[kCutTerms], cross[NR];
     const int32_t ce = cut[e];
     if (pair != kPairSecond) {
 #pragma unroll
@@ -384,13 +395,13 @@ __device__ __forceinline__ void smooth_cut_n(const Grid &g, T sigma, const int32
 #pragma unroll
         for (int q = 0; q < NR; ++q) {
             const T *X = x.p[q];
-            TW c = TW(0);
+            TA c = TA(0);
 #pragma unroll
             for (int t = kCutOwn; t < kCutTerms; ++t) {
                 const CutTerm ct = cut_term(COMP, t);
-                c += w[t] * TW((X + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz))[p]);
+                c += TA(w[t]) * TA((X + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz))[p]);
             }
-            cross[q] = c;
+            cross[q] = T(c);
         }
         if (!mine) {
 #pragma unroll
@@ -398,23 +409,24 @@ __device__ __forceinline__ void smooth_cut_n(const Grid &g, T sigma, const int32
             return;
         }
     }
+    const TA w0 = tab.w0[e];
 #pragma unroll
-    for (int t = 0; t < kCutOwn; ++t) w[t] = W[t * n + e];
-    const TW a = W[kCutTerms * n + e];
-    const TW d = fused(-TW(sigma), a, W[(kCutTerms + 1) * n + e]);
+    for (int t = 1; t < kCutOwn; ++t) w[t] = W[t * n + e];
+    const T a = W[kCutTerms * n + e];
+    const T d = fused(-sigma, a, W[(kCutTerms + 1) * n + e]);
     T nv[NR];
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
         const T *X = x.p[q];
         const T xs = (X + COMP * P)[p];
-        TW row = centre_terms(w[0], TW(sigma), a, TW(xs));
+        TA row = centre_terms(w0, TA(sigma), TA(a), TA(xs));
 #pragma unroll
         for (int t = 1; t < kCutOwn; ++t) {
             const CutTerm ct = cut_term(COMP, t);
-            row += w[t] * TW((X + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz))[p]);
+            row += TA(w[t]) * TA((X + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz))[p]);
         }
-        row += cross[q];
-        nv[q] = xs + T(TW((f.p[q] + COMP * P)[p]) - row) / T(d);
+        row += TA(cross[q]);
+        nv[q] = xs + T(TA((f.p[q] + COMP * P)[p]) - row) / d;
     }
 #pragma unroll
     for (int q = 0; q < NR; ++q) put_face_at<T>(g, x.p[q] + COMP * P, COMP, p, nv[q]);
@@ -445,14 +457,15 @@ k_smooth_split(Grid g, T sigma, SmoothArgs<T> A, VPtr<const T> f, VPtr<T> x) {
     const uint32_t b = blockIdx.x;
     if (b < A.ncb) {
         const uint32_t L = (b % kXcd) * (A.ncb / kXcd) + b / kXcd;
+        const CutTab<T, T> W{A.W, A.W};
         if (!A.wave_split) {
             const uint32_t e = L * kThreads + threadIdx.x;
-            if (e < A.n) smooth_cut_n<T, COMP, NR>(g, sigma, A.cut, A.n, A.colour, A.W, A.pair, A.S, 0, f, x, e);
+            if (e < A.n) smooth_cut_n<T, COMP, NR, T>(g, sigma, A.cut, A.n, A.colour, W, A.pair, A.S, 0, f, x, e);
         } else {
             const int q = threadIdx.x >> 6;
             const uint32_t e = L * 64 + (threadIdx.x & 63);
             if (q < NR && e < A.n)
-                smooth_cut_n<T, COMP, 1>(g, sigma, A.cut, A.n, A.colour, A.W, A.pair, A.S, q, vptr1(f.p[q]),
+                smooth_cut_n<T, COMP, 1, T>(g, sigma, A.cut, A.n, A.colour, W, A.pair, A.S, q, vptr1(f.p[q]),
                                          vptr1(x.p[q]), e);
         }
     } else {
@@ -476,9 +489,10 @@ k_smooth_split(Grid g, T sigma, SmoothArgs<T> A, VPtr<const T> f, VPtr<T> x) {
 constexpr int kLdsThreads = 1024;
 
 // the tabulated row of a thread's entry of a class
-template <class TW>
+template <class T, class TA>
 struct LdsRow {
-    TW w[kCutTerms], a, d;
+    TA w0;
+    T w[kCutTerms], a, d;   // w[0] unused
 };
 
 // A workgroup barrier that orders LDS accesses only: loads from global memory
@@ -490,27 +504,27 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // the update of one row of component COMP in LDS (smooth_cut_n, smooth_vac_n)
-template <class T, int COMP, bool PMC, class TW>
-__device__ __forceinline__ void lds_update(const Grid &g, T sigma, T ih2, T dvac, T *xs, const LdsRow<TW> &r, bool cut,
+template <class T, int COMP, bool PMC, class TA>
+__device__ __forceinline__ void lds_update(const Grid &g, T sigma, T ih2, T dvac, T *xs, const LdsRow<T, TA> &r, bool cut,
                                            uint32_t p, T fv) {
     const int P = (int)g.P, dy = g.sy, dz = (int)g.sz;
     T *xc = xs + COMP * P;
     const T xp = xc[p];
     T nv;
     if (cut) {
-        TW cross = TW(0), row = centre_terms(r.w[0], TW(sigma), r.a, TW(xp));
+        TA cross = TA(0), row = centre_terms(r.w0, TA(sigma), TA(r.a), TA(xp));
 #pragma unroll
         for (int u = kCutOwn; u < kCutTerms; ++u) {
             const CutTerm ct = cut_term(COMP, u);
-            cross += r.w[u] * TW(xs[(int)p + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz)]);
+            cross += TA(r.w[u]) * TA(xs[(int)p + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz)]);
         }
 #pragma unroll
         for (int u = 1; u < kCutOwn; ++u) {
             const CutTerm ct = cut_term(COMP, u);
-            row += r.w[u] * TW(xs[(int)p + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz)]);
+            row += TA(r.w[u]) * TA(xs[(int)p + (ct.comp * P + ct.di + ct.dj * dy + ct.dk * dz)]);
         }
-        row += cross;
-        nv = xp + T(TW(fv) - row) / T(fused(-TW(sigma), r.a, r.d));
+        row += TA(T(cross));
+        nv = xp + T(TA(fv) - row) / fused(-sigma, r.a, r.d);
     } else {
         nv = xp + (fv - vac_row_m<T>(xc, p, dy, dz, ih2, sigma, xp)) / dvac;
     }
@@ -518,8 +532,8 @@ __device__ __forceinline__ void lds_update(const Grid &g, T sigma, T ih2, T dvac
     else xc[p] = nv;
 }
 
-template <class T, bool PMC, class TW>
-__device__ __forceinline__ void sweeps_lds_body(const Grid &g, T sigma, const LdsRows &R, const TW *__restrict__ W,
+template <class T, bool PMC, class TA>
+__device__ __forceinline__ void sweeps_lds_body(const Grid &g, T sigma, const LdsRows &R, const CutTab<T, TA> &W,
                                                 int sweeps, int reverse, int zero, const T *__restrict__ f,
                                                 T *__restrict__ x, T *xs) {
     const int P = (int)g.P, n3 = 3 * P;
@@ -531,11 +545,13 @@ __device__ __forceinline__ void sweeps_lds_body(const Grid &g, T sigma, const Ld
         if (t >= nc + R.vac_off[q + 1] - v0) return 0u;
         return (uint32_t)(t < nc ? R.cut[c0 + t] : R.vac[v0 + t - nc]) & 0x7fffffffu;
     };
-    auto load_row = [&](LdsRow<TW> &r, int q, int t) __attribute__((always_inline)) {
+    auto load_row = [&](LdsRow<T, TA> &r, int q, int t) __attribute__((always_inline)) {
         const int base = R.cut_off[q & ~1], n = R.cut_off[(q & ~1) + 2] - base;
-        const TW *w = W + (int64_t)kCutW * base + (R.cut_off[q] - base);
+        const int64_t off = (int64_t)kCutW * base + (R.cut_off[q] - base);
+        const T *w = W.w + off;
+        r.w0 = (W.w0 + off)[t];
 #pragma unroll
-        for (int u = 0; u < kCutTerms; ++u) r.w[u] = (w + u * n)[t];
+        for (int u = 1; u < kCutTerms; ++u) r.w[u] = (w + u * n)[t];
         r.a = (w + kCutTerms * n)[t];
         r.d = (w + (kCutTerms + 1) * n)[t];
     };
@@ -549,7 +565,7 @@ __device__ __forceinline__ void sweeps_lds_body(const Grid &g, T sigma, const Ld
 #pragma unroll 1
     for (int it = 0; it < 6 * sweeps; ++it) {
         const int nc = R.cut_off[q + 1] - R.cut_off[q], n = nc + R.vac_off[q + 1] - R.vac_off[q], comp = q >> 1;
-        LdsRow<TW> r;
+        LdsRow<T, TA> r;
         uint32_t p = pn;
         T fv = f[comp * P + p];
         if (tid < nc) load_row(r, q, tid);
@@ -580,7 +596,7 @@ template <class T, bool PMC>
 __global__ void __launch_bounds__(kLdsThreads)
 k_sweeps_lds(Grid g, T sigma, LdsRows R, const T *__restrict__ W, int sweeps, int reverse, int zero, VPtr<const T> f,
              VPtr<T> x) {
-    sweeps_lds_body<T, PMC, T>(g, sigma, R, W, sweeps, reverse, zero, f.p[blockIdx.x], x.p[blockIdx.x],
+    sweeps_lds_body<T, PMC, T>(g, sigma, R, CutTab<T, T>{W, W}, sweeps, reverse, zero, f.p[blockIdx.x], x.p[blockIdx.x],
                           reinterpret_cast<T *>(lds_raw));
 }
 
@@ -1808,11 +1824,13 @@ __global__ void k_copy_masked(int64_t n, const double *__restrict__ in, const do
 
 // ---------------------------------------------------------------------------
 // Batched V-cycle steps (see BJob): the same bodies as the single-operator
-// kernels, the cut rows with FP64 tables and sums: FP32 weights round 15
-// numbers per row, and the fused V-cycle of smooth fields was left with an
-// error of 6.5e-8 (rms against FP64, eight cavities of 16^3 to 64^3), where
-// rows formed from the fractions had 5.1e-8; these leave 4.4e-8, for 1,005 us
-// instead of 918 on 16 cavities of 32^3 to 96^3.  A block finds its job in a
+// kernels.  The cut rows take the FP32 tables but for the centre weight, and
+// are summed in FP64.  With a centre weight rounded to FP32 (6 / h^2 beside
+// neighbours of 1 / h^2) and sums in FP32 the fused V-cycle of smooth fields
+// was left with an error of 6.5e-8 (rms against FP64, eight cavities of 16^3 to
+// 64^3), where rows formed from the fractions had 5.1e-8; these leave 4.6e-8
+// at the same speed (885 and 893 us for 16 cavities of 32^3 to 96^3; FP64
+// tables throughout left 4.4e-8 and took 973).  A block finds its job in a
 // table (one scalar load; a search over the jobs' offsets took a dependent
 // load per halving), and the XCDs, which blocks reach round-robin, each take
 // one run of logical blocks.
@@ -1832,16 +1850,16 @@ kb_step(const BJob *__restrict__ jobs, const int32_t *__restrict__ job_of) {
     } else if (STEP == BS_SMOOTH) {
         if (lb < J.ncut) {
             if (item < J.n)
-                smooth_cut_n<T, COMP, 1, double>(J.g, J.sigma, J.cut, J.n, J.colour, J.w, J.pair, J.s, 0, vptr1(J.in),
-                                                 vptr1(J.out), (uint32_t)item);
+                smooth_cut_n<T, COMP, 1, double>(J.g, J.sigma, J.cut, J.n, J.colour, CutTab<T, double>{J.w, J.w0}, J.pair,
+                                                 J.s, 0, vptr1(J.in), vptr1(J.out), (uint32_t)item);
         } else {
             smooth_vac_n<T, COMP, 1>(J.g, J.sigma, vptr1(J.in), vptr1(J.out), (uint32_t)(item - J.ncut * blockDim.x),
                                      J.runs, J.nruns);
         }
     } else if (STEP == BS_RESID) {
         if (lb < J.ncut) {
-            apply_cut_part<T, AK_RESID, T, double>(J.g, J.sigma, J.w, J.cut, J.n, true, (uint32_t)(item >> 6),
-                                                   (uint32_t)(item & 63), J.in, J.aux, J.out);
+            apply_cut_part<T, AK_RESID, T, double>(J.g, J.sigma, CutTab<T, double>{J.w, J.w0}, J.cut, J.n, true,
+                                                   (uint32_t)(item >> 6), (uint32_t)(item & 63), J.in, J.aux, J.out);
         } else {
             const uint32_t t = (uint32_t)(item - J.ncut * blockDim.x);
             if (t >> kRunLog >= J.nruns) return;
@@ -1862,8 +1880,8 @@ kb_step(const BJob *__restrict__ jobs, const int32_t *__restrict__ job_of) {
 __global__ void __launch_bounds__(kLdsThreads)
 kb_sweeps(const BJob *__restrict__ jobs) {
     const BJob &J = jobs[blockIdx.x];
-    sweeps_lds_body<float, false, double>(J.g, J.sigma, J.lds, J.lds.w64, J.sweeps, J.reverse, !J.reverse, J.in,
-                                          J.out, reinterpret_cast<float *>(lds_raw));
+    sweeps_lds_body<float, false, double>(J.g, J.sigma, J.lds, CutTab<float, double>{J.lds.w32, J.lds.w64}, J.sweeps,
+                                          J.reverse, !J.reverse, J.in, J.out, reinterpret_cast<float *>(lds_raw));
 }
 
 }  // namespace
